@@ -155,6 +155,7 @@ wl::Sched make_sched(const wl_ctx* ctx, const wl_ens* e, int32_t n_pts) {
   s.n_items = base * n_sub;
   s.n_wg = 0;  // set by the launcher (workgroup size depends on precision)
   s.n_xcd = 8;  // MI355X: 8 XCDs; workgroups are dealt round-robin
+  s.split = 1;  // set by the launcher
   return s;
 }
 

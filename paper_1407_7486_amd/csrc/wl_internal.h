@@ -28,6 +28,7 @@ struct Sched {
   int64_t n_items;          // G * n_sub * n_chunks
   int32_t n_wg;             // workgroups (set by the launcher)
   int32_t n_xcd;            // XCDs the dispatcher round-robins over
+  int32_t split;            // waves an item's loops are dealt to (launcher)
 };
 
 // Which part of each loop a per-loop evaluation walks: segments seg_off ..
@@ -96,10 +97,9 @@ struct ReqDesc {
 };
 
 constexpr int kWavesPerWG = 4;  // batch and per-loop kernels
-// k_average: waves per workgroup (barrier-coupled), by precision: 8 for
-// the FP32 kernels, 4 (one per SIMD) for the FP64 ones.
-constexpr int avg_waves(int prec) { return prec == 2 ? 4 : 8; }
 constexpr int kWave = 64;
+// most waves that an item's loops are dealt to (k_average, k_disc)
+constexpr int kSplitWaves = 8;
 
 // Launchers (wl_kernels.hip).  All enqueue on `stream` and return the HIP
 // launch status.

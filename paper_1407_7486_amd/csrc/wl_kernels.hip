@@ -358,17 +358,17 @@ __device__ __forceinline__ LaneF32 lane_consts(double rho, double s, double T,
 //          of A), qe_i the scale of qa_i's rounding (field_f32): the
 //          squared size of each term's rounding relative to u, the two
 //          parts of the cross product being summed apart.
-// Per-wave staging buffers of the FP32 segment walk, one of 64 segments for
-// each wave of a workgroup (every kernel that walks segments in FP32 runs
-// workgroups of at most 8 waves, fixed by its launch bounds).  One array for
-// the module, so that a kernel instantiating several walks holds one copy.
-__shared__ float4 g_stage[8][kWave];
+// `stage`: the wave's LDS staging buffer of kWave segments (unused by the
+// walks that read through scalar loads).
+constexpr bool staged_walk(int kind, bool spin, bool comp) {
+  return comp && !(kind == kSech2 && spin);
+}
 
 template <int KIND, bool SPIN, bool COMP, int EST = 0>
 __device__ __forceinline__ void loop_sums_f32(const float4* __restrict__ seg,
                                               int32_t n, const LaneF32& c,
-                                              const FieldArgs& f, double& A,
-                                              double& B, double& Q) {
+                                              const FieldArgs& f, float4* stage,
+                                              double& A, double& B, double& Q) {
   constexpr bool kSpinSum = SPIN && KIND != kConst;
   const float Rf = KIND == kSech2 ? c.R_s : c.R;
   const float Uf = KIND == kSech2 ? c.U_s : c.U;
@@ -420,10 +420,9 @@ __device__ __forceinline__ void loop_sums_f32(const float4* __restrict__ seg,
   };
   Acc s_ = {0.0f, 0.0f, 0.0f};  // plain mode: FP32 sums
   int32_t i = 0;
-  if constexpr (COMP && !(KIND == kSech2 && SPIN)) {
-    const int32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if constexpr (staged_walk(KIND, SPIN, COMP)) {
     const int32_t ln = threadIdx.x % kWave;
-    float4* buf = g_stage[wv];
+    float4* buf = stage;
     for (; i + 64 <= n; i += 64) {
       // every lane's reads of the previous 64 are issued before the buffer
       // is refilled, and the refill before any read (LDS operations of a
@@ -769,15 +768,18 @@ __device__ __forceinline__ double phase_l2(double Q, int32_t n, double R, double
 }
 
 // Per-loop contributions to the scale and rounding accumulators of a mean:
-//   a += |w| max(1, S)                       (the scale M_S, times N_l)
-//   v += (sin(phi) cosh(S) l2)^2             (the random rounding of the
+//   da = |w| max(1, S)                       (the scale M_S, times N_l)
+//   dv = (sin(phi) cosh(S) l2)^2             (the random rounding of the
 //                                              mean, times N_l^2 / (K u)^2)
-// (cosh(S) l2 clamped at 1e150 so that v stays finite).
+// (cosh(S) l2 clamped at 1e150 so that dv stays finite).  Rounded products,
+// never fused into a caller's sum: a sum formed by another wave from stored
+// terms then gets the same bits.
 __device__ __forceinline__ void loop_scale(double w, double S, double cw, double ch,
-                                           double l2, double& a, double& v) {
-  a += fabs(w) * fmax(1.0, S);
+                                           double l2, double& da, double& dv) {
+#pragma clang fp contract(off)
+  da = fabs(w) * fmax(1.0, S);
   const double x = fmin(ch * l2, 1e150);
-  v += fmax(0.0, 1.0 - cw * cw) * (x * x);
+  dv = fmax(0.0, 1.0 - cw * cw) * (x * x);
 }
 
 // The three levels of the discretisation estimate (Sec. 4.1) from the sums
@@ -846,15 +848,15 @@ __device__ __forceinline__ int32_t tile_point(int32_t p, int32_t n_T, int32_t n_
   return j * n_T + k;
 }
 
-// One loop at this lane's grid point: its w is added to acc, and its
-// contributions to the scale and rounding accumulators of the mean to a, v
-// (loop_scale).  nrm: the loop's norms sqrt(sum c^2), sqrt(sum d_y^2).
+// One loop at this lane's grid point: its w, and its contributions da, dv to
+// the scale and rounding accumulators of the mean (loop_scale).  nrm: the
+// loop's norms sqrt(sum c^2), sqrt(sum d_y^2).
 template <int KIND, bool SPIN, int PREC>
-__device__ __forceinline__ void avg_loop(const float4* __restrict__ seg,
-                                         const double4* __restrict__ seg64, float2 nrm,
-                                         int32_t n_ppl, int64_t l, double rho, double s,
-                                         double T, const LaneF32& c, const FieldArgs& f,
-                                         double& acc, double& a, double& v) {
+__device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
+                                           const double4* __restrict__ seg64, float2 nrm,
+                                           int32_t n_ppl, int64_t l, double rho, double s,
+                                           double T, const LaneF32& c, const FieldArgs& f,
+                                           float4* stage, double& w, double& da, double& dv) {
   double A, B, Q, phi, S, cw, ch, R, U;
   if constexpr (PREC == 2) {
     loop_sums_f64<KIND, SPIN, true>(SegArray64{seg64 + l * n_ppl}, n_ppl, rho, s, f, A, B,
@@ -865,15 +867,28 @@ __device__ __forceinline__ void avg_loop(const float4* __restrict__ seg,
     if constexpr (PREC == 3)
       loop_sums_f32k<KIND, SPIN>(seg + l * n_ppl, n_ppl, c, f, A, B, Q);
     else
-      loop_sums_f32<KIND, SPIN, PREC == 0, 1>(seg + l * n_ppl, n_ppl, c, f, A, B, Q);
+      loop_sums_f32<KIND, SPIN, PREC == 0, 1>(seg + l * n_ppl, n_ppl, c, f, stage, A, B, Q);
     R = KIND == kSech2 ? c.R_s : c.R;
     U = KIND == kSech2 ? c.U_s : c.U;
   }
   epilogue_parts<SPIN, PREC>(A, B, T, n_ppl, f, phi, S, cw, ch);
-  const double w = wprod<SPIN>(cw, ch);
+  w = wprod<SPIN>(cw, ch);
+  loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, PREC == 2 ? f.cphi : f.cphi32), da,
+             dv);
+}
+
+// The same, added to the sums of an item.
+template <int KIND, bool SPIN, int PREC>
+__device__ __forceinline__ void avg_loop(const float4* __restrict__ seg,
+                                         const double4* __restrict__ seg64, float2 nrm,
+                                         int32_t n_ppl, int64_t l, double rho, double s,
+                                         double T, const LaneF32& c, const FieldArgs& f,
+                                         float4* stage, double& acc, double& a, double& v) {
+  double w, da, dv;
+  loop_terms<KIND, SPIN, PREC>(seg, seg64, nrm, n_ppl, l, rho, s, T, c, f, stage, w, da, dv);
   acc += w;
-  loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, PREC == 2 ? f.cphi : f.cphi32), a,
-             v);
+  a += da;
+  v += dv;
 }
 
 // The domain of a grid point: rho_cm >= 0 and T > 0, both finite.
@@ -912,7 +927,7 @@ __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
                                          const double4* __restrict__ seg64,
                                          const float2* __restrict__ norm, int32_t n_ppl,
                                          const ReqDesc& q, int64_t loops_per_group,
-                                         int64_t item) {
+                                         int64_t item, float4* stage) {
   const int32_t lane = threadIdx.x % kWave;
   const ItemRange r = item_range(item, q.n_chunks, q.n_sub, loops_per_group,
                                  q.loops_per_sub);
@@ -927,7 +942,8 @@ __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
 
   double acc = 0.0, a = 0.0, v = 0.0;
   for (int64_t l = r.l0; l < r.l1; ++l)
-    avg_loop<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, q.f, acc, a, v);
+    avg_loop<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, q.f, stage, acc, a,
+                               v);
   if (valid) {
     const int64_t o = r.gs * n_pts + pg;
     q.out[o] = acc;
@@ -1123,48 +1139,85 @@ __device__ __forceinline__ void scale_point(const double* __restrict__ pa,
 }
 
 // ------------------------------------------------------------- kernels
-// One workgroup = avg_waves(PREC) consecutive items, normally chunks of one
-// (group, sub-range): they walk the same loops, and a barrier after every
-// loop keeps them in step so that a loop's segments are fetched from HBM
-// about once per workgroup and then served from the caches.  Every wave,
-// including padding waves past the last item, runs the same
-// loops_per_sub barrier iterations.
+// One workgroup = one item, its loops dealt to the workgroup's sc.split
+// waves (1 to 8): round k gives wave w loop l0 + k split + w.  The loops'
+// terms go through LDS (two buffers, so one barrier per round) and the first
+// wave adds them in loop order: the sums do not depend on the split.
+// Why waves share an item's chunk rather than its loops: the walk costs more
+// where a wave has lanes near the axis, and the barrier makes the waves of a
+// workgroup wait for the slowest; waves of one chunk have the same lanes.
+// With 8 chunks per workgroup and one loop at a time the sech^2 spinor
+// workload (65536 x 4096, 64 x 64) took 548 ms, in this form 508 ms, the
+// Gaussian spinor at 16384 x 4096 97 and 88 ms.  And an item of 8 loops is
+// walked by 8 waves, so that a small launch spreads over the chip: 2048 x
+// 4096 on 32 x 32 in FP64 23.3 -> 18.5 ms, 1024 x 1024 on 8 x 16 in the
+// constant field 193 -> 37 us (loop_split).  A loop's segments are
+// read by every chunk's workgroup at about the same time, from the XCD's L2.
 // Register budget 64 VGPRs, 8 waves per SIMD: the FP32 kernels (77
 // uncapped, 6 waves) then spill three per-item values, reloaded after the
-// item's last loop; the FP64 ones need at most 60 (their polynomial
-// coefficients are scalar operands), 8 waves in workgroups of 4.
+// item's last loop; the FP64 ones need at most 62 (their polynomial
+// coefficients are scalar operands).
+// Dynamic LDS: per wave a staging buffer of kWave segments, then the terms.
 template <int KIND, bool SPIN, int PREC>
-__global__ __launch_bounds__(avg_waves(PREC) * kWave)
+__global__ __launch_bounds__(kSplitWaves * kWave)
 __attribute__((amdgpu_waves_per_eu(8))) void k_average(
     const float4* __restrict__ seg, const double4* __restrict__ seg64,
     const float2* __restrict__ norm, int32_t n_ppl,
     const double* __restrict__ rho_g, const double* __restrict__ T_g,
     int32_t n_T, int32_t n_pts, FieldArgs f, Sched sc,
     double* __restrict__ out, double* __restrict__ out_a, double* __restrict__ out_v) {
+  extern __shared__ float4 split_lds[];
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
-  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd) * avg_waves(PREC) + wave;
-  const bool live = item < sc.n_items;
-  ItemRange r = item_range(live ? item : 0, sc.n_chunks, sc.n_sub, sc.loops_per_group,
-                           sc.loops_per_sub);
-  if (!live) r.l1 = r.l0;
-
+  const int32_t split = sc.split;
+  float4* stage = split_lds + wave * kWave;
+  double* terms = (double*)(split_lds + split * kWave);  // [2][split][3][kWave]
+  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
+  const ItemRange r = item_range(item, sc.n_chunks, sc.n_sub, sc.loops_per_group,
+                                 sc.loops_per_sub);
   const int32_t p = r.chunk * kWave + lane;
-  const bool valid = live && p < n_pts;
-  const int32_t pg = tile_point(p < n_pts ? p : n_pts - 1, n_T, n_pts);
+  const bool valid = p < n_pts;
+  const int32_t pg = tile_point(valid ? p : n_pts - 1, n_T, n_pts);
   const double rho = rho_g[pg / n_T];
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
 
   double acc = 0.0, a = 0.0, v = 0.0;
-  for (int64_t k = 0; k < sc.loops_per_sub; ++k) {
-    const int64_t l = r.l0 + k;
+  double* mine = terms + wave * 3 * kWave + lane;
+  double* all = terms + lane;
+  const int32_t other = split * 3 * kWave;  // from one buffer to the other
+  for (int64_t l0 = r.l0; l0 < r.l1; l0 += split) {
+    const int64_t l = l0 + wave;
+    double w, da, dv;
     if (l < r.l1)
-      avg_loop<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, f, acc, a, v);
+      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, f, stage, w,
+                                   da, dv);
+    if (split == 1) {
+      acc += w;
+      a += da;
+      v += dv;
+      continue;
+    }
+    if (l < r.l1) {
+      mine[0] = w;
+      mine[kWave] = da;
+      mine[2 * kWave] = dv;
+    }
     __syncthreads();
+    if (wave == 0) {
+      const int32_t n = r.l1 - l0 < split ? (int32_t)(r.l1 - l0) : split;
+      for (int32_t q = 0; q < n; ++q) {
+        acc += all[3 * q * kWave];
+        a += all[(3 * q + 1) * kWave];
+        v += all[(3 * q + 2) * kWave];
+      }
+    }
+    const int32_t step = mine < terms + other ? other : -other;
+    mine += step;
+    all += step;
   }
-  if (valid) {
+  if (valid && wave == 0) {
     const int64_t o = r.gs * n_pts + pg;
     // a grid point outside the domain (device grids are not validated on
     // the host) gives NaN, whatever its arithmetic produced
@@ -1224,45 +1277,77 @@ __global__ __launch_bounds__(256) void k_scale(const double* __restrict__ pa,
   flags[p] = esc ? 1 : 0;
 }
 
-// Discretisation estimate (Sec. 4.1): the schedule, workgroup shape and
-// barrier of k_average, with the loop split into its circle, square and
-// triangle sub-loops (from the sub-loop segment array, `sub` for the FP32
-// paths, `sub64` for FP64) and three accumulators, one per level (N, N/2,
-// N/4).  With `full`, the N level is the whole loop (segment array `seg` or
-// `seg64`), which doubles the segment work.  Output level k of item gs lands
-// in out[(k * G * n_sub + gs) * n_pts + p].
-// The FP32 kernels are held to 80 VGPRs (6 waves per SIMD, three 8-wave
-// workgroups per CU): their three sets of sums need ~100, which would leave
-// room for two workgroups, and the few values spilled to scratch (live
-// across the sub-loop walks, not inside them) cost less than the lost
-// occupancy.  The FP64 kernels need at most 75 and run at the same 6
-// waves per SIMD, spilling nothing inside a segment walk.
+// The three levels' terms of one loop at this lane's grid point.
 template <int KIND, bool SPIN, int PREC>
-__global__ __launch_bounds__(avg_waves(PREC) * kWave)
+__device__ __forceinline__ void disc_terms(const float4* __restrict__ seg,
+                                           const float4* __restrict__ sub,
+                                           const double4* __restrict__ seg64,
+                                           const double4* __restrict__ sub64, int32_t n_ppl,
+                                           int64_t l, double rho, double s, double T,
+                                           const LaneF32& c, const FieldArgs& f, bool full,
+                                           double& w1, double& w2, double& w4) {
+  const int32_t h = n_ppl / 2, q = n_ppl / 4;
+  double Ac, Bc, As, Bs, At, Bt;
+  if constexpr (PREC == 2) {
+    const double4* u = sub64 + l * n_ppl;
+    loop_sums_f64seg<KIND, SPIN>(u, h, rho, s, f, Ac, Bc);
+    loop_sums_f64seg<KIND, SPIN>(u + h, q, rho, s, f, As, Bs);
+    loop_sums_f64seg<KIND, SPIN>(u + h + q, q, rho, s, f, At, Bt);
+  } else {
+    const float4* u = sub + l * n_ppl;
+    double Q;
+    loop_sums_f32<KIND, SPIN, PREC == 0>(u, h, c, f, Ac, Bc, Q);
+    loop_sums_f32<KIND, SPIN, PREC == 0>(u + h, q, c, f, As, Bs, Q);
+    loop_sums_f32<KIND, SPIN, PREC == 0>(u + h + q, q, c, f, At, Bt, Q);
+  }
+  w1 = 0.0;
+  disc_levels<SPIN, PREC>(Ac, Bc, As, Bs, At, Bt, T, h, q, f, full, w1, w2, w4);
+  if (full) {
+    double A, B, phi, S;
+    if constexpr (PREC == 2) {
+      loop_sums_f64seg<KIND, SPIN>(seg64 + l * n_ppl, n_ppl, rho, s, f, A, B);
+    } else {
+      double Q;
+      loop_sums_f32<KIND, SPIN, PREC == 0>(seg + l * n_ppl, n_ppl, c, f, A, B, Q);
+    }
+    w1 = epilogue<SPIN, PREC>(A, B, T, n_ppl, f, phi, S);
+  }
+}
+
+// Discretisation estimate (Sec. 4.1): the schedule and workgroup shape of
+// k_average (one item, its loops dealt to the workgroup's waves), with the
+// loop split into its circle, square and triangle sub-loops (from the
+// sub-loop segment array, `sub` for the FP32 paths, `sub64` for FP64) and
+// three accumulators, one per level (N, N/2, N/4).  With `full`, the N level
+// is the whole loop (segment array `seg` or `seg64`), which doubles the
+// segment work.  Output level k of item gs lands in
+// out[(k * G * n_sub + gs) * n_pts + p].
+// The FP32 kernels are held to 80 VGPRs (6 waves per SIMD): their three sets
+// of sums need ~100, and the few values spilled to scratch (live across the
+// sub-loop walks, not inside them) cost less than the lost occupancy.  The
+// FP64 kernels need at most 76 and run at the same 6 waves per SIMD,
+// spilling nothing inside a segment walk.  4096 x 2048 loops on 32 x 32,
+// sech^2 spinor: 4.65 ms with 8 chunks per workgroup, 4.21 ms in this form.
+template <int KIND, bool SPIN, int PREC>
+__global__ __launch_bounds__(kSplitWaves * kWave)
 __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
     const float4* __restrict__ seg, const float4* __restrict__ sub,
     const double4* __restrict__ seg64, const double4* __restrict__ sub64, int32_t n_ppl,
     const double* __restrict__ rho_g, const double* __restrict__ T_g,
     int32_t n_T, int32_t n_pts, FieldArgs f, Sched sc, int32_t full,
     double* __restrict__ out) {
+  extern __shared__ float4 split_lds[];
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
-  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd) * avg_waves(PREC) + wave;
-  const bool live = item < sc.n_items;
-  const int64_t it = live ? item : 0;
-  const int32_t chunk = (int32_t)(it % sc.n_chunks);
-  const int64_t gs = it / sc.n_chunks;  // g * n_sub + sub
-  const int64_t g = gs / sc.n_sub;
-  const int64_t sr = gs % sc.n_sub;
-  const int64_t l0 = g * sc.loops_per_group + sr * sc.loops_per_sub;
-  int64_t l1 = l0 + sc.loops_per_sub;
-  const int64_t gend = (g + 1) * sc.loops_per_group;
-  if (l1 > gend) l1 = gend;
-  if (!live) l1 = l0;
-
-  const int32_t p = chunk * kWave + lane;
-  const bool valid = live && p < n_pts;
-  const int32_t pg = tile_point(p < n_pts ? p : n_pts - 1, n_T, n_pts);
+  const int32_t split = sc.split;
+  float4* stage = split_lds + wave * kWave;
+  double* terms = (double*)(split_lds + split * kWave);  // [2][split][3][kWave]
+  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
+  const ItemRange r = item_range(item, sc.n_chunks, sc.n_sub, sc.loops_per_group,
+                                 sc.loops_per_sub);
+  const int32_t p = r.chunk * kWave + lane;
+  const bool valid = p < n_pts;
+  const int32_t pg = tile_point(valid ? p : n_pts - 1, n_T, n_pts);
   const double rho = rho_g[pg / n_T];
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
@@ -1270,9 +1355,13 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   const int32_t h = n_ppl / 2, q = n_ppl / 4;
 
   double acc1 = 0.0, acc2 = 0.0, acc4 = 0.0;
-  for (int64_t k = 0; k < sc.loops_per_sub; ++k) {
-    const int64_t l = l0 + k;
-    if (l < l1) {
+  double* mine = terms + wave * 3 * kWave + lane;
+  double* all = terms + lane;
+  const int32_t other = split * 3 * kWave;  // from one buffer to the other
+  for (int64_t l0 = r.l0; l0 < r.l1; l0 += split) {
+    const int64_t l = l0 + wave;
+    double w1 = 0.0, w2, w4;
+    if (l < r.l1) {
       double Ac, Bc, As, Bs, At, Bt;
       if constexpr (PREC == 2) {
         const double4* u = sub64 + l * n_ppl;
@@ -1282,11 +1371,10 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
       } else {
         const float4* u = sub + l * n_ppl;
         double Q;
-        loop_sums_f32<KIND, SPIN, PREC == 0>(u, h, c, f, Ac, Bc, Q);
-        loop_sums_f32<KIND, SPIN, PREC == 0>(u + h, q, c, f, As, Bs, Q);
-        loop_sums_f32<KIND, SPIN, PREC == 0>(u + h + q, q, c, f, At, Bt, Q);
+        loop_sums_f32<KIND, SPIN, PREC == 0>(u, h, c, f, stage, Ac, Bc, Q);
+        loop_sums_f32<KIND, SPIN, PREC == 0>(u + h, q, c, f, stage, As, Bs, Q);
+        loop_sums_f32<KIND, SPIN, PREC == 0>(u + h + q, q, c, f, stage, At, Bt, Q);
       }
-      double w1 = 0.0, w2, w4;
       disc_levels<SPIN, PREC>(Ac, Bc, As, Bs, At, Bt, T, h, q, f, full != 0, w1, w2, w4);
       if (full) {
         double A, B, phi, S;
@@ -1294,21 +1382,40 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
           loop_sums_f64seg<KIND, SPIN>(seg64 + l * n_ppl, n_ppl, rho, s, f, A, B);
         } else {
           double Q;
-          loop_sums_f32<KIND, SPIN, PREC == 0>(seg + l * n_ppl, n_ppl, c, f, A, B, Q);
+          loop_sums_f32<KIND, SPIN, PREC == 0>(seg + l * n_ppl, n_ppl, c, f, stage, A, B, Q);
         }
         w1 = epilogue<SPIN, PREC>(A, B, T, n_ppl, f, phi, S);
       }
+    }
+    if (split == 1) {
       acc1 += w1;
       acc2 += w2;
       acc4 += w4;
+      continue;
+    }
+    if (l < r.l1) {
+      mine[0] = w1;
+      mine[kWave] = w2;
+      mine[2 * kWave] = w4;
     }
     __syncthreads();
+    if (wave == 0) {
+      const int32_t n = r.l1 - l0 < split ? (int32_t)(r.l1 - l0) : split;
+      for (int32_t k = 0; k < n; ++k) {
+        acc1 += all[3 * k * kWave];
+        acc2 += all[(3 * k + 1) * kWave];
+        acc4 += all[(3 * k + 2) * kWave];
+      }
+    }
+    const int32_t step = mine < terms + other ? other : -other;
+    mine += step;
+    all += step;
   }
-  if (valid) {
+  if (valid && wave == 0) {
     const int64_t L = sc.n_items / sc.n_chunks;  // G * n_sub
-    out[gs * n_pts + pg] = acc1;
-    out[(L + gs) * n_pts + pg] = acc2;
-    out[(2 * L + gs) * n_pts + pg] = acc4;
+    out[r.gs * n_pts + pg] = acc1;
+    out[(L + r.gs) * n_pts + pg] = acc2;
+    out[(2 * L + r.gs) * n_pts + pg] = acc4;
   }
 }
 
@@ -1342,6 +1449,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
     const float4* __restrict__ seg, const double4* __restrict__ seg64,
     const float2* __restrict__ norm, int32_t n_ppl, const BatchHeader* __restrict__ hdr,
     unsigned int* __restrict__ counter, int64_t loops_per_group) {
+  __shared__ float4 stage[kWavesPerWG][kWave];
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = (int32_t)hdr->n_reqs;
@@ -1358,7 +1467,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
     const ReqDesc& q = reqs[lo];
     const int64_t li = item - q.item_begin;
     switch (q.f.kind * 2 + q.spin) {
-#define WL_ITEM(K, SP) run_item<K, SP, PREC>(seg, seg64, norm, n_ppl, q, loops_per_group, li)
+#define WL_ITEM(K, SP) \
+  run_item<K, SP, PREC>(seg, seg64, norm, n_ppl, q, loops_per_group, li, stage[wave])
       case 0: WL_ITEM(kConst, false); break;
       case 1: WL_ITEM(kConst, true); break;
       case 2: WL_ITEM(kSech2, false); break;
@@ -1584,14 +1694,16 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
   const double T = T_g[pp % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
+  __shared__ float4 stage[staged_walk(KIND, SPIN, PREC == 0) ? kWavesPerWG : 1][kWave];
   double A, B, Q, phi, S;
   if constexpr (PREC == 2) {
     loop_sums_f64seg<KIND, SPIN>(seg64 + l * n_ppl + sl.seg_off, sl.m, rho, s, f, A, B);
   } else if constexpr (PREC == 3) {
     loop_sums_f32k<KIND, SPIN>(seg + l * n_ppl + sl.seg_off, sl.m, c, f, A, B, Q);
   } else {
-    loop_sums_f32<KIND, SPIN, PREC == 0, PREC == 0 ? 2 : 0>(seg + l * n_ppl + sl.seg_off,
-                                                            sl.m, c, f, A, B, Q);
+    loop_sums_f32<KIND, SPIN, PREC == 0, PREC == 0 ? 2 : 0>(
+        seg + l * n_ppl + sl.seg_off, sl.m, c, f,
+        stage[staged_walk(KIND, SPIN, PREC == 0) ? wave : 0], A, B, Q);
   }
   double w = epilogue<SPIN, PREC>(A, B, T, sl.m, f, phi, S);
   if constexpr (PREC == 0) {
@@ -1801,6 +1913,26 @@ __global__ __launch_bounds__(256) void k_disc_finish(double* __restrict__ sums,
 }
 
 // ------------------------------------------------------------ dispatch
+// Over how many waves the loops of an item are dealt, the waves of its
+// workgroup: one per loop, at most 8.  Measured over 1 to 16 waves, rows of
+// 1 to 32 loops and 32 to 131072 items, 8 is the fastest or within 1% of it
+// wherever a row has 8 loops, also where it leaves waves idle in a last
+// round (9 loops, 4096 items of 1024 segments: 1.38 ms, with 3 waves 1.50,
+// with 1 1.72): workgroups of whole multiples of 4 waves load the 4 SIMDs
+// evenly, and many short workgroups even out the chunks' unequal costs.  The
+// sums do not depend on the split.  A grid whose threads would not fit 32
+// bits takes fewer waves.
+int32_t loop_split(const Sched& sc) {
+  int64_t s = sc.loops_per_sub < kSplitWaves ? sc.loops_per_sub : kSplitWaves;
+  while (s > 1 && sc.n_items * s > ((int64_t)1 << 25)) s >>= 1;
+  return (int32_t)s;
+}
+
+// Dynamic LDS of a workgroup of `split` waves (k_average, k_disc).
+size_t split_lds_bytes(int32_t split) {
+  return (size_t)split * kWave * (sizeof(float4) + (split > 1 ? 6 * sizeof(double) : 0));
+}
+
 template <int KIND, bool SPIN, int PREC>
 hipError_t launch_avg_t(const FieldArgs& f, const float4* seg, const double4* seg64,
                         const float2* norm, int32_t n_ppl, const double* rho,
@@ -1809,10 +1941,11 @@ hipError_t launch_avg_t(const FieldArgs& f, const float4* seg, const double4* se
   if ((PREC == 2 ? seg64 == nullptr : seg == nullptr) || norm == nullptr)
     return hipErrorInvalidValue;
   Sched s = s0;
-  s.n_wg = (int32_t)((s.n_items + avg_waves(PREC) - 1) / avg_waves(PREC));
-  hipLaunchKernelGGL((k_average<KIND, SPIN, PREC>), dim3(s.n_wg),
-                     dim3(avg_waves(PREC) * kWave), 0, st, seg, seg64, norm, n_ppl, rho, T,
-                     n_T, n_pts, f, s, out, out_a, out_v);
+  s.split = loop_split(s);
+  s.n_wg = (int32_t)s.n_items;
+  hipLaunchKernelGGL((k_average<KIND, SPIN, PREC>), dim3(s.n_wg), dim3(s.split * kWave),
+                     split_lds_bytes(s.split), st, seg, seg64, norm, n_ppl, rho, T, n_T, n_pts,
+                     f, s, out, out_a, out_v);
   return hipGetLastError();
 }
 
@@ -1844,10 +1977,11 @@ hipError_t launch_disc_t(const FieldArgs& f, const float4* seg, const float4* su
                 : (sub == nullptr || (full && seg == nullptr)))
     return hipErrorInvalidValue;
   Sched s = s0;
-  s.n_wg = (int32_t)((s.n_items + avg_waves(PREC) - 1) / avg_waves(PREC));
-  hipLaunchKernelGGL((k_disc<KIND, SPIN, PREC>), dim3(s.n_wg),
-                     dim3(avg_waves(PREC) * kWave), 0, st, seg, sub, seg64, sub64, n_ppl, rho,
-                     T, n_T, n_pts, f, s, full, out);
+  s.split = loop_split(s);
+  s.n_wg = (int32_t)s.n_items;
+  hipLaunchKernelGGL((k_disc<KIND, SPIN, PREC>), dim3(s.n_wg), dim3(s.split * kWave),
+                     split_lds_bytes(s.split), st, seg, sub, seg64, sub64, n_ppl, rho, T, n_T,
+                     n_pts, f, s, full, out);
   return hipGetLastError();
 }
 
