@@ -222,6 +222,7 @@ bool build_batch(const wl_ens* ens, const wl_request* const* reqs, const FieldAr
   int64_t* d_esc_begin = (int64_t*)(((uintptr_t)(d_count + n) + 7) & ~(uintptr_t)7);
   hdr->esc_begin = d_esc_begin;
   int64_t items = 0, sums = 0, pts = 0, part = 0, acc = 0, go = 0;
+  int32_t tiles = 0;
   for (int32_t i = 0; i < n; ++i) {
     const wl_request& q = *reqs[i];
     const ReqPlan& pl = plans[i];
@@ -249,6 +250,8 @@ bool build_batch(const wl_ens* ens, const wl_request* const* reqs, const FieldAr
     e.n_T = q.n_T;
     e.n_pts = pl.n_pts;
     e.spin = q.spin;
+    e.tile_begin = tiles;
+    tiles += (pl.n_pts + kFinishPts - 1) / kFinishPts;
     desc[i] = e;
     lay->sums_begin.push_back(sums);
     lay->pts_begin.push_back(pts);
@@ -673,9 +676,8 @@ static size_t eval_scratch_bytes(const wl::Sched& s, int64_t n_groups, int32_t n
 }
 
 // Enqueue one evaluation; grid and outputs are device memory: the main
-// kernel, the per-point scale and rounding estimate (and for WL_FP32C the
-// FP64 recomputation of the flagged points), the sub-range reduction and
-// the statistics.  With `noalloc` the call allocates nothing: the scratch
+// kernel, then the group sums, statistics, scale and rounding estimate per
+// point (and for WL_FP32C the FP64 recomputation of the flagged points).  With `noalloc` the call allocates nothing: the scratch
 // is the static array (ctx->d_noalloc), the FP64 segment array must exist
 // already, and no timing events are recorded.
 static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& fa,
@@ -729,16 +731,9 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
     if (e == hipSuccess) ctx->n_timed++;
   }
   if (e == hipSuccess)
-    e = wl::launch_scale_escalate(precision, spin, fa, ens->d_x, ens->d_y, ens->n_ppl, d_rho,
-                                  d_T, n_T, n_pts, s, ens->n_loops, p_a, p_v, scale,
-                                  o.fp_err, flags, list, p_w, ctx->stream);
-  if (e == hipSuccess && s.n_sub > 1)
-    e = wl::launch_reduce_sub(p_w, ens->n_groups, s.n_sub, n_pts, o.sums, ctx->stream);
-  if (e == hipSuccess && (o.mean || o.err))
-    e = wl::launch_stats(o.sums, ens->n_groups, n_pts, ens->n_loops, o.mean, o.err,
-                         ctx->stream);
-  if (e == hipSuccess && o.escalated)
-    e = hipMemcpyAsync(o.escalated, flags, n_pts, hipMemcpyDeviceToDevice, ctx->stream);
+    e = wl::launch_finish(precision, spin, fa, ens->d_x, ens->d_y, ens->n_ppl, d_rho, d_T, n_T,
+                          n_pts, s, ens->n_groups, ens->n_loops, p_w, p_a, p_v, o.sums, o.mean,
+                          o.err, scale, o.fp_err, flags, o.escalated, list, ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "kernel launch");
   return WL_OK;
 }
@@ -1132,12 +1127,9 @@ int wl_discretisation(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
     e = hipEventRecord(ev1, ctx->stream);
     if (e == hipSuccess) ctx->n_timed++;
   }
-  if (e == hipSuccess && s.n_sub > 1)
-    e = wl::launch_reduce_sub(level_out, 3 * (int32_t)G, s.n_sub, (int32_t)n_pts, d_sums,
-                              ctx->stream);
   if (e == hipSuccess)
-    e = wl::launch_disc_finish(d_sums, (int32_t)G, (int32_t)n_pts, ens->n_loops, d_mean,
-                               d_err, d_delta, ctx->stream);
+    e = wl::launch_disc_finish(level_out, d_sums, (int32_t)G, s.n_sub, (int32_t)n_pts,
+                               ens->n_loops, d_mean, d_err, d_delta, ctx->stream);
   if (e == hipSuccess && group_sums)
     e = hipMemcpyAsync(group_sums, d_sums, sums_n * sizeof(double), hipMemcpyDeviceToHost,
                        ctx->stream);

@@ -93,11 +93,13 @@ struct ReqDesc {
   int64_t sums_begin;   // offset of [G][n_pts] group sums in the batch
   int64_t pts_begin;    // offset of [n_pts] means / errors in the batch
   int32_t n_sub, n_chunks, n_T, n_pts;
-  int32_t spin, pad;
+  int32_t spin;
+  int32_t tile_begin;   // first finishing tile (kFinishPts points) in the batch
 };
 
 constexpr int kWavesPerWG = 4;  // batch and per-loop kernels
 constexpr int kWave = 64;
+constexpr int kFinishPts = 16;  // grid points per tile of the finishing kernels
 // most waves that an item's loops are dealt to (k_average, k_disc)
 constexpr int kSplitWaves = 8;
 
@@ -130,18 +132,22 @@ hipError_t launch_average(int precision, int spin, const FieldArgs& f,
                           int32_t n_T, int32_t n_pts, const Sched& s, double* d_out,
                           double* d_out_a, double* d_out_v, hipStream_t stream);
 
-// Per grid point from d_out_a, d_out_v: the scale (M_S), the rounding-error
-// estimate of the mean and the FP64 recomputation flag (scale and fp_err
-// may be NULL).  Then, for WL_FP32C, the flagged points compacted into
-// d_list [n_pts + 1] (the last entry their count) and the FP64 recomputation
-// of their item sums in d_out from the raw points d_x, d_y.
-hipError_t launch_scale_escalate(int precision, int spin, const FieldArgs& f,
-                                 const float* d_x, const float* d_y, int32_t n_ppl,
-                                 const double* d_rho, const double* d_T, int32_t n_T,
-                                 int32_t n_pts, const Sched& s, int64_t n_loops,
-                                 const double* d_out_a, const double* d_out_v,
-                                 double* d_scale, double* d_fp_err, uint8_t* d_flags,
-                                 int32_t* d_list, double* d_out, hipStream_t stream);
+// The results of an evaluation from its item sums d_out, d_out_a, d_out_v:
+// the group sums d_sums (d_out itself when n_sub == 1), means and errors
+// (either may be NULL), the scale (M_S), the rounding-error estimate
+// (d_fp_err may be NULL) and the FP64 recomputation flags d_flags [n_pts]
+// (also to d_flags_out if set).  For WL_FP32C then the flagged points
+// compacted into d_list [n_pts + 1] (the last entry their count), the FP64
+// recomputation of their item sums in d_out from the raw points d_x, d_y, and
+// their results again.
+hipError_t launch_finish(int precision, int spin, const FieldArgs& f, const float* d_x,
+                         const float* d_y, int32_t n_ppl, const double* d_rho,
+                         const double* d_T, int32_t n_T, int32_t n_pts, const Sched& s,
+                         int32_t n_groups, int64_t n_loops, double* d_out,
+                         const double* d_out_a, const double* d_out_v, double* d_sums,
+                         double* d_mean, double* d_err, double* d_scale, double* d_fp_err,
+                         uint8_t* d_flags, uint8_t* d_flags_out, int32_t* d_list,
+                         hipStream_t stream);
 
 // The segment array of the precision asked must be set: d_seg (FP32 paths)
 // or d_seg64 (FP64), whole-loop or sub-loop layout as `sl` says.
@@ -174,34 +180,26 @@ hipError_t launch_disc(int precision, int spin, const FieldArgs& f, const float4
                        int32_t n_T, int32_t n_pts, const Sched& s, int32_t full,
                        double* d_out, hipStream_t stream);
 
-// d_sums [4][G][n_pts] with levels 0..2 filled: writes level 3 (the
-// extrapolation), the means and errors [4][n_pts] and delta [n_pts] (each
-// output may be NULL but d_sums).
-hipError_t launch_disc_finish(double* d_sums, int32_t n_groups, int32_t n_pts,
-                              int64_t n_loops, double* d_mean, double* d_err,
-                              double* d_delta, hipStream_t stream);
+// From the level sums d_part [3][G n_sub][n_pts]: the group sums d_sums
+// [4][G][n_pts] (its levels 0..2 are d_part itself when n_sub == 1; level 3
+// is the extrapolation), the means and errors [4][n_pts] and delta [n_pts]
+// (each may be NULL).
+hipError_t launch_disc_finish(const double* d_part, double* d_sums, int32_t n_groups,
+                              int32_t n_sub, int32_t n_pts, int64_t n_loops, double* d_mean,
+                              double* d_err, double* d_delta, hipStream_t stream);
 
-// Batched evaluation: counter reset, persistent item kernel, scale and
-// escalation flags, (WL_FP32C) persistent FP64 recomputation of the flagged
-// points, sub-range reduction and statistics, all reading `d_hdr`
-// (BatchHeader followed by the descriptors, whose pointers place every
-// array).  Results at d_res: [group sums | means | errors | scales |
-// rounding estimates | flags | ...] with the sizes from the header.  Grid
-// sizes are fixed (n_wg persistent workgroups) and d_counter holds
-// kBatchCounters work counters, so the sequence can be captured once and
-// replayed.
+// Batched evaluation: counter reset, persistent item kernel, results and
+// recomputation flags, (WL_FP32C) persistent FP64 recomputation of the
+// flagged points and their results again, all reading `d_hdr` (BatchHeader
+// followed by the descriptors, whose pointers place every array).  Results at
+// d_res: [group sums | means | errors | scales | rounding estimates | flags |
+// ...] with the sizes from the header.  Grid sizes are fixed (n_wg persistent
+// workgroups) and d_counter holds kBatchCounters work counters, so the
+// sequence can be captured once and replayed.
 hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg64,
                         const float2* d_norm, const float* d_x, const float* d_y,
                         int32_t n_ppl, const void* d_hdr, int32_t n_groups, int64_t n_loops,
                         unsigned int* d_counter, double* d_res, int32_t n_wg,
-                        hipStream_t stream);
-
-hipError_t launch_reduce_sub(const double* d_partial, int32_t n_groups,
-                             int32_t n_sub, int32_t n_pts, double* d_sums,
-                             hipStream_t stream);
-
-hipError_t launch_stats(const double* d_sums, int32_t n_groups, int32_t n_pts,
-                        int64_t n_loops, double* d_mean, double* d_err,
                         hipStream_t stream);
 
 }  // namespace wl

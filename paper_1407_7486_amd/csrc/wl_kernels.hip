@@ -1097,44 +1097,169 @@ __device__ __forceinline__ void compact_flags(const uint8_t* __restrict__ flags,
   if (threadIdx.x == 0) *count = base;
 }
 
-// Per grid point p of one evaluation, from the partial sums pa, pv
-// ([rows][n_pts], rows = G n_sub) of loop_scale's accumulators:
+// Tree sum over the slots of a finishing block: thread (slot q, point pt)
+// holds x[0 .. n); afterwards every thread holds the sums over the slots of
+// its point, added in an order fixed by the number of slots alone.
+constexpr int kFinPts = kFinishPts;  // grid points of a block's tile
+constexpr int kFinSlots = 64;        // most slots (groups walked side by side)
+template <int N>
+__device__ __forceinline__ void slot_sums(double (&x)[N]) {
+  __shared__ double red[N][kFinSlots * kFinPts];
+  const int32_t t = threadIdx.x, pt = t % kFinPts;
+#pragma unroll
+  for (int k = 0; k < N; ++k) red[k][t] = x[k];
+  __syncthreads();
+  for (int32_t h = blockDim.x / 2; h >= kFinPts; h >>= 1) {
+    if (t < h) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) red[k][t] += red[k][t + h];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = red[k][pt];
+  __syncthreads();  // red is used again by the next call
+}
+
+// Totals over the groups in group order (the mean of equal group sums then
+// carries no rounding of its own: the standard error of groups that agree to
+// the last bit is that of their sums): every slot hands in its group's sums
+// of a round, and slot k adds quantity k of the round's n groups in order
+// while the others read on (two buffers, one barrier per round).
+template <int N>
+__device__ __forceinline__ void add_in_order(const double (&S)[N], double (&tot)[N],
+                                             int32_t& buf, int32_t n) {
+  __shared__ double round[2][N][kFinSlots * kFinPts];
+  const int32_t pt = threadIdx.x % kFinPts, q = threadIdx.x / kFinPts;
+#pragma unroll
+  for (int k = 0; k < N; ++k) round[buf][k][threadIdx.x] = S[k];
+  __syncthreads();
+  if (q < N) {
+    const double* r = round[buf][q] + pt;
+    for (int32_t j = 0; j < n; ++j) tot[0] += r[j * kFinPts];
+  }
+  buf ^= 1;
+}
+// Slot k's total (in its tot[0]) of quantity k to every thread's tot[k].
+template <int N>
+__device__ __forceinline__ void share_totals(double (&tot)[N]) {
+  __shared__ double all[N][kFinPts];
+  const int32_t pt = threadIdx.x % kFinPts, q = threadIdx.x / kFinPts;
+  if (q < N) all[q][pt] = tot[0];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) tot[k] = all[k][pt];
+  __syncthreads();  // the buffers are used again by the next tile
+}
+
+// What the finishing kernels read and write for one evaluation: the items'
+// partial sums pw, pa, pv ([G n_sub][n_pts] of w and of loop_scale's terms)
+// and the results.  With n_sub == 1 pw is sums.
+struct Finish {
+  const double* pw;
+  const double* pa;
+  const double* pv;
+  double* sums;      // [G][n_pts]
+  double* mean;      // [n_pts]; each of the following may be NULL but scale
+  double* err;       // and flags
+  double* scale;
+  double* fp_err;
+  uint8_t* flags;
+  uint8_t* flags_out;
+  const int32_t* list;  // flagged points (second pass)
+  int32_t n_groups, n_sub, n_pts, prec;
+  int64_t n_loops;
+};
+
+// The results of kFinPts grid points by one block: group sums (sub-ranges in
+// order), mean and standard error of the group means (Sec. 4.2.3), and from
+// the accumulators
 //   ms  the scale M_S = (1/N_l) sum_l |w_l| max(1, S_l),
 //   fe  the stated rounding-error estimate of the mean,
 //       kPhaseK u sqrt(sum_l v_l) / N_l + kSysK u M_S (u of the precision),
 //   esc whether the point is recomputed in FP64 (compensated FP32 only):
 //       when kDecideK u sqrt(sum_l v_l) / N_l exceeds kEscalate M_S, half
-//       the mean tolerance 1e-6 M_S; the estimate then takes FP64's u.
+//       the mean tolerance 1e-6 M_S; the estimate is then that of the rows
+//       left in FP32 (esc_row_threshold).
 // kDecideK is the decision's calibration: the largest mean error measured
 // against the FP64 oracle on the stress fields (1024 loops of 8192 points,
 // every sech^2 tube) is 3.1 u sqrt(sum_l v_l) / N_l, and a single loop's
 // phase error stays below 18 u sqrt(sum_i t_i^2); at kDecideK = 16 a point
 // left in FP32 is then within half the tolerance even when one loop
 // carries the mean.
-__device__ __forceinline__ void scale_point(const double* __restrict__ pa,
-                                            const double* __restrict__ pv, int64_t rows,
-                                            int32_t n_pts, int64_t n_loops, int32_t prec,
-                                            int32_t p, double& ms, double& fe, bool& esc) {
-  double sa = 0.0, sv = 0.0;
-  for (int64_t r = 0; r < rows; ++r) {
-    sa += pa[r * n_pts + p];
-    sv += pv[r * n_pts + p];
-  }
-  ms = sa / (double)n_loops;
-  const double u = prec == 2 ? kU64 : kU32;
-  const double rnd = u * sqrt(sv) / (double)n_loops;
-  esc = prec == 0 && kDecideK * rnd > kEscalate * ms;
-  if (!esc) {
-    fe = kPhaseK * rnd + kSysK * u * ms;
-  } else {
-    // the rows left in FP32 (esc_row_threshold) and their estimate
-    const double thr = esc_row_threshold(ms, n_loops, rows);
-    double rest = 0.0;
-    for (int64_t r = 0; r < rows; ++r) {
-      const double v = pv[r * n_pts + p];
-      if (!(v > thr)) rest += v;
+// AGAIN: the second pass, after the recomputation: the tile's points are
+// list[16 tile ..) of the cnt flagged ones, whose group sums, mean, error and
+// estimate are formed again.
+// Thread (slot q, point pt): the slots take the groups q, q + slots, ...; 16
+// points make 128-byte reads of a row.  What bounds it is the latency of the
+// row reads, so the rows are spread over up to 64 slots: one thread per point
+// walking every row, and kernels of their own for the sub-range sums and the
+// statistics, took 43 us together for 1024 loops on 8 x 16 points (16 groups
+// of 8 rows) and 1.35 ms for 2048 groups on 192 points; this takes 5 and 89.
+template <bool AGAIN>
+__device__ __forceinline__ void finish_tile(const Finish& f, int32_t tile, int32_t cnt) {
+  const int32_t pt = threadIdx.x % kFinPts, q = threadIdx.x / kFinPts;
+  const int32_t slots = blockDim.x / kFinPts;
+  const int32_t i = tile * kFinPts + pt;
+  const bool valid = i < cnt;
+  int32_t p = valid ? i : cnt - 1;
+  if constexpr (AGAIN) p = f.list[p];
+  const int64_t n_pts = f.n_pts;
+  double thr = 0.0;
+  if constexpr (AGAIN)
+    thr = esc_row_threshold(f.scale[p], f.n_loops, (int64_t)f.n_groups * f.n_sub);
+  double x[2] = {0.0, 0.0};  // sums of a, v (AGAIN: of the v left in FP32)
+  double tot[1] = {0.0};
+  int32_t buf = 0;
+  for (int32_t g0 = 0; g0 < f.n_groups; g0 += slots) {
+    const int32_t g = g0 + q;
+    double S[1] = {0.0};
+    if (g < f.n_groups) {
+      const int64_t row = (int64_t)g * f.n_sub;
+#pragma unroll 4
+      for (int32_t s = 0; s < f.n_sub; ++s) {
+        const int64_t o = (row + s) * n_pts + p;
+        S[0] += f.pw[o];
+        const double v = f.pv[o];
+        if constexpr (AGAIN) {
+          if (!(v > thr)) x[1] += v;
+        } else {
+          x[0] += f.pa[o];
+          x[1] += v;
+        }
+      }
+      if (f.n_sub > 1 && valid) f.sums[g * n_pts + p] = S[0];
     }
-    fe = kPhaseK * u * sqrt(rest) / (double)n_loops + kSysK * u * ms;
+    add_in_order(S, tot, buf, min(slots, f.n_groups - g0));
+  }
+  share_totals(tot);
+  slot_sums(x);
+  const double m = tot[0] / (double)f.n_loops;
+  const double per = (double)(f.n_loops / f.n_groups);
+  double ss[1] = {0.0};
+  for (int32_t g = q; valid && g < f.n_groups; g += slots) {
+    // this thread's own sums, or the items' when there is one per group
+    const double d = f.sums[g * n_pts + p] / per - m;
+    ss[0] += d * d;
+  }
+  slot_sums(ss);
+  if (!valid || q != 0) return;
+  if (f.mean) f.mean[p] = m;
+  if (f.err)
+    f.err[p] = f.n_groups > 1
+                   ? sqrt(ss[0] / ((double)f.n_groups * (f.n_groups - 1)))
+                   : NAN;
+  const double u = f.prec == 2 ? kU64 : kU32;
+  const double rnd = u * sqrt(x[1]) / (double)f.n_loops;
+  if constexpr (AGAIN) {
+    if (f.fp_err) f.fp_err[p] = kPhaseK * rnd + kSysK * u * f.scale[p];
+  } else {
+    const double ms = x[0] / (double)f.n_loops;
+    const bool esc = f.prec == 0 && kDecideK * rnd > kEscalate * ms;
+    f.scale[p] = ms;
+    if (f.fp_err) f.fp_err[p] = kPhaseK * rnd + kSysK * u * ms;
+    f.flags[p] = esc ? 1 : 0;
+    if (f.flags_out) f.flags_out[p] = esc ? 1 : 0;
   }
 }
 
@@ -1259,59 +1384,14 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(const uint8_t* __re
   compact_flags(flags, n_pts, list, count);
 }
 
-// Scale, rounding estimate and escalation flag per grid point of one
-// evaluation (scale_point); scale and fp_err may be NULL.
-__global__ __launch_bounds__(256) void k_scale(const double* __restrict__ pa,
-                                               const double* __restrict__ pv, int64_t rows,
-                                               int32_t n_pts, int64_t n_loops, int32_t prec,
-                                               double* __restrict__ scale,
-                                               double* __restrict__ fp_err,
-                                               uint8_t* __restrict__ flags) {
-  const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_pts) return;
-  double ms, fe;
-  bool esc;
-  scale_point(pa, pv, rows, n_pts, n_loops, prec, p, ms, fe, esc);
-  if (scale) scale[p] = ms;
-  if (fp_err) fp_err[p] = fe;
-  flags[p] = esc ? 1 : 0;
-}
-
-// The three levels' terms of one loop at this lane's grid point.
-template <int KIND, bool SPIN, int PREC>
-__device__ __forceinline__ void disc_terms(const float4* __restrict__ seg,
-                                           const float4* __restrict__ sub,
-                                           const double4* __restrict__ seg64,
-                                           const double4* __restrict__ sub64, int32_t n_ppl,
-                                           int64_t l, double rho, double s, double T,
-                                           const LaneF32& c, const FieldArgs& f, bool full,
-                                           double& w1, double& w2, double& w4) {
-  const int32_t h = n_ppl / 2, q = n_ppl / 4;
-  double Ac, Bc, As, Bs, At, Bt;
-  if constexpr (PREC == 2) {
-    const double4* u = sub64 + l * n_ppl;
-    loop_sums_f64seg<KIND, SPIN>(u, h, rho, s, f, Ac, Bc);
-    loop_sums_f64seg<KIND, SPIN>(u + h, q, rho, s, f, As, Bs);
-    loop_sums_f64seg<KIND, SPIN>(u + h + q, q, rho, s, f, At, Bt);
-  } else {
-    const float4* u = sub + l * n_ppl;
-    double Q;
-    loop_sums_f32<KIND, SPIN, PREC == 0>(u, h, c, f, Ac, Bc, Q);
-    loop_sums_f32<KIND, SPIN, PREC == 0>(u + h, q, c, f, As, Bs, Q);
-    loop_sums_f32<KIND, SPIN, PREC == 0>(u + h + q, q, c, f, At, Bt, Q);
-  }
-  w1 = 0.0;
-  disc_levels<SPIN, PREC>(Ac, Bc, As, Bs, At, Bt, T, h, q, f, full, w1, w2, w4);
-  if (full) {
-    double A, B, phi, S;
-    if constexpr (PREC == 2) {
-      loop_sums_f64seg<KIND, SPIN>(seg64 + l * n_ppl, n_ppl, rho, s, f, A, B);
-    } else {
-      double Q;
-      loop_sums_f32<KIND, SPIN, PREC == 0>(seg + l * n_ppl, n_ppl, c, f, A, B, Q);
-    }
-    w1 = epilogue<SPIN, PREC>(A, B, T, n_ppl, f, phi, S);
-  }
+// The results of an evaluation (finish_tile), one block per tile of points;
+// AGAIN: of its flagged points, after their recomputation.
+template <bool AGAIN>
+__global__ __launch_bounds__(kFinPts * kFinSlots) void k_finish(
+    Finish f, const int32_t* __restrict__ count) {
+  const int32_t cnt = AGAIN ? __builtin_amdgcn_readfirstlane(*count) : f.n_pts;
+  for (int64_t tile = blockIdx.x; tile * kFinPts < cnt; tile += gridDim.x)
+    finish_tile<AGAIN>(f, (int32_t)tile, cnt);
 }
 
 // Discretisation estimate (Sec. 4.1): the schedule and workgroup shape of
@@ -1419,16 +1499,23 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   }
 }
 
-// Next item of a persistent wavefront's work loop: one increment of the
-// counter per wave, whose old value every lane receives.  Every lane
-// executes the atomic (lane 0 adds 1, the others 0; the compiler folds the
-// wave's lanes into one memory operation), so that no lane-dependent branch
-// sits in the loop: around a branch on the lane the compiler may send lanes
-// 1..63 from the end of one item straight back to the broadcast, where they
-// then run without lane 0 and read a stale item.
-__device__ __forceinline__ int64_t take_item(unsigned int* counter) {
+// Next item of a persistent wavefront's work loop: the wave's own index for
+// the first one, then one increment of the counter per wave, whose old value
+// every lane receives.  (With an atomic for the first item too, 8192 waves
+// took 96 us to find an empty list: the atomics of one address follow one
+// another.)  Every lane executes the atomic (lane 0 adds 1, the others 0; the
+// compiler folds the wave's lanes into one memory operation), so that no
+// lane-dependent branch sits in the loop: around a branch on the lane the
+// compiler may send lanes 1..63 from the end of one item straight back to the
+// broadcast, where they then run without lane 0 and read a stale item.
+__device__ __forceinline__ int64_t first_item() {
+  return (int64_t)blockIdx.x * kWavesPerWG +
+         __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+}
+__device__ __forceinline__ int64_t next_item(unsigned int* counter) {
   const unsigned int t = atomicAdd(counter, threadIdx.x % kWave == 0 ? 1u : 0u);
-  return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+  return (int64_t)gridDim.x * kWavesPerWG +
+         (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)t);
 }
 
 // Batched evaluation of uneven requests in one persistent launch.  Items of
@@ -1455,9 +1542,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = (int32_t)hdr->n_reqs;
   const int64_t total_items = hdr->total_items;
-  for (;;) {
-    const int64_t item = take_item(counter);
-    if (item >= total_items) break;
+  for (int64_t item = first_item(); item < total_items; item = next_item(counter)) {
     // request owning the item: last r with item_begin <= item
     int32_t lo = 0, hi = n_reqs - 1;
     while (lo < hi) {
@@ -1504,9 +1589,7 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
   // the table is written by an earlier kernel, so its entries come in
   // through vector loads: wave_uniform keeps the loop's branches scalar
   const int64_t total = wave_uniform(esc_begin[n_reqs]);
-  for (;;) {
-    const int64_t item = take_item(counter);
-    if (item >= total) break;
+  for (int64_t item = first_item(); item < total; item = next_item(counter)) {
     // request owning the item: last r with esc_begin[r] <= item (a request
     // without items has the same entry as the next one and is passed over)
     int32_t lo = 0, hi = n_reqs - 1;
@@ -1523,25 +1606,36 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
   }
 }
 
-// First recomputation item of each request of a batch, per variant (one
-// thread, in request order): for the request's variant v,
+// First recomputation item of each request of a batch, per variant, in
+// request order: for the request's variant v,
 // esc_begin[v][r + 1] = esc_begin[v][r] + esc_items(G n_sub_r, count_r);
-// the other variants' tables repeat their entry.
-__global__ void k_esc_begin(const BatchHeader* __restrict__ hdr, int32_t n_groups,
-                            int64_t loops_per_group) {
+// the other variants' tables repeat their entry.  One workgroup: its threads
+// read a tile of requests side by side, then one thread per variant adds.
+constexpr int kEscTile = 256;
+__global__ __launch_bounds__(kEscTile) void k_esc_begin(const BatchHeader* __restrict__ hdr,
+                                                        int32_t n_groups) {
+  __shared__ int64_t items[kEscTile];
+  __shared__ int32_t variant[kEscTile];
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = (int32_t)hdr->n_reqs;
-  int64_t* __restrict__ esc_begin = hdr->esc_begin;
-  int64_t acc[kVariants];
-  for (int v = 0; v < kVariants; ++v) {
-    acc[v] = 0;
-    esc_begin[(int64_t)v * (n_reqs + 1)] = 0;
-  }
-  for (int32_t r = 0; r < n_reqs; ++r) {
-    const int v = reqs[r].f.kind * 2 + (reqs[r].spin ? 1 : 0);
-    acc[v] += esc_items((int64_t)n_groups * reqs[r].n_sub, *reqs[r].count);
-    for (int u = 0; u < kVariants; ++u) esc_begin[(int64_t)u * (n_reqs + 1) + r + 1] = acc[u];
+  const int32_t t = threadIdx.x;
+  int64_t* table = hdr->esc_begin + (int64_t)t * (n_reqs + 1);  // t < kVariants
+  int64_t acc = 0;
+  if (t < kVariants) table[0] = 0;
+  for (int32_t r0 = 0; r0 < n_reqs; r0 += kEscTile) {
+    if (r0 + t < n_reqs) {
+      const ReqDesc& q = reqs[r0 + t];
+      items[t] = esc_items((int64_t)n_groups * q.n_sub, *q.count);
+      variant[t] = q.f.kind * 2 + (q.spin ? 1 : 0);
+    }
+    __syncthreads();
+    if (t < kVariants)
+      for (int32_t r = r0; r < n_reqs && r < r0 + kEscTile; ++r) {
+        if (variant[r - r0] == t) acc += items[r - r0];
+        table[r + 1] = acc;
+      }
+    __syncthreads();
   }
 }
 
@@ -1559,99 +1653,33 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_batch(
   }
 }
 
-// Scale, rounding estimate and escalation flag of every grid point of a
-// batch (thread t handles point t of the concatenation over requests).
-__global__ __launch_bounds__(256) void k_scale_batch(const BatchHeader* __restrict__ hdr,
-                                                     int32_t n_groups, int64_t n_loops,
-                                                     int32_t prec) {
+// The results of a batch (finish_tile): the tiles of all requests form one
+// index space (request r owns those from tile_begin_r), walked grid-stride.
+// Result region: [group sums | means | errors | ...].
+template <bool AGAIN>
+__global__ __launch_bounds__(kFinPts * kFinSlots) void k_finish_batch(
+    const BatchHeader* __restrict__ hdr, int32_t n_groups, int64_t n_loops, int32_t prec,
+    double* __restrict__ res) {
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = (int32_t)hdr->n_reqs;
-  const int64_t total_pts = hdr->total_pts;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total_pts;
-       t += (int64_t)gridDim.x * blockDim.x) {
+  const ReqDesc& last = reqs[n_reqs - 1];
+  const int32_t total = last.tile_begin + (last.n_pts + kFinPts - 1) / kFinPts;
+  double* mean = res + hdr->total_sums;
+  for (int32_t t = blockIdx.x; t < total; t += gridDim.x) {
     int32_t lo = 0, hi = n_reqs - 1;
     while (lo < hi) {
       const int32_t mid = (lo + hi + 1) >> 1;
-      if (reqs[mid].pts_begin <= t) lo = mid; else hi = mid - 1;
+      if (reqs[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
     }
     const ReqDesc& q = reqs[lo];
-    const int32_t p = (int32_t)(t - q.pts_begin);
-    double ms, fe;
-    bool esc;
-    scale_point(q.out_a, q.out_v, (int64_t)n_groups * q.n_sub, q.n_pts, n_loops, prec, p,
-                ms, fe, esc);
-    q.scale[p] = ms;
-    q.fp_err[p] = fe;
-    q.flags[p] = esc ? 1 : 0;
-  }
-}
-
-// Batched sub-range reduction and statistics: thread t handles output t of
-// the concatenation over requests (binary search for its request).
-// Result region of a batch: [group sums | means | errors | partials].
-__global__ __launch_bounds__(256) void k_reduce_batch(const BatchHeader* __restrict__ hdr,
-                                                      double* __restrict__ sums) {
-  const ReqDesc* __restrict__ reqs =
-      (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
-  const int64_t total = hdr->total_sums;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    int32_t lo = 0, hi = n_reqs - 1;
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (reqs[mid].sums_begin <= t) lo = mid; else hi = mid - 1;
-    }
-    const ReqDesc& q = reqs[lo];
-    if (q.n_sub == 1) continue;  // written directly by the item kernel
-    const int64_t o = t - q.sums_begin;
-    const int64_t g = o / q.n_pts, p = o % q.n_pts;
-    double acc = 0.0;
-    for (int32_t s = 0; s < q.n_sub; ++s) acc += q.out[(g * q.n_sub + s) * q.n_pts + p];
-    sums[t] = acc;
-  }
-}
-
-__device__ __forceinline__ void stats_point(const double* __restrict__ sums,
-                                            int32_t n_groups, int32_t n_pts,
-                                            int64_t n_loops, int32_t p, double& m,
-                                            double& e) {
-  double tot = 0.0;
-  for (int32_t g = 0; g < n_groups; ++g) tot += sums[(int64_t)g * n_pts + p];
-  m = tot / (double)n_loops;
-  const double per = (double)(n_loops / n_groups);
-  double ss = 0.0;
-  for (int32_t g = 0; g < n_groups; ++g) {
-    const double d = sums[(int64_t)g * n_pts + p] / per - m;
-    ss += d * d;
-  }
-  e = n_groups > 1 ? sqrt(ss / ((double)n_groups * (n_groups - 1))) : NAN;
-}
-
-__global__ __launch_bounds__(256) void k_stats_batch(const BatchHeader* __restrict__ hdr,
-                                                     int32_t n_groups, int64_t n_loops,
-                                                     double* __restrict__ res) {
-  const ReqDesc* __restrict__ reqs =
-      (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
-  const int64_t total_pts = hdr->total_pts;
-  const double* __restrict__ sums = res;
-  double* __restrict__ mean = res + hdr->total_sums;
-  double* __restrict__ err = mean + total_pts;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total_pts;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    int32_t lo = 0, hi = n_reqs - 1;
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (reqs[mid].pts_begin <= t) lo = mid; else hi = mid - 1;
-    }
-    const ReqDesc& q = reqs[lo];
-    double m, e;
-    stats_point(sums + q.sums_begin, n_groups, q.n_pts, n_loops,
-                (int32_t)(t - q.pts_begin), m, e);
-    mean[t] = m;
-    err[t] = e;
+    const int32_t tile = t - q.tile_begin;
+    const int32_t cnt = AGAIN ? __builtin_amdgcn_readfirstlane(*q.count) : q.n_pts;
+    if (AGAIN && tile * kFinPts >= cnt) continue;
+    const Finish f{q.out, q.out_a, q.out_v, res + q.sums_begin, mean + q.pts_begin,
+                   mean + hdr->total_pts + q.pts_begin, q.scale, q.fp_err, q.flags, nullptr,
+                   q.list, n_groups, q.n_sub, q.n_pts, prec, n_loops};
+    finish_tile<AGAIN>(f, tile, cnt);
   }
 }
 
@@ -1857,59 +1885,67 @@ __global__ __launch_bounds__(256) void k_prep_sub64(const float* __restrict__ X,
   }
 }
 
-__global__ __launch_bounds__(256) void k_reduce_sub(const double* __restrict__ part,
-                                                    int32_t n_groups, int32_t n_sub,
-                                                    int32_t n_pts,
-                                                    double* __restrict__ sums) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)n_groups * n_pts) return;
-  const int64_t g = t / n_pts, p = t % n_pts;
-  double acc = 0.0;
-  for (int32_t s = 0; s < n_sub; ++s) acc += part[(g * n_sub + s) * n_pts + p];
-  sums[t] = acc;
+// Discretisation estimate, per grid point (Sec. 4.1), in the block shape of
+// finish_tile (same sums): from the items' level sums part [3][G n_sub]
+// [n_pts] the group sums of the three levels, the extrapolated level's
+// (8/3 W_N - 2 W_N/2 + 1/3 W_N/4, group by group, written as level 3), then
+// mean and group standard error of the four levels and
+// delta = |W_N - W_inf|.  sums: [4][G][n_pts], part when n_sub == 1.
+__global__ __launch_bounds__(kFinPts * kFinSlots) void k_disc_finish(
+    const double* part, double* sums, int32_t n_groups, int32_t n_sub, int32_t n_pts,
+    int64_t n_loops, double* __restrict__ mean, double* __restrict__ err,
+    double* __restrict__ delta) {
+  const int32_t pt = threadIdx.x % kFinPts, q = threadIdx.x / kFinPts;
+  const int32_t slots = blockDim.x / kFinPts;
+  const int64_t L = (int64_t)n_groups * n_pts, LP = L * n_sub;
+  for (int64_t tile = blockIdx.x; tile * kFinPts < n_pts; tile += gridDim.x) {
+    const int64_t i = tile * kFinPts + pt;
+    const bool valid = i < n_pts;
+    const int64_t p = valid ? i : n_pts - 1;
+    double x[4] = {0.0, 0.0, 0.0, 0.0};
+    int32_t buf = 0;
+    for (int32_t g0 = 0; g0 < n_groups; g0 += slots) {
+      const int32_t g = g0 + q;
+      double S[4] = {0.0, 0.0, 0.0, 0.0};
+      if (g < n_groups) {
+        for (int32_t s = 0; s < n_sub; ++s) {
+          const int64_t o = ((int64_t)g * n_sub + s) * n_pts + p;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) S[k] += part[k * LP + o];
+        }
+        S[3] = (8.0 * S[0] - 6.0 * S[1] + S[2]) / 3.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (valid && (k == 3 || n_sub > 1)) sums[k * L + (int64_t)g * n_pts + p] = S[k];
+      }
+      add_in_order(S, x, buf, min(slots, n_groups - g0));
+    }
+    share_totals(x);
+    const double per = (double)(n_loops / n_groups);
+    double ss[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int32_t g = q; valid && g < n_groups; g += slots)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double d = sums[k * L + (int64_t)g * n_pts + p] / per - x[k] / (double)n_loops;
+        ss[k] += d * d;
+      }
+    slot_sums(ss);
+    if (!valid || q != 0) continue;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (mean) mean[(int64_t)k * n_pts + p] = x[k] / (double)n_loops;
+      if (err)
+        err[(int64_t)k * n_pts + p] =
+            n_groups > 1 ? sqrt(ss[k] / ((double)n_groups * (n_groups - 1))) : NAN;
+    }
+    if (delta) delta[p] = fabs(x[0] / (double)n_loops - x[3] / (double)n_loops);
+  }
 }
 
-// Mean and standard error of the group means (Sec. 4.2.3) per grid point.
-__global__ __launch_bounds__(256) void k_stats(const double* __restrict__ sums,
-                                               int32_t n_groups, int32_t n_pts,
-                                               int64_t n_loops,
-                                               double* __restrict__ mean,
-                                               double* __restrict__ err) {
-  const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_pts) return;
-  double m, e;
-  stats_point(sums, n_groups, n_pts, n_loops, p, m, e);
-  if (mean) mean[p] = m;
-  if (err) err[p] = e;
-}
-
-// Discretisation estimate, per grid point: the extrapolated level's group
-// sums (8/3 W_N - 2 W_N/2 + 1/3 W_N/4, group by group, written as level 3),
-// then mean and group standard error of the four levels and
-// delta = |W_N - W_inf| (Sec. 4.1).  sums: [4][G][n_pts].
-__global__ __launch_bounds__(256) void k_disc_finish(double* __restrict__ sums,
-                                                     int32_t n_groups, int32_t n_pts,
-                                                     int64_t n_loops,
-                                                     double* __restrict__ mean,
-                                                     double* __restrict__ err,
-                                                     double* __restrict__ delta) {
-  const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_pts) return;
-  const int64_t L = (int64_t)n_groups * n_pts;
-  for (int32_t g = 0; g < n_groups; ++g) {
-    const int64_t o = (int64_t)g * n_pts + p;
-    sums[3 * L + o] = (8.0 * sums[o] - 6.0 * sums[L + o] + sums[2 * L + o]) / 3.0;
-  }
-  double m0 = 0.0, m3 = 0.0;
-  for (int32_t k = 0; k < 4; ++k) {
-    double m, e;
-    stats_point(sums + k * L, n_groups, n_pts, n_loops, p, m, e);
-    if (mean) mean[(int64_t)k * n_pts + p] = m;
-    if (err) err[(int64_t)k * n_pts + p] = e;
-    if (k == 0) m0 = m;
-    if (k == 3) m3 = m;
-  }
-  if (delta) delta[p] = fabs(m0 - m3);
+// Threads of a finishing block: a slot per group, 16 to 64 (a function of the
+// group count alone, so that every path sums in the same order).
+int32_t finish_threads(int32_t n_groups) {
+  return kFinPts * (n_groups <= 16 ? 16 : n_groups <= 32 ? 32 : kFinSlots);
 }
 
 // ------------------------------------------------------------ dispatch
@@ -1952,12 +1988,8 @@ hipError_t launch_avg_t(const FieldArgs& f, const float4* seg, const double4* se
 template <int KIND, bool SPIN>
 hipError_t launch_esc_t(const FieldArgs& f, const float* x, const float* y, int32_t n_ppl,
                         const double* rho, const double* T, int32_t n_T, int32_t n_pts,
-                        const Sched& s, const uint8_t* flags, int32_t* list, int32_t* count,
+                        const Sched& s, const int32_t* list, const int32_t* count,
                         const double* pv, const double* scale, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_compact, dim3(1), dim3(kCompactThreads), 0, st, flags, n_pts, list,
-                     count);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   // at most n_pts points flagged: enough workgroups for the largest count
   // (the evaluation's n_items items), up to 4096 (16384 waves, 4 per SIMD on
   // 1024 SIMDs four times over)
@@ -1966,6 +1998,28 @@ hipError_t launch_esc_t(const FieldArgs& f, const float* x, const float* y, int3
   hipLaunchKernelGGL((k_escalate<KIND, SPIN>), dim3((uint32_t)n_wg), dim3(kWavesPerWG * kWave),
                      0, st, x, y, n_ppl, rho, T, n_T, n_pts, f, s, list, count, pv, scale, out);
   return hipGetLastError();
+}
+
+hipError_t launch_escalate(int spin, const FieldArgs& f, const float* x, const float* y,
+                           int32_t n_ppl, const double* rho, const double* T, int32_t n_T,
+                           int32_t n_pts, const Sched& s, const int32_t* list,
+                           const int32_t* count, const double* pv, const double* scale,
+                           double* out, hipStream_t st) {
+  switch (f.kind * 2 + spin) {
+#define WL_ESC(K, SP)                                                                       \
+  return launch_esc_t<K, SP>(f, x, y, n_ppl, rho, T, n_T, n_pts, s, list, count, pv, scale, \
+                             out, st)
+    case 0: WL_ESC(kConst, false);
+    case 1: WL_ESC(kConst, true);
+    case 2: WL_ESC(kSech2, false);
+    case 3: WL_ESC(kSech2, true);
+    case 4: WL_ESC(kGauss, false);
+    case 5: WL_ESC(kGauss, true);
+    case 6: WL_ESC(kRational, false);
+    case 7: WL_ESC(kRational, true);
+#undef WL_ESC
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <int KIND, bool SPIN, int PREC>
@@ -2086,34 +2140,32 @@ hipError_t launch_average(int precision, int spin, const FieldArgs& f,
                d_out, d_out_a, d_out_v, stream)
 }
 
-hipError_t launch_scale_escalate(int precision, int spin, const FieldArgs& f,
-                                 const float* d_x, const float* d_y, int32_t n_ppl,
-                                 const double* d_rho, const double* d_T, int32_t n_T,
-                                 int32_t n_pts, const Sched& s, int64_t n_loops,
-                                 const double* d_out_a, const double* d_out_v,
-                                 double* d_scale, double* d_fp_err, uint8_t* d_flags,
-                                 int32_t* d_list, double* d_out, hipStream_t stream) {
-  const int64_t rows = s.n_items / s.n_chunks;  // G * n_sub
-  hipLaunchKernelGGL(k_scale, dim3((uint32_t)((n_pts + 255) / 256)), dim3(256), 0, stream,
-                     d_out_a, d_out_v, rows, n_pts, n_loops, (int32_t)precision, d_scale,
-                     d_fp_err, d_flags);
+hipError_t launch_finish(int precision, int spin, const FieldArgs& f, const float* d_x,
+                         const float* d_y, int32_t n_ppl, const double* d_rho,
+                         const double* d_T, int32_t n_T, int32_t n_pts, const Sched& s,
+                         int32_t n_groups, int64_t n_loops, double* d_out,
+                         const double* d_out_a, const double* d_out_v, double* d_sums,
+                         double* d_mean, double* d_err, double* d_scale, double* d_fp_err,
+                         uint8_t* d_flags, uint8_t* d_flags_out, int32_t* d_list,
+                         hipStream_t stream) {
+  int32_t* d_count = d_list + n_pts;
+  const Finish fin{d_out,    d_out_a, d_out_v,     d_sums, d_mean,   d_err,   d_scale,   d_fp_err,
+                   d_flags,  d_flags_out, d_list, n_groups, s.n_sub, n_pts, precision, n_loops};
+  int64_t n_wg = (n_pts + kFinPts - 1) / kFinPts;
+  if (n_wg > 65536) n_wg = 65536;
+  const dim3 grid((uint32_t)n_wg), blk(finish_threads(n_groups));
+  hipLaunchKernelGGL((k_finish<false>), grid, blk, 0, stream, fin, d_count);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || precision != 0) return e;
-  switch (f.kind * 2 + spin) {
-#define WL_ESC(K, SP)                                                                   \
-  return launch_esc_t<K, SP>(f, d_x, d_y, n_ppl, d_rho, d_T, n_T, n_pts, s, d_flags, d_list, \
-                             d_list + n_pts, d_out_v, d_scale, d_out, stream)
-    case 0: WL_ESC(kConst, false);
-    case 1: WL_ESC(kConst, true);
-    case 2: WL_ESC(kSech2, false);
-    case 3: WL_ESC(kSech2, true);
-    case 4: WL_ESC(kGauss, false);
-    case 5: WL_ESC(kGauss, true);
-    case 6: WL_ESC(kRational, false);
-    case 7: WL_ESC(kRational, true);
-#undef WL_ESC
-    default: return hipErrorInvalidValue;
-  }
+  hipLaunchKernelGGL(k_compact, dim3(1), dim3(kCompactThreads), 0, stream, d_flags, n_pts,
+                     d_list, d_count);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  e = launch_escalate(spin, f, d_x, d_y, n_ppl, d_rho, d_T, n_T, n_pts, s, d_list, d_count,
+                      d_out_v, d_scale, d_out, stream);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_finish<true>), dim3((uint32_t)(n_wg < 1024 ? n_wg : 1024)), blk, 0,
+                     stream, fin, d_count);
+  return hipGetLastError();
 }
 
 hipError_t launch_per_loop(int precision, int spin, const FieldArgs& f,
@@ -2157,11 +2209,14 @@ hipError_t launch_disc(int precision, int spin, const FieldArgs& f, const float4
               s, full, d_out, stream)
 }
 
-hipError_t launch_disc_finish(double* d_sums, int32_t n_groups, int32_t n_pts,
-                              int64_t n_loops, double* d_mean, double* d_err,
-                              double* d_delta, hipStream_t stream) {
-  hipLaunchKernelGGL(k_disc_finish, dim3((uint32_t)((n_pts + 255) / 256)), dim3(256), 0,
-                     stream, d_sums, n_groups, n_pts, n_loops, d_mean, d_err, d_delta);
+hipError_t launch_disc_finish(const double* d_part, double* d_sums, int32_t n_groups,
+                              int32_t n_sub, int32_t n_pts, int64_t n_loops, double* d_mean,
+                              double* d_err, double* d_delta, hipStream_t stream) {
+  int64_t n_wg = (n_pts + kFinPts - 1) / kFinPts;
+  if (n_wg > 65536) n_wg = 65536;
+  hipLaunchKernelGGL(k_disc_finish, dim3((uint32_t)n_wg), dim3(finish_threads(n_groups)), 0,
+                     stream, d_part, d_sums, n_groups, n_sub, n_pts, n_loops, d_mean, d_err,
+                     d_delta);
   return hipGetLastError();
 }
 
@@ -2194,13 +2249,14 @@ hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg
       return hipErrorInvalidValue;
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scale_batch, dim3(2048), dim3(256), 0, stream, hdr, n_groups, n_loops,
-                     (int32_t)precision);
+  const dim3 fin(finish_threads(n_groups));
+  hipLaunchKernelGGL((k_finish_batch<false>), dim3(512), fin, 0, stream, hdr, n_groups,
+                     n_loops, (int32_t)precision, d_res);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (precision == 0) {
     hipLaunchKernelGGL(k_compact_batch, dim3(256), dim3(kCompactThreads), 0, stream, hdr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_esc_begin, dim3(1), dim3(1), 0, stream, hdr, n_groups, lpg);
+    hipLaunchKernelGGL(k_esc_begin, dim3(1), dim3(kEscTile), 0, stream, hdr, n_groups);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 #define WL_ESCB(K, SP, V)                                                              \
   hipLaunchKernelGGL((k_escalate_batch<K, SP>), dim3(n_wg), blk, 0, stream, d_x, d_y, n_ppl, \
@@ -2215,30 +2271,11 @@ hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg
     WL_ESCB(kRational, false, 6)
     WL_ESCB(kRational, true, 7)
 #undef WL_ESCB
+    hipLaunchKernelGGL((k_finish_batch<true>), dim3(512), fin, 0, stream, hdr, n_groups,
+                       n_loops, (int32_t)precision, d_res);
+    e = hipGetLastError();
   }
-  hipLaunchKernelGGL(k_reduce_batch, dim3(2048), dim3(256), 0, stream, hdr, d_res);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_stats_batch, dim3(2048), dim3(256), 0, stream, hdr, n_groups, n_loops,
-                     d_res);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_sub(const double* d_partial, int32_t n_groups,
-                             int32_t n_sub, int32_t n_pts, double* d_sums,
-                             hipStream_t stream) {
-  const int64_t total = (int64_t)n_groups * n_pts;
-  hipLaunchKernelGGL(k_reduce_sub, dim3((uint32_t)((total + 255) / 256)),
-                     dim3(256), 0, stream, d_partial, n_groups, n_sub, n_pts,
-                     d_sums);
-  return hipGetLastError();
-}
-
-hipError_t launch_stats(const double* d_sums, int32_t n_groups, int32_t n_pts,
-                        int64_t n_loops, double* d_mean, double* d_err,
-                        hipStream_t stream) {
-  hipLaunchKernelGGL(k_stats, dim3((uint32_t)((n_pts + 255) / 256)), dim3(256),
-                     0, stream, d_sums, n_groups, n_pts, n_loops, d_mean, d_err);
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace wl
