@@ -15,6 +15,15 @@ and two elementary functions of the FP64 path:
     as functions of v = f^2,          reduction of Phi to the nearest
     |f| <= 1/8                        quarter turn)
 
+and, for the FP64 segment walk's table-driven forms,
+
+  2^(j/64), j = 0 .. 63, and          (exp2 after the reduction
+  (2^f - 1)/f on [-1/128, 1/128]       t = n + j/64 + f)
+  (c_j, 1 + log2 c_j), j = 0 .. 127,  (log2(1 + E) for E < 1/2: c_j the
+  c_j = 1/(1 + (j + 1/2)/256), and     double nearest the reciprocal of the
+  log2(1 + r)/r on [-1/511, 1/511]     middle of 1 + E's interval of width
+                                       1/256, r = (1 + E) c_j - 1)
+
 All are analytic on their intervals.  Coefficients come from Chebyshev
 interpolation of the exact function (mpmath, 60 digits) on the stated
 interval, converted to the monomial basis in v and rounded to the target
@@ -63,6 +72,29 @@ def sin2pi_exact(v):
         return 2 * mp.pi
     f = mp.sqrt(v)
     return mp.sin(2 * mp.pi * f) / f
+
+
+def exp2m1_exact(f):
+    f = mp.mpf(f)
+    if f == 0:
+        return mp.log(2)
+    return mp.expm1(f * mp.log(2)) / f
+
+
+def log2p1_exact(r):
+    r = mp.mpf(r)
+    if r == 0:
+        return 1 / mp.log(2)
+    return mp.log1p(r) / r / mp.log(2)
+
+
+def emit_table(name, values, comment):
+    print(f"/* {name}: {comment} */")
+    print(f"static __constant__ double {name}[{len(values)}] = {{")
+    for x in values:
+        print(f"    {repr(float(x))},")
+    print("};")
+    print()
 
 
 def cheb_monomial(f, a, b, deg):
@@ -151,3 +183,10 @@ if __name__ == "__main__":
          const_mem=False)
     emit("WL_SIN2PI_F64", sin2pi_exact, 0.0, 1 / 64, 7, np.float64, "double", "",
          const_mem=False)
+    emit("WL_EXP2M1_F64", exp2m1_exact, -1 / 128, 1 / 128, 4, np.float64, "double", "")
+    emit("WL_LOG2P1_F64", log2p1_exact, -1 / 511, 1 / 511, 4, np.float64, "double", "")
+    emit_table("WL_EXP2_TAB", [mp.power(2, mp.mpf(j) / 64) for j in range(64)],
+               "2^(j/64), rounded to double")
+    inv = [mp.mpf(float(1 / (1 + (mp.mpf(j) + 0.5) / 256))) for j in range(128)]
+    emit_table("WL_LOG2_TAB", [v for c in inv for v in (c, 1 + mp.log(c, 2))],
+               "pairs c_j, 1 + log2 c_j")

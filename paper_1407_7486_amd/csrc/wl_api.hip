@@ -64,9 +64,8 @@ int check_field(wl_ctx* ctx, const wl_field* f, wl::FieldArgs* a) {
   const double log2e = 1.4426950408889634074;
   a->kind = f->kind;
   a->inv_lam_d = 1.0 / l;
-  a->inv_lam2_d = 1.0 / (l * l);
   a->lam2_d = l * l;
-  a->inv_lam2 = (float)a->inv_lam2_d;
+  a->inv_lam2 = (float)(1.0 / (l * l));
   a->lam2 = (float)a->lam2_d;
   a->lam2_lo = (float)(a->lam2_d - (double)a->lam2);
   a->thr = 0.0f;
@@ -76,8 +75,10 @@ int check_field(wl_ctx* ctx, const wl_field* f, wl::FieldArgs* a) {
       a->cphi = 0.5 * f->eB0;
       a->cspin = f->eB0;
       break;
-    case WL_SECH2:  // g = eB0 lam^2 qa, b = eB0 * 4 * E/(1+E)^2
-      a->cphi = f->eB0 * l * l;
+    case WL_SECH2:  // g = eB0 lam^2 qa, b = eB0 * 4 * E/(1+E)^2; the walks
+      // work in units scaled by gs = 2 log2(e)/lambda: qa is divided by
+      // ln2 gs^2 and the cross product multiplied by gs^2
+      a->cphi = (f->eB0 * l * l) * 0.69314718055994530942;
       a->cspin = 4.0 * f->eB0;
       break;
     case WL_GAUSS:  // g = (eB0 lam^2/2) (1-E)/rho^2, b = eB0 E
@@ -91,9 +92,6 @@ int check_field(wl_ctx* ctx, const wl_field* f, wl::FieldArgs* a) {
       a->cspin = f->eB0 * l * l * l * l;
       break;
   }
-  // FP32 sech^2 works in units scaled by gs = 2 log2(e)/lambda: its qa is
-  // divided by ln2 gs^2 and its cross product multiplied by gs^2
-  a->cphi32 = f->kind == WL_SECH2 ? a->cphi * 0.69314718055994530942 : a->cphi;
   a->exp2_scale = (float)e2;
   a->exp2_scale_lo = (float)(e2 - (double)a->exp2_scale);
   return WL_OK;

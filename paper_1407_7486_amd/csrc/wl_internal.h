@@ -52,10 +52,10 @@ struct FieldArgs {
   float exp2_scale_lo, lam2_lo;  // rounding residues of exp2_scale, lam2
   float thr;         // GAUSS: rho^2 below which the polynomial branch is used
   // FP64 path
-  double inv_lam_d, inv_lam2_d, lam2_d;
+  double inv_lam_d, lam2_d;
   // epilogue: Phi = cphi * sum_i cross_i qa_i ; S = cspin (T/N) sum_i qb_i
-  // (cphi32 for the FP32 paths, whose sech^2 qa is in scaled units)
-  double cphi, cspin, cphi32;
+  // (in the walks' units: sech^2's cphi holds ln 2)
+  double cphi, cspin;
 };
 
 // Header of a batch in device memory, followed (at kBatchDescOffset) by

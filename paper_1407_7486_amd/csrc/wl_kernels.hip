@@ -104,7 +104,7 @@ __device__ __forceinline__ double horner_s_f64(const double (&c)[DEG + 1], doubl
 // register pair (held across the walk, one pair per polynomial), the
 // others as scalar operands, so that the first step stays one FMA.  With
 // every coefficient a vector operand the FP64 sech^2 spinor kernel needed
-// 128 VGPRs (4 waves per SIMD); in this form it needs 60 (8 waves).
+// 128 VGPRs (4 waves per SIMD); in this form it runs at 64 (8 waves).
 template <int DEG>
 __device__ __forceinline__ double horner_sv_f64(const double (&c)[DEG + 1], double v) {
   double acc;
@@ -160,8 +160,8 @@ __device__ __forceinline__ void field_f32(float r2, const FieldArgs& f, float th
     // u tanh u - ln cosh u = ln2 (1 - log2(1+E) - t E/(1+E)) the phase weight
     // is qa = (1 - log2(1+E) - t E/(1+E)) / r2: g/(eB0 lambda^2) divided by
     // ln2 gs^2.  The cross product's parts are in the same units (gs^2 times
-    // the unscaled ones), so gs^2 cancels in the product and the FP32
-    // epilogue constant cphi32 carries ln2.  The terms cancel as u -> 0: below
+    // the unscaled ones), so gs^2 cancels in the product and the epilogue
+    // constant cphi carries ln2.  The terms cancel as u -> 0: below
     // u = 1/2 a degree-4 polynomial in u^2 is used; between 1/2 and 1 the
     // cancellation costs at most a factor ~6 (per-segment relative error
     // below 1e-6), and fewer waves carry a near lane than with u < 1.
@@ -216,69 +216,131 @@ __device__ __forceinline__ void field_f32(float r2, const FieldArgs& f, float th
 // answers to 1e-12 relative): hardware estimates refined by Newton steps,
 // and polynomials whose coefficients (wl_poly.h) sit in constant memory.
 
-// 1/x for x > 0 normal: the hardware estimate (about 23 correct bits) and
-// two Newton steps.
+// 1/x for x > 0 normal: the hardware estimate r (about 23 correct bits) and
+// one third-order step r (1 + e + e^2), e = 1 - x r.
 __device__ __forceinline__ double rcp64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 
-// 1/sqrt(x) for x > 0 normal: the hardware estimate and two Newton steps
-// y <- y + y (1/2 - (x/2) y^2).
-__device__ __forceinline__ double rsq64(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  return fma(y, fma(-h * y, y, 0.5), y);
+// sqrt(x) and 1/sqrt(x) for x > 0 normal: the hardware estimate y of 1/sqrt
+// (about 23 correct bits) and one third-order step for both,
+// 1 + e/2 + 3 e^2/8 with e = 1 - x y^2.
+__device__ __forceinline__ void sqrt_rsq64(double x, double& root, double& inv) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = fma(-g, y, 1.0);
+  const double k = e * fma(0.375, e, 0.5);
+  root = fma(g, k, g);
+  inv = fma(y, k, y);
 }
 
-// 2^-t for t >= 0: -t = n + f with n = rint(-t), |f| <= 1/2 (exact), a
-// degree-11 polynomial for 2^f and the exponent added by ldexp.  t is
-// clamped at 4096 first (2^-4096 is 0 in FP64), so that n fits an int and f
-// stays in range.
-__device__ __forceinline__ double exp2_neg64(double t) {
-  const double tc = -fmin(t, 4096.0);
-  const double n = rint(tc);
-  const double p = horner_sv_f64<WL_EXP2_F64_DEG>(WL_EXP2_F64, tc - n);
-  return ldexp(p, (int)n);
-}
-
+// Tables of the FP64 walk's exp2 and log2, copied to LDS (2.5 KB) by each
+// workgroup: a lane reads its own entry there while other waves issue.  The
+// walk is bound by FP64 issue (4.5 cycles per wave-instruction): with 64
+// entries 2^-t takes 9 FP64 instructions instead of 16 and with 128 entries
+// log2(1+E) 7 instead of 14.  Together with the scaled units, the third-order
+// steps above and (recomputation) the staged segments: 32768 x 1024 loops on
+// 64 x 64, sech^2 spinor, 264 -> 211 ms; the recomputation of 558 points of
+// 1024 x 8192 loops 13.9 -> 10.7 ms.  The error against 64-bit values in
+// torch is the same (means of 2048 x 4096 loops 2.6e-14 before and after).
+struct Tables64 {
+  double exp2[64];
+  double2 log2[128];
+};
 template <int KIND>
-__device__ __forceinline__ void field_f64(double r2, const FieldArgs& f,
-                                          double& qa, double& qb) {
+constexpr bool uses_tables() {
+  return KIND == kSech2 || KIND == kGauss;
+}
+// Every thread of the workgroup calls it, before any use and any return.
+__device__ __forceinline__ void load_tables64(Tables64& tab) {
+  for (int32_t i = threadIdx.x; i < 64; i += blockDim.x) tab.exp2[i] = WL_EXP2_TAB[i];
+  for (int32_t i = threadIdx.x; i < 128; i += blockDim.x)
+    tab.log2[i] = make_double2(WL_LOG2_TAB[2 * i], WL_LOG2_TAB[2 * i + 1]);
+  __syncthreads();
+}
+
+// 2^-t for t >= 0: -t = n/64 + f with n = rint(-64 t) (the low word of
+// 1.5 2^52 - 64 t), |f| <= 1/128; 2^(n mod 64 / 64) from the table with
+// n div 64 added to its exponent, times 1 + f P(f), P of degree 4.  t is
+// held below 1021 first (its high word, an integer minimum), where 2^-t is
+// still normal; beyond, the result stays near 2^-1021 instead of 0.
+__device__ __forceinline__ double exp2_neg64(double t, const Tables64& tab) {
+  const double tc = __hiloint2double((int)min((uint32_t)__double2hiint(t), 0x408fe000u),
+                                     __double2loint(t));
+  constexpr double kMagic = 6755399441055744.0;  // 1.5 2^52
+  const double z = fma(-64.0, tc, kMagic);
+  const int n = __double2loint(z);
+  const double f = fma(z - kMagic, -0.015625, -tc);
+  const double T0 = tab.exp2[n & 63];
+  const double T = __hiloint2double(__double2hiint(T0) + (int)((uint32_t)(n >> 6) << 20),
+                                    __double2loint(T0));
+  return fma(T, f * horner_sv_f64<WL_EXP2M1_F64_DEG>(WL_EXP2M1_F64, f), T);
+}
+
+// 1 - log2(1 + E) for E < 1/2, opE = 1 + E rounded: the interval of width
+// 1/256 from the top mantissa bits of opE, c its middle's reciprocal,
+// log2(1 + E) = log2(1 + r) - log2 c with r = E c + (c - 1) (rounded once,
+// c - 1 is exact), |r| <= 1/511, and log2(1 + r) = r Q(r), Q of degree 4.
+__device__ __forceinline__ double one_minus_log2_1p(double E, double opE,
+                                                    const Tables64& tab) {
+  const double2 c = tab.log2[(__double2hiint(opE) >> 12) & 127];
+  const double r = fma(E, c.x, c.x - 1.0);
+  return fma(-r, horner_sv_f64<WL_LOG2P1_F64_DEG>(WL_LOG2P1_F64, r), c.y);
+}
+
+// The FP64 walk's units: the geometry is multiplied by gs so that the squared
+// radius is r2 = t^2 (sech^2: t = 2 u log2(e), u = rho/lambda, as in FP32) or
+// r2 = v log2(e) (Gaussian: v = u^2), the arguments of exp2; the cross
+// product is in the same units, and what the ratio of qa to its value in
+// plain units leaves (ln 2 for sech^2) is in the epilogue constant cphi.
+template <int KIND>
+__device__ __forceinline__ double unit_scale64(const FieldArgs& f) {
+  if constexpr (KIND == kSech2) return kTwoLog2e * f.inv_lam_d;
+  if constexpr (KIND == kGauss) return 1.2011224087864498 * f.inv_lam_d;  // sqrt(log2 e)
+  return 1.0;
+}
+
+// The phase weight qa and the spin integrand b1 b2 (a product the caller
+// adds with one FMA; as for the sums below, written out so that every kernel
+// rounds alike).
+template <int KIND>
+__device__ __forceinline__ void field_f64(double r2, const FieldArgs& f, const Tables64& tab,
+                                          double& qa, double& b1, double& b2) {
   if constexpr (KIND == kConst) {
     (void)r2;
     (void)f;
     qa = 1.0;
-    qb = 1.0;
+    b1 = b2 = 1.0;
   } else if constexpr (KIND == kSech2) {
-    // q = 1/rho, t = 2u log2(e) with u = rho/lambda, E = exp(-2u) = 2^-t;
-    // 1/r2 = q^2.  Away from the axis (u >= 1/2, so E <= 1/e) the phase
-    // weight is (ln2 - ln(1+E) - 2u E/(1+E)) / r2 with ln(1+E) = E P(E).
-    const double q = rsq64(r2);
-    const double t = (r2 * q) * (kTwoLog2e * f.inv_lam_d);
-    const double E = exp2_neg64(t);
-    const double ip = rcp64(1.0 + E);
+    // E = exp(-2u) = 2^-t.  Away from the axis (u >= 1/2, so E <= 1/e) the
+    // phase weight is (1 - log2(1+E) - t E/(1+E)) / r2.
+    constexpr double kInv = 1.0 / (kTwoLog2e * kTwoLog2e);  // r2 -> u^2
+    double t, q;
+    sqrt_rsq64(r2, t, q);
+    const double E = exp2_neg64(t, tab);
+    const double opE = 1.0 + E;
+    const double ip = rcp64(opE);
     const double Eip = E * ip;
-    qb = Eip * ip;
-    const double v = r2 * f.inv_lam2_d;
-    if (v < 0.25) {
-      qa = horner_sv_f64<WL_Q_SECH2_F64_DEG>(WL_Q_SECH2_F64, v) * f.inv_lam2_d;
+    b1 = Eip;
+    b2 = ip;
+    if (r2 < 0.25 * kTwoLog2e * kTwoLog2e) {
+      qa = horner_sv_f64<WL_Q_SECH2_F64_DEG>(WL_Q_SECH2_F64, r2 * kInv) * (kInv / kLn2);
     } else {
-      const double L = E * horner_sv_f64<WL_LOG1P_F64_DEG>(WL_LOG1P_F64, E);
-      qa = fma(-(t * kLn2), Eip, kLn2 - L) * (q * q);
+      qa = fma(-t, Eip, one_minus_log2_1p(E, opE, tab)) * (q * q);
     }
   } else if constexpr (KIND == kGauss) {
-    const double v = r2 * f.inv_lam2_d;
-    const double E = exp2_neg64(v * kLog2e);
-    qb = E;
-    qa = v < 0.5 ? horner_sv_f64<WL_P_GAUSS_F64_DEG>(WL_P_GAUSS_F64, v) * f.inv_lam2_d
-                 : (1.0 - E) * rcp64(r2);
+    const double E = exp2_neg64(r2, tab);
+    b1 = E;
+    b2 = 1.0;
+    qa = r2 < 0.5 * kLog2e
+             ? horner_sv_f64<WL_P_GAUSS_F64_DEG>(WL_P_GAUSS_F64, r2 * kLn2) * kLn2
+             : (1.0 - E) * rcp64(r2);
   } else {
     const double r = rcp64(r2 + f.lam2_d);
     qa = r;
-    qb = r * r;
+    b1 = b2 = r;
   }
 }
 
@@ -294,12 +356,6 @@ __device__ __forceinline__ double4 seg_quantities64(double x0, double y0, double
   o.w = x0 * y1 - y0 * x1;
   return o;
 }
-
-// An FP64 segment array read in place.
-struct SegArray64 {
-  const double4* __restrict__ seg;
-  __device__ __forceinline__ double4 operator()(int32_t i) const { return seg[i]; }
-};
 
 struct LaneF32 {
   float rho_hi, rho_lo;  // rho_cm = hi + lo
@@ -576,31 +632,44 @@ __device__ __forceinline__ void loop_sums_f32k(const float4* __restrict__ seg, i
 // rounding of m_y^2 and c) and read from an array: the midpoint's radius
 // from m_x and m_y^2, and the
 // cross product's two parts summed apart as in the FP32 path,
-// cross = s^2 c + rho s d_y.  With EST, Q = sum_i qa_i^2.  `fetch` returns
-// segment i's quantities (SegArray64).
-template <int KIND, bool SPIN, bool EST, class Fetch>
-__device__ __forceinline__ void loop_sums_f64(const Fetch& fetch, int32_t n, double rho,
-                                              double s, const FieldArgs& f, double& A,
-                                              double& B, double& Q) {
-  constexpr bool kSpinSum = SPIN && KIND != kConst;
-  const double s2 = s * s;
+// cross = s^2 c + rho s d_y, with rho and s = sqrt(T) in the walk's units
+// (unit_scale64).  With EST, Q = sum_i qa_i^2.
+template <int KIND, bool SPIN, bool EST>
+struct Sums64 {
   double ac = 0.0, ad = 0.0, b = 0.0, q2 = 0.0;
-  double4 qn = fetch(0);
+  __device__ __forceinline__ void add(const double4& q, double rho, double s, double s2,
+                                      const FieldArgs& f, const Tables64& tab) {
+    const double mx = fma(s, q.x, rho);
+    double qa, b1, b2;
+    field_f64<KIND>(fma(mx, mx, fma(s2, q.y, 1e-300)), f, tab, qa, b1, b2);
+    ac = fma(q.w, qa, ac);
+    ad = fma(q.z, qa, ad);
+    if constexpr (SPIN && KIND != kConst) b = fma(b1, b2, b);
+    if constexpr (EST) q2 = fma3_f64(qa, qa, q2);
+  }
+  __device__ __forceinline__ void finish(double rho, double s, double s2, int32_t n, double& A,
+                                         double& B) const {
+    A = fma(s2, ac, (rho * s) * ad);
+    B = SPIN && KIND != kConst ? b : (double)n;
+  }
+};
+
+template <int KIND, bool SPIN, bool EST>
+__device__ __forceinline__ void loop_sums_f64(const double4* __restrict__ seg, int32_t n,
+                                              double rho, double s, const FieldArgs& f,
+                                              const Tables64& tab, double& A, double& B,
+                                              double& Q) {
+  const double s2 = s * s;
+  Sums64<KIND, SPIN, EST> sums;
+  double4 qn = seg[0];
   for (int32_t i = 0; i < n; ++i) {
     // the next segment's load is in flight while this one is evaluated
     const double4 q = qn;
-    qn = fetch(i + 1 < n ? i + 1 : i);
-    const double mx = fma(s, q.x, rho);
-    double qa, qb;
-    field_f64<KIND>(fma(mx, mx, fma(s2, q.y, 1e-300)), f, qa, qb);
-    ac = fma(q.w, qa, ac);
-    ad = fma(q.z, qa, ad);
-    if constexpr (kSpinSum) b += qb;
-    if constexpr (EST) q2 = fma3_f64(qa, qa, q2);
+    qn = seg[i + 1 < n ? i + 1 : i];
+    sums.add(q, rho, s, s2, f, tab);
   }
-  A = s2 * ac + (rho * s) * ad;
-  B = kSpinSum ? b : (double)n;
-  Q = q2;
+  sums.finish(rho, s, s2, n, A, B);
+  Q = sums.q2;
 }
 
 // The FP64 sums of a (sub-)loop formed from its raw FP32 points: the
@@ -609,50 +678,56 @@ __device__ __forceinline__ void loop_sums_f64(const Fetch& fetch, int32_t n, dou
 // circle, square and triangle sub-loops.  Each segment's quantities are
 // those of the FP64 segment arrays (seg_quantities64) and the sums are
 // formed as loop_sums_f64 forms them, so the results equal the FP64 path's
-// bit for bit.  The points are wave-uniform: they arrive by scalar loads,
-// one point ahead, and only the segment in hand occupies vector registers.
+// bit for bit.  P lanes of the wave (lane p of them) walk the loop together:
+// each forms the quantities of one segment of a block of P and leaves them
+// in `stage` (P entries of two double2 in LDS), from where the block is read back as
+// broadcasts, the next block's points in flight: formed by every lane for
+// itself they took 12 of 73 FP64 instructions per segment.
 template <int KIND, bool SPIN>
 __device__ __forceinline__ void loop_sums_f64raw(const float* __restrict__ x,
                                                  const float* __restrict__ y, int32_t n_ppl,
                                                  int32_t first, int32_t stride, int32_t m,
                                                  double rho, double s, const FieldArgs& f,
-                                                 double& A, double& B) {
-  constexpr bool kSpinSum = SPIN && KIND != kConst;
+                                                 const Tables64& tab, double2* stage, int32_t p,
+                                                 int32_t P, double& A, double& B) {
   const double s2 = s * s;
-  double ac = 0.0, ad = 0.0, b = 0.0;
-  int32_t a = first;
-  float x0 = x[a], y0 = y[a];
-  int32_t nb = a + stride;
-  if (nb >= n_ppl) nb -= n_ppl;
-  float x1 = x[nb], y1 = y[nb];
-  for (int32_t j = 0; j < m; ++j) {
-    // the point after next is loaded while this segment is evaluated
-    int32_t nn = nb + stride;
-    if (nn >= n_ppl) nn -= n_ppl;
-    const float x2 = x[nn], y2 = y[nn];
-    const double4 q = seg_quantities64(x0, y0, x1, y1);
-    const double mx = fma(s, q.x, rho);
-    double qa, qb;
-    field_f64<KIND>(fma(mx, mx, fma(s2, q.y, 1e-300)), f, qa, qb);
-    ac = fma(q.w, qa, ac);
-    ad = fma(q.z, qa, ad);
-    if constexpr (kSpinSum) b += qb;
-    x0 = x1;
-    y0 = y1;
-    x1 = x2;
-    y1 = y2;
-    nb = nn;
+  Sums64<KIND, SPIN, false> sums;
+  float x0, y0, x1, y1;
+  auto load = [&](int32_t i) {  // the end points of segment i (the last one's beyond it)
+    const int32_t j = i < m ? i : m - 1;
+    const int32_t a = first + j * stride;
+    const int32_t b = a + stride < n_ppl ? a + stride : a + stride - n_ppl;
+    x0 = x[a];
+    y0 = y[a];
+    x1 = x[b];
+    y1 = y[b];
+  };
+  load(p);
+  for (int32_t i = 0; i < m; i += P) {
+    const double4 mine = seg_quantities64(x0, y0, x1, y1);
+    // every lane's reads of the previous block are issued before the buffer
+    // is refilled, and the refill before any read (LDS operations of a wave
+    // complete in order)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    stage[2 * p] = make_double2(mine.x, mine.y);
+    stage[2 * p + 1] = make_double2(mine.z, mine.w);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    load(i + P + p);
+    const int32_t n = m - i < P ? m - i : P;
+    double2 m_n = stage[0], d_n = stage[1];
+    for (int32_t k = 0; k < n; ++k) {
+      const double4 q = make_double4(m_n.x, m_n.y, d_n.x, d_n.y);
+      const int32_t next = k + 1 < n ? k + 1 : k;
+      m_n = stage[2 * next];
+      d_n = stage[2 * next + 1];
+      sums.add(q, rho, s, s2, f, tab);
+    }
   }
-  A = s2 * ac + (rho * s) * ad;
-  B = kSpinSum ? b : (double)m;
-}
-
-template <int KIND, bool SPIN>
-__device__ __forceinline__ void loop_sums_f64seg(const double4* __restrict__ seg, int32_t n,
-                                                 double rho, double s, const FieldArgs& f,
-                                                 double& A, double& B) {
-  double Q;
-  loop_sums_f64<KIND, SPIN, false>(SegArray64{seg}, n, rho, s, f, A, B, Q);
+  sums.finish(rho, s, s2, m, A, B);
 }
 
 // Per-loop epilogue in FP64: phase, spin exponent and w.  The phase is
@@ -726,7 +801,7 @@ template <bool SPIN, int PREC>
 __device__ __forceinline__ void epilogue_parts(double A, double B, double T, int32_t n,
                                                const FieldArgs& f, double& phi, double& S,
                                                double& cw, double& ch) {
-  phi = (PREC == 2 ? f.cphi : f.cphi32) * A;
+  phi = f.cphi * A;
   S = SPIN ? f.cspin * (T / n) * B : 0.0;
   wparts<SPIN, PREC>(phi, S, cw, ch);
 }
@@ -794,7 +869,7 @@ __device__ __forceinline__ void disc_levels(double Ac, double Bc, double As, dou
                                             double At, double Bt, double T, int32_t h,
                                             int32_t q, const FieldArgs& f, bool full,
                                             double& w1, double& w2, double& w4) {
-  const double cp = PREC == 2 ? f.cphi : f.cphi32;
+  const double cp = f.cphi;
   const double pc = cp * Ac, ps = cp * As, pt = cp * At;
   double sc = 0.0, ss = 0.0, st = 0.0;
   if constexpr (SPIN) {
@@ -850,17 +925,18 @@ __device__ __forceinline__ int32_t tile_point(int32_t p, int32_t n_T, int32_t n_
 
 // One loop at this lane's grid point: its w, and its contributions da, dv to
 // the scale and rounding accumulators of the mean (loop_scale).  nrm: the
-// loop's norms sqrt(sum c^2), sqrt(sum d_y^2).
+// loop's norms sqrt(sum c^2), sqrt(sum d_y^2).  rho, s: FP64 in the walk's
+// units (unit_scale64; the FP32 paths take theirs from c).
 template <int KIND, bool SPIN, int PREC>
 __device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
                                            const double4* __restrict__ seg64, float2 nrm,
                                            int32_t n_ppl, int64_t l, double rho, double s,
                                            double T, const LaneF32& c, const FieldArgs& f,
-                                           float4* stage, double& w, double& da, double& dv) {
+                                           float4* stage, const Tables64& tab, double& w,
+                                           double& da, double& dv) {
   double A, B, Q, phi, S, cw, ch, R, U;
   if constexpr (PREC == 2) {
-    loop_sums_f64<KIND, SPIN, true>(SegArray64{seg64 + l * n_ppl}, n_ppl, rho, s, f, A, B,
-                                    Q);
+    loop_sums_f64<KIND, SPIN, true>(seg64 + l * n_ppl, n_ppl, rho, s, f, tab, A, B, Q);
     R = s * s;
     U = rho * s;
   } else {
@@ -873,8 +949,7 @@ __device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
   }
   epilogue_parts<SPIN, PREC>(A, B, T, n_ppl, f, phi, S, cw, ch);
   w = wprod<SPIN>(cw, ch);
-  loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, PREC == 2 ? f.cphi : f.cphi32), da,
-             dv);
+  loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, f.cphi), da, dv);
 }
 
 // The same, added to the sums of an item.
@@ -883,9 +958,11 @@ __device__ __forceinline__ void avg_loop(const float4* __restrict__ seg,
                                          const double4* __restrict__ seg64, float2 nrm,
                                          int32_t n_ppl, int64_t l, double rho, double s,
                                          double T, const LaneF32& c, const FieldArgs& f,
-                                         float4* stage, double& acc, double& a, double& v) {
+                                         float4* stage, const Tables64& tab, double& acc,
+                                         double& a, double& v) {
   double w, da, dv;
-  loop_terms<KIND, SPIN, PREC>(seg, seg64, nrm, n_ppl, l, rho, s, T, c, f, stage, w, da, dv);
+  loop_terms<KIND, SPIN, PREC>(seg, seg64, nrm, n_ppl, l, rho, s, T, c, f, stage, tab, w, da,
+                               dv);
   acc += w;
   a += da;
   v += dv;
@@ -927,7 +1004,7 @@ __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
                                          const double4* __restrict__ seg64,
                                          const float2* __restrict__ norm, int32_t n_ppl,
                                          const ReqDesc& q, int64_t loops_per_group,
-                                         int64_t item, float4* stage) {
+                                         int64_t item, float4* stage, const Tables64& tab) {
   const int32_t lane = threadIdx.x % kWave;
   const ItemRange r = item_range(item, q.n_chunks, q.n_sub, loops_per_group,
                                  q.loops_per_sub);
@@ -939,11 +1016,13 @@ __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
   const double T = q.T[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, q.f);
+  const double gs = PREC == 2 ? unit_scale64<KIND>(q.f) : 1.0;
+  const double rho_u = rho * gs, s_u = s * gs;
 
   double acc = 0.0, a = 0.0, v = 0.0;
   for (int64_t l = r.l0; l < r.l1; ++l)
-    avg_loop<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, q.f, stage, acc, a,
-                               v);
+    avg_loop<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, q.f, stage, tab,
+                               acc, a, v);
   if (valid) {
     const int64_t o = r.gs * n_pts + pg;
     q.out[o] = acc;
@@ -985,12 +1064,10 @@ __device__ __forceinline__ double esc_row_threshold(double ms, int64_t n_loops, 
 // chunk size C is 64, halved down to 8 while the items would not fill two
 // rounds of the chip's wave slots (a few flagged points then still spread
 // over every SIMD).  A chunk of more than 32 points takes one per lane, the
-// wave walking each loop together (its points come in through scalar loads
-// that the wave shares).  A chunk of at most P = 32, 16 or 8 points leaves
-// lanes free: the wave's lanes then form R = 64/P copies of the chunk, copy
-// r walking loops l0 + r, l0 + r + R, ... through vector loads (R loops per
-// wave, so a load touches at most 8 cache lines), and a fixed butterfly
-// adds the copies' sums.  Items are numbered chunk-major, k = c rows + gs
+// wave walking each loop together.  A chunk of at most P = 32, 16 or 8
+// points leaves lanes free: the wave's lanes then form R = 64/P copies of
+// the chunk, copy r walking loops l0 + r, l0 + r + R, ..., each copy staging
+// its own loop's segments, and a fixed butterfly adds the copies' sums.  Items are numbered chunk-major, k = c rows + gs
 // (rows = G n_sub), so that the items of a small count lie side by side and
 // spread over every XCD and compute unit.  The split depends only on the
 // count, so a request gives the same bits alone and in a batch.
@@ -1007,6 +1084,10 @@ __device__ __forceinline__ int64_t esc_items(int64_t rows, int32_t cnt) {
   return rows * (((int64_t)cnt + C - 1) / C);
 }
 
+// Staging entries (double2) of a wave of the recomputation: a segment of two
+// per lane, and one between the copies.
+constexpr int kEscStage = 2 * kWave + 8;
+
 template <int KIND, bool SPIN>
 __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
                                               const float* __restrict__ Y, int32_t n_ppl,
@@ -1018,7 +1099,8 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
                                               const int32_t* __restrict__ list, int32_t cnt,
                                               const double* __restrict__ pv,
                                               const double* __restrict__ scale,
-                                              double* __restrict__ out) {
+                                              double* __restrict__ out, double2* stage,
+                                              const Tables64& tab) {
   const int32_t chunk = (int32_t)(k / rows);
   const int64_t gs = k % rows;
   const int64_t g = gs / n_sub;
@@ -1040,29 +1122,22 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
   const double rho = rho_g[pg / n_T];
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
+  const double gs_u = unit_scale64<KIND>(f);
+  const double rho_u = rho * gs_u, s_u = s * gs_u;
   double acc = 0.0;
-  if (P == kWave) {
-    for (int64_t l = l0; l < l1; ++l) {
-      double A, B, phi, S;
-      // (wave_uniform keeps the compiler from merging this walk with the
-      // copies' below, which would make these loads vector loads)
-      const int64_t lu = wave_uniform(l);
-      loop_sums_f64raw<KIND, SPIN>(X + lu * n_ppl, Y + lu * n_ppl, n_ppl, 0, 1, n_ppl, rho,
-                                   s, f, A, B);
-      acc += epilogue<SPIN, 2>(A, B, T, n_ppl, f, phi, S);
-    }
-  } else {
-    const int32_t R = kWave / P;
-    for (int64_t l = l0 + r; l < l1; l += R) {
-      double A, B, phi, S;
-      loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, 0, 1, n_ppl, rho, s,
-                                   f, A, B);
-      acc += epilogue<SPIN, 2>(A, B, T, n_ppl, f, phi, S);
-    }
-    if (P == 8) acc += __shfl_xor(acc, 8);
-    if (P <= 16) acc += __shfl_xor(acc, 16);
-    acc += __shfl_xor(acc, 32);
+  // copy r's part of the staging buffer: P entries, and 16 bytes between the
+  // copies so that their broadcasts fall on different banks
+  double2* mine = stage + 2 * r * P + r;
+  const int32_t R = kWave / P;
+  for (int64_t l = l0 + r; l < l1; l += R) {
+    double A, B, phi, S;
+    loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, 0, 1, n_ppl, rho_u, s_u,
+                                 f, tab, mine, p, P, A, B);
+    acc += epilogue<SPIN, 2>(A, B, T, n_ppl, f, phi, S);
   }
+  if (P == 8) acc += __shfl_xor(acc, 8);
+  if (P <= 16) acc += __shfl_xor(acc, 16);
+  if (P <= 32) acc += __shfl_xor(acc, 32);
   if (need && r == 0) out[gs * n_pts + pg] = acc;
 }
 
@@ -1280,8 +1355,8 @@ __device__ __forceinline__ void finish_tile(const Finish& f, int32_t tile, int32
 // read by every chunk's workgroup at about the same time, from the XCD's L2.
 // Register budget 64 VGPRs, 8 waves per SIMD: the FP32 kernels (77
 // uncapped, 6 waves) then spill three per-item values, reloaded after the
-// item's last loop; the FP64 ones need at most 62 (their polynomial
-// coefficients are scalar operands).
+// item's last loop; the FP64 ones at most two (their polynomial coefficients
+// are scalar operands).
 // Dynamic LDS: per wave a staging buffer of kWave segments, then the terms.
 template <int KIND, bool SPIN, int PREC>
 __global__ __launch_bounds__(kSplitWaves * kWave)
@@ -1295,6 +1370,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
   const int32_t split = sc.split;
+  __shared__ Tables64 tab;
+  if constexpr (PREC == 2 && uses_tables<KIND>()) load_tables64(tab);
   float4* stage = split_lds + wave * kWave;
   double* terms = (double*)(split_lds + split * kWave);  // [2][split][3][kWave]
   const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
@@ -1307,6 +1384,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
+  const double gs = PREC == 2 ? unit_scale64<KIND>(f) : 1.0;
+  const double rho_u = rho * gs, s_u = s * gs;
 
   double acc = 0.0, a = 0.0, v = 0.0;
   double* mine = terms + wave * 3 * kWave + lane;
@@ -1316,8 +1395,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
     const int64_t l = l0 + wave;
     double w, da, dv;
     if (l < r.l1)
-      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, f, stage, w,
-                                   da, dv);
+      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, f, stage,
+                                   tab, w, da, dv);
     if (split == 1) {
       acc += w;
       a += da;
@@ -1355,8 +1434,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
 
 // FP64 recomputation of the flagged grid points of an evaluation: the
 // esc_items(G n_sub, count) items of escalate_item, grid-stride (four waves
-// per workgroup, no barrier).  Register budget 84 VGPRs, 6 waves per SIMD
-// (the sech^2 spinor walk needs 80).
+// per workgroup, no barrier after the tables).  Register budget 84 VGPRs, 6
+// waves per SIMD.
 template <int KIND, bool SPIN>
 __global__ __launch_bounds__(kWavesPerWG * kWave)
 __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate(
@@ -1365,6 +1444,9 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate(
     int32_t n_pts, FieldArgs f, Sched sc, const int32_t* __restrict__ list,
     const int32_t* __restrict__ count, const double* __restrict__ pv,
     const double* __restrict__ scale, double* __restrict__ out) {
+  __shared__ Tables64 tab;
+  __shared__ double2 stage[kWavesPerWG][kEscStage];
+  if constexpr (uses_tables<KIND>()) load_tables64(tab);
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t cnt = __builtin_amdgcn_readfirstlane(*count);
   const int64_t rows = sc.n_items / sc.n_chunks;
@@ -1373,7 +1455,7 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate(
        k += (int64_t)gridDim.x * kWavesPerWG)
     escalate_item<KIND, SPIN>(X, Y, n_ppl, rho_g, T_g, n_T, n_pts, f, k, rows, sc.n_sub,
                               sc.loops_per_group, sc.loops_per_sub, list, cnt, pv, scale,
-                              out);
+                              out, stage[wave], tab);
 }
 
 // The flagged points of one evaluation, compacted (compact_flags).
@@ -1405,7 +1487,7 @@ __global__ __launch_bounds__(kFinPts * kFinSlots) void k_finish(
 // The FP32 kernels are held to 80 VGPRs (6 waves per SIMD): their three sets
 // of sums need ~100, and the few values spilled to scratch (live across the
 // sub-loop walks, not inside them) cost less than the lost occupancy.  The
-// FP64 kernels need at most 76 and run at the same 6 waves per SIMD,
+// FP64 kernels need at most 77 and run at the same 6 waves per SIMD,
 // spilling nothing inside a segment walk.  4096 x 2048 loops on 32 x 32,
 // sech^2 spinor: 4.65 ms with 8 chunks per workgroup, 4.21 ms in this form.
 template <int KIND, bool SPIN, int PREC>
@@ -1420,6 +1502,8 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
   const int32_t split = sc.split;
+  __shared__ Tables64 tab;
+  if constexpr (PREC == 2 && uses_tables<KIND>()) load_tables64(tab);
   float4* stage = split_lds + wave * kWave;
   double* terms = (double*)(split_lds + split * kWave);  // [2][split][3][kWave]
   const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
@@ -1432,7 +1516,10 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
+  const double gs = PREC == 2 ? unit_scale64<KIND>(f) : 1.0;
+  const double rho_u = rho * gs, s_u = s * gs;
   const int32_t h = n_ppl / 2, q = n_ppl / 4;
+  double Q;
 
   double acc1 = 0.0, acc2 = 0.0, acc4 = 0.0;
   double* mine = terms + wave * 3 * kWave + lane;
@@ -1445,12 +1532,11 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
       double Ac, Bc, As, Bs, At, Bt;
       if constexpr (PREC == 2) {
         const double4* u = sub64 + l * n_ppl;
-        loop_sums_f64seg<KIND, SPIN>(u, h, rho, s, f, Ac, Bc);
-        loop_sums_f64seg<KIND, SPIN>(u + h, q, rho, s, f, As, Bs);
-        loop_sums_f64seg<KIND, SPIN>(u + h + q, q, rho, s, f, At, Bt);
+        loop_sums_f64<KIND, SPIN, false>(u, h, rho_u, s_u, f, tab, Ac, Bc, Q);
+        loop_sums_f64<KIND, SPIN, false>(u + h, q, rho_u, s_u, f, tab, As, Bs, Q);
+        loop_sums_f64<KIND, SPIN, false>(u + h + q, q, rho_u, s_u, f, tab, At, Bt, Q);
       } else {
         const float4* u = sub + l * n_ppl;
-        double Q;
         loop_sums_f32<KIND, SPIN, PREC == 0>(u, h, c, f, stage, Ac, Bc, Q);
         loop_sums_f32<KIND, SPIN, PREC == 0>(u + h, q, c, f, stage, As, Bs, Q);
         loop_sums_f32<KIND, SPIN, PREC == 0>(u + h + q, q, c, f, stage, At, Bt, Q);
@@ -1459,9 +1545,9 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
       if (full) {
         double A, B, phi, S;
         if constexpr (PREC == 2) {
-          loop_sums_f64seg<KIND, SPIN>(seg64 + l * n_ppl, n_ppl, rho, s, f, A, B);
+          loop_sums_f64<KIND, SPIN, false>(seg64 + l * n_ppl, n_ppl, rho_u, s_u, f, tab, A,
+                                           B, Q);
         } else {
-          double Q;
           loop_sums_f32<KIND, SPIN, PREC == 0>(seg + l * n_ppl, n_ppl, c, f, stage, A, B, Q);
         }
         w1 = epilogue<SPIN, PREC>(A, B, T, n_ppl, f, phi, S);
@@ -1528,7 +1614,7 @@ __device__ __forceinline__ int64_t next_item(unsigned int* counter) {
 // 5 at its 86): more waves hide the scalar-load and dispatch latencies of
 // the persistent item loop better than the spills it costs (measured
 // 2.20e12 -> 2.50e12 segment-evals/s on a 128-request batch).  The FP64
-// one runs at the same 8 waves (it needs 64 VGPRs, two per-item values
+// one runs at the same 8 waves (64 VGPRs, six per-item values
 // spilled outside the walks).
 template <int PREC>
 __global__ __launch_bounds__(kWavesPerWG * kWave)
@@ -1536,7 +1622,9 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
     const float4* __restrict__ seg, const double4* __restrict__ seg64,
     const float2* __restrict__ norm, int32_t n_ppl, const BatchHeader* __restrict__ hdr,
     unsigned int* __restrict__ counter, int64_t loops_per_group) {
-  __shared__ float4 stage[kWavesPerWG][kWave];
+  __shared__ float4 stage[kWavesPerWG][PREC == 0 ? kWave : 1];
+  __shared__ Tables64 tab;
+  if constexpr (PREC == 2) load_tables64(tab);
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
@@ -1553,7 +1641,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
     const int64_t li = item - q.item_begin;
     switch (q.f.kind * 2 + q.spin) {
 #define WL_ITEM(K, SP) \
-  run_item<K, SP, PREC>(seg, seg64, norm, n_ppl, q, loops_per_group, li, stage[wave])
+  run_item<K, SP, PREC>(seg, seg64, norm, n_ppl, q, loops_per_group, li, stage[wave], \
+                        tab)
       case 0: WL_ITEM(kConst, false); break;
       case 1: WL_ITEM(kConst, true); break;
       case 2: WL_ITEM(kSech2, false); break;
@@ -1581,6 +1670,10 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
     const float* __restrict__ X, const float* __restrict__ Y, int32_t n_ppl,
     const BatchHeader* __restrict__ hdr, unsigned int* __restrict__ counter,
     int32_t n_groups, int64_t loops_per_group) {
+  __shared__ Tables64 tab;
+  __shared__ double2 stage[kWavesPerWG][kEscStage];
+  if constexpr (uses_tables<KIND>()) load_tables64(tab);
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = (int32_t)hdr->n_reqs;
@@ -1602,7 +1695,7 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
     escalate_item<KIND, SPIN>(X, Y, n_ppl, q.rho, q.T, q.n_T, q.n_pts, q.f,
                               item - wave_uniform(esc_begin[lo]), (int64_t)n_groups * q.n_sub,
                               q.n_sub, loops_per_group, q.loops_per_sub, q.list, cnt, q.out_v,
-                              q.scale, q.out);
+                              q.scale, q.out, stage[wave], tab);
   }
 }
 
@@ -1708,6 +1801,10 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
     int32_t n_T, int32_t n_pts, int32_t n_chunks, FieldArgs f, int64_t loop0,
     int64_t n_loops, double* __restrict__ o_phase, double* __restrict__ o_spin,
     double* __restrict__ o_w) {
+  __shared__ Tables64 tab;
+  constexpr bool kRaw = PREC == 0;  // recomputes flagged lanes from the raw points
+  __shared__ double2 raw_stage[kRaw ? kWavesPerWG : 1][2 * kWave];
+  if constexpr ((PREC == 2 || kRaw) && uses_tables<KIND>()) load_tables64(tab);
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
   const int64_t item = (int64_t)blockIdx.x * kWavesPerWG + wave;
@@ -1723,9 +1820,11 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
   __shared__ float4 stage[staged_walk(KIND, SPIN, PREC == 0) ? kWavesPerWG : 1][kWave];
+  const double gs = unit_scale64<KIND>(f);
   double A, B, Q, phi, S;
   if constexpr (PREC == 2) {
-    loop_sums_f64seg<KIND, SPIN>(seg64 + l * n_ppl + sl.seg_off, sl.m, rho, s, f, A, B);
+    loop_sums_f64<KIND, SPIN, false>(seg64 + l * n_ppl + sl.seg_off, sl.m, rho * gs, s * gs, f,
+                                     tab, A, B, Q);
   } else if constexpr (PREC == 3) {
     loop_sums_f32k<KIND, SPIN>(seg + l * n_ppl + sl.seg_off, sl.m, c, f, A, B, Q);
   } else {
@@ -1735,12 +1834,13 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
   }
   double w = epilogue<SPIN, PREC>(A, B, T, sl.m, f, phi, S);
   if constexpr (PREC == 0) {
-    const double l2 = fabs(f.cphi32) * sqrt(Q);
+    const double l2 = fabs(f.cphi) * sqrt(Q);
     const bool esc = valid && kPhaseK * kU32 * l2 > 1e-5 * fmax(1.0, fabs(phi));
     if (__ballot(esc) != 0) {
       double A64, B64, phi64, S64;
       loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, sl.first, sl.stride,
-                                   sl.m, rho, s, f, A64, B64);
+                                   sl.m, rho * gs, s * gs, f, tab, raw_stage[kRaw ? wave : 0],
+                                   lane, kWave, A64, B64);
       const double w64 = epilogue<SPIN, 2>(A64, B64, T, sl.m, f, phi64, S64);
       if (esc) {
         phi = phi64;
