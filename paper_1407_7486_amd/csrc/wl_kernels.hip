@@ -678,7 +678,8 @@ __device__ __forceinline__ void loop_sums_f64(const double4* __restrict__ seg, i
 // circle, square and triangle sub-loops.  Each segment's quantities are
 // those of the FP64 segment arrays (seg_quantities64) and the sums are
 // formed as loop_sums_f64 forms them, so the results equal the FP64 path's
-// bit for bit.  P lanes of the wave (lane p of them) walk the loop together:
+// bit for bit when one wave walks them all.  Segments i0 .. i1-1 are added to
+// `sums`.  P lanes of the wave (lane p of them) walk the loop together:
 // each forms the quantities of one segment of a block of P and leaves them
 // in `stage` (P entries of two double2 in LDS), from where the block is read back as
 // broadcasts, the next block's points in flight: formed by every lane for
@@ -686,15 +687,16 @@ __device__ __forceinline__ void loop_sums_f64(const double4* __restrict__ seg, i
 template <int KIND, bool SPIN>
 __device__ __forceinline__ void loop_sums_f64raw(const float* __restrict__ x,
                                                  const float* __restrict__ y, int32_t n_ppl,
-                                                 int32_t first, int32_t stride, int32_t m,
-                                                 double rho, double s, const FieldArgs& f,
-                                                 const Tables64& tab, double2* stage, int32_t p,
-                                                 int32_t P, double& A, double& B) {
+                                                 int32_t first, int32_t stride, int32_t i0,
+                                                 int32_t i1, double rho, double s,
+                                                 const FieldArgs& f, const Tables64& tab,
+                                                 double2* stage, int32_t p, int32_t P,
+                                                 Sums64<KIND, SPIN, false>& sums) {
+  if (i0 >= i1) return;
   const double s2 = s * s;
-  Sums64<KIND, SPIN, false> sums;
   float x0, y0, x1, y1;
   auto load = [&](int32_t i) {  // the end points of segment i (the last one's beyond it)
-    const int32_t j = i < m ? i : m - 1;
+    const int32_t j = i < i1 ? i : i1 - 1;
     const int32_t a = first + j * stride;
     const int32_t b = a + stride < n_ppl ? a + stride : a + stride - n_ppl;
     x0 = x[a];
@@ -702,8 +704,8 @@ __device__ __forceinline__ void loop_sums_f64raw(const float* __restrict__ x,
     x1 = x[b];
     y1 = y[b];
   };
-  load(p);
-  for (int32_t i = 0; i < m; i += P) {
+  load(i0 + p);
+  for (int32_t i = i0; i < i1; i += P) {
     const double4 mine = seg_quantities64(x0, y0, x1, y1);
     // every lane's reads of the previous block are issued before the buffer
     // is refilled, and the refill before any read (LDS operations of a wave
@@ -717,7 +719,7 @@ __device__ __forceinline__ void loop_sums_f64raw(const float* __restrict__ x,
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     load(i + P + p);
-    const int32_t n = m - i < P ? m - i : P;
+    const int32_t n = i1 - i < P ? i1 - i : P;
     double2 m_n = stage[0], d_n = stage[1];
     for (int32_t k = 0; k < n; ++k) {
       const double4 q = make_double4(m_n.x, m_n.y, d_n.x, d_n.y);
@@ -727,7 +729,6 @@ __device__ __forceinline__ void loop_sums_f64raw(const float* __restrict__ x,
       sums.add(q, rho, s, s2, f, tab);
     }
   }
-  sums.finish(rho, s, s2, m, A, B);
 }
 
 // Per-loop epilogue in FP64: phase, spin exponent and w.  The phase is
@@ -1060,20 +1061,27 @@ __device__ __forceinline__ double esc_row_threshold(double ms, int64_t n_loops, 
 // points): the sub-range's loops are walked in FP64 from the raw points
 // (loop_sums_f64raw, the FP64 path's arithmetic) for the flagged points
 // list[C c .. C c + C - 1] (ascending, cnt of them), and each point's sum
-// of w over the sub-range is written over the item's FP32 partial sum.  The
-// chunk size C is 64, halved down to 8 while the items would not fill two
-// rounds of the chip's wave slots (a few flagged points then still spread
-// over every SIMD).  A chunk of more than 32 points takes one per lane, the
+// of w over the sub-range is written over the item's FP32 partial sum.  A
+// workgroup of four waves takes an item, each wave a quarter of every loop's
+// segments; the quarters' sums go through LDS and are added in order.  (With
+// a whole loop to a wave, a few flagged points ran one or two waves per SIMD
+// and many left a part-empty last round of long items: 36 points of 2040 x
+// 1003 loops 0.49 -> 0.18 ms, 561 points of 1024 x 8192 10.7 -> 9.6 ms.)  The
+// chunk size C is 64, halved down to 8 while there are fewer items than
+// kEscFill (a few flagged points then still spread over every SIMD; smaller
+// chunks than that mix more loops in a wave, near and far from the axis:
+// 561 points of 1024 x 8192 loops take 9.6 ms at C = 32, 10.2 at C = 8).  A chunk of more than 32 points takes one per lane, the
 // wave walking each loop together.  A chunk of at most P = 32, 16 or 8
 // points leaves lanes free: the wave's lanes then form R = 64/P copies of
 // the chunk, copy r walking loops l0 + r, l0 + r + R, ..., each copy staging
-// its own loop's segments, and a fixed butterfly adds the copies' sums.  Items are numbered chunk-major, k = c rows + gs
-// (rows = G n_sub), so that the items of a small count lie side by side and
-// spread over every XCD and compute unit.  The split depends only on the
-// count, so a request gives the same bits alone and in a batch.
-constexpr int kEscWaves = 6;  // waves per SIMD of the recomputation kernels
-// two rounds of wave slots: 1024 SIMDs (256 CUs) x kEscWaves, twice
-constexpr int64_t kEscFill = 2 * 1024 * kEscWaves;
+// its own loop's segments, and a fixed butterfly adds the copies' sums.
+// Items are numbered chunk-major, k = c rows + gs (rows = G n_sub), so that
+// the items of a small count lie side by side and spread over every XCD and
+// compute unit.  The split depends only on the count, so a request gives the
+// same bits alone and in a batch.
+constexpr int kEscWaves = 5;  // waves per SIMD of the recomputation kernels
+// a little over one round of workgroups (256 CUs x kEscWaves)
+constexpr int64_t kEscFill = 1536;
 __device__ __forceinline__ int32_t esc_chunk(int64_t rows, int32_t cnt) {
   int32_t C = kWave;
   while (C > 8 && rows * (((int64_t)cnt + C - 1) / C) < kEscFill) C >>= 1;
@@ -1084,10 +1092,16 @@ __device__ __forceinline__ int64_t esc_items(int64_t rows, int32_t cnt) {
   return rows * (((int64_t)cnt + C - 1) / C);
 }
 
-// Staging entries (double2) of a wave of the recomputation: a segment of two
-// per lane, and one between the copies.
-constexpr int kEscStage = 2 * kWave + 8;
+// LDS of a workgroup of the recomputation: per wave the staging entries (a
+// segment of two per lane, and one between the copies), and two buffers of
+// the waves' sums (ac, ad, b) of one round of loops.
+struct EscShared {
+  Tables64 tab;
+  double2 stage[kWavesPerWG][2 * kWave + 8];
+  double part[2][kWavesPerWG][3][kWave];
+};
 
+// One item by the whole workgroup; buf: the buffer of the next round.
 template <int KIND, bool SPIN>
 __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
                                               const float* __restrict__ Y, int32_t n_ppl,
@@ -1099,14 +1113,15 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
                                               const int32_t* __restrict__ list, int32_t cnt,
                                               const double* __restrict__ pv,
                                               const double* __restrict__ scale,
-                                              double* __restrict__ out, double2* stage,
-                                              const Tables64& tab) {
+                                              double* __restrict__ out, EscShared& sh,
+                                              int32_t& buf) {
   const int32_t chunk = (int32_t)(k / rows);
   const int64_t gs = k % rows;
   const int64_t g = gs / n_sub;
   const int64_t l0 = g * loops_per_group + (gs % n_sub) * loops_per_sub;
   int64_t l1 = l0 + loops_per_sub;
   if (l1 > (g + 1) * loops_per_group) l1 = (g + 1) * loops_per_group;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = (int32_t)(threadIdx.x % kWave);
   const int32_t C = esc_chunk(rows, cnt);                // wave-uniform
   const int32_t cnt_c = min(C, cnt - chunk * C);         // 1 .. C
@@ -1115,7 +1130,7 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
   const bool esc = p < cnt_c;
   const int32_t pg = list[chunk * C + (esc ? p : cnt_c - 1)];
   // only the rows that carry the point's estimate are recomputed; an item
-  // none of whose points needs its row does nothing
+  // none of whose points needs its row does nothing (the same for every wave)
   const int64_t n_loops = loops_per_group * (rows / n_sub);
   const bool need = esc && pv[gs * n_pts + pg] > esc_row_threshold(scale[pg], n_loops, rows);
   if (__ballot(need) == 0) return;
@@ -1127,14 +1142,34 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
   double acc = 0.0;
   // copy r's part of the staging buffer: P entries, and 16 bytes between the
   // copies so that their broadcasts fall on different banks
-  double2* mine = stage + 2 * r * P + r;
+  double2* mine = sh.stage[wave] + 2 * r * P + r;
   const int32_t R = kWave / P;
-  for (int64_t l = l0 + r; l < l1; l += R) {
-    double A, B, phi, S;
-    loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, 0, 1, n_ppl, rho_u, s_u,
-                                 f, tab, mine, p, P, A, B);
-    acc += epilogue<SPIN, 2>(A, B, T, n_ppl, f, phi, S);
+  const int32_t quarter = (n_ppl + kWavesPerWG - 1) / kWavesPerWG;
+  const int32_t i0 = wave * quarter, i1 = min(i0 + quarter, n_ppl);
+  for (int64_t lr = l0; lr < l1; lr += R) {
+    const int64_t l = lr + r;
+    Sums64<KIND, SPIN, false> sums;
+    if (l < l1)
+      loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, 0, 1, i0, i1, rho_u,
+                                   s_u, f, sh.tab, mine, p, P, sums);
+    sh.part[buf][wave][0][lane] = sums.ac;
+    sh.part[buf][wave][1][lane] = sums.ad;
+    if constexpr (SPIN && KIND != kConst) sh.part[buf][wave][2][lane] = sums.b;
+    __syncthreads();
+    if (wave == 0 && l < l1) {
+      double A, B, phi, S;
+#pragma unroll
+      for (int w = 1; w < kWavesPerWG; ++w) {
+        sums.ac += sh.part[buf][w][0][lane];
+        sums.ad += sh.part[buf][w][1][lane];
+        if constexpr (SPIN && KIND != kConst) sums.b += sh.part[buf][w][2][lane];
+      }
+      sums.finish(rho_u, s_u, s_u * s_u, n_ppl, A, B);
+      acc += epilogue<SPIN, 2>(A, B, T, n_ppl, f, phi, S);
+    }
+    buf ^= 1;
   }
+  if (wave != 0) return;
   if (P == 8) acc += __shfl_xor(acc, 8);
   if (P <= 16) acc += __shfl_xor(acc, 16);
   if (P <= 32) acc += __shfl_xor(acc, 32);
@@ -1433,9 +1468,9 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
 }
 
 // FP64 recomputation of the flagged grid points of an evaluation: the
-// esc_items(G n_sub, count) items of escalate_item, grid-stride (four waves
-// per workgroup, no barrier after the tables).  Register budget 84 VGPRs, 6
-// waves per SIMD.
+// esc_items(G n_sub, count) items of escalate_item, grid-stride.  Register
+// budget 96 VGPRs, 5 waves per SIMD (4 to 6 measured alike: FP64 issue bounds
+// it).
 template <int KIND, bool SPIN>
 __global__ __launch_bounds__(kWavesPerWG * kWave)
 __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate(
@@ -1444,18 +1479,17 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate(
     int32_t n_pts, FieldArgs f, Sched sc, const int32_t* __restrict__ list,
     const int32_t* __restrict__ count, const double* __restrict__ pv,
     const double* __restrict__ scale, double* __restrict__ out) {
-  __shared__ Tables64 tab;
-  __shared__ double2 stage[kWavesPerWG][kEscStage];
-  if constexpr (uses_tables<KIND>()) load_tables64(tab);
-  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  __shared__ EscShared sh;
   const int32_t cnt = __builtin_amdgcn_readfirstlane(*count);
   const int64_t rows = sc.n_items / sc.n_chunks;
   const int64_t total = esc_items(rows, cnt);
-  for (int64_t k = (int64_t)blockIdx.x * kWavesPerWG + wave; k < total;
-       k += (int64_t)gridDim.x * kWavesPerWG)
+  if (blockIdx.x >= total) return;
+  if constexpr (uses_tables<KIND>()) load_tables64(sh.tab);
+  int32_t buf = 0;
+  for (int64_t k = blockIdx.x; k < total; k += gridDim.x)
     escalate_item<KIND, SPIN>(X, Y, n_ppl, rho_g, T_g, n_T, n_pts, f, k, rows, sc.n_sub,
                               sc.loops_per_group, sc.loops_per_sub, list, cnt, pv, scale,
-                              out, stage[wave], tab);
+                              out, sh, buf);
 }
 
 // The flagged points of one evaluation, compacted (compact_flags).
@@ -1670,9 +1704,8 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
     const float* __restrict__ X, const float* __restrict__ Y, int32_t n_ppl,
     const BatchHeader* __restrict__ hdr, unsigned int* __restrict__ counter,
     int32_t n_groups, int64_t loops_per_group) {
-  __shared__ Tables64 tab;
-  __shared__ double2 stage[kWavesPerWG][kEscStage];
-  if constexpr (uses_tables<KIND>()) load_tables64(tab);
+  __shared__ EscShared sh;
+  __shared__ unsigned int taken[2];
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
@@ -1682,7 +1715,10 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
   // the table is written by an earlier kernel, so its entries come in
   // through vector loads: wave_uniform keeps the loop's branches scalar
   const int64_t total = wave_uniform(esc_begin[n_reqs]);
-  for (int64_t item = first_item(); item < total; item = next_item(counter)) {
+  if (blockIdx.x >= total) return;
+  if constexpr (uses_tables<KIND>()) load_tables64(sh.tab);
+  int32_t buf = 0, turn = 0;
+  for (int64_t item = blockIdx.x; item < total;) {
     // request owning the item: last r with esc_begin[r] <= item (a request
     // without items has the same entry as the next one and is passed over)
     int32_t lo = 0, hi = n_reqs - 1;
@@ -1695,7 +1731,18 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
     escalate_item<KIND, SPIN>(X, Y, n_ppl, q.rho, q.T, q.n_T, q.n_pts, q.f,
                               item - wave_uniform(esc_begin[lo]), (int64_t)n_groups * q.n_sub,
                               q.n_sub, loops_per_group, q.loops_per_sub, q.list, cnt, q.out_v,
-                              q.scale, q.out, stage[wave], tab);
+                              q.scale, q.out, sh, buf);
+    // the workgroup's next item, taken by its first wave (as next_item; every
+    // lane stores the same value).  Two slots: a wave may still read the last
+    // one while the first wave, an item ahead, writes the next.
+    if (wave == 0) {
+      const unsigned int t = atomicAdd(counter, threadIdx.x % kWave == 0 ? 1u : 0u);
+      taken[turn] = (unsigned int)__builtin_amdgcn_readfirstlane((int)t);
+    }
+    __syncthreads();
+    item = (int64_t)gridDim.x +
+           (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)taken[turn]);
+    turn ^= 1;
   }
 }
 
@@ -1838,9 +1885,11 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
     const bool esc = valid && kPhaseK * kU32 * l2 > 1e-5 * fmax(1.0, fabs(phi));
     if (__ballot(esc) != 0) {
       double A64, B64, phi64, S64;
-      loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, sl.first, sl.stride,
+      Sums64<KIND, SPIN, false> sums;
+      loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, sl.first, sl.stride, 0,
                                    sl.m, rho * gs, s * gs, f, tab, raw_stage[kRaw ? wave : 0],
-                                   lane, kWave, A64, B64);
+                                   lane, kWave, sums);
+      sums.finish(rho * gs, s * gs, (s * gs) * (s * gs), sl.m, A64, B64);
       const double w64 = epilogue<SPIN, 2>(A64, B64, T, sl.m, f, phi64, S64);
       if (esc) {
         phi = phi64;
@@ -2093,7 +2142,7 @@ hipError_t launch_esc_t(const FieldArgs& f, const float* x, const float* y, int3
   // at most n_pts points flagged: enough workgroups for the largest count
   // (the evaluation's n_items items), up to 4096 (16384 waves, 4 per SIMD on
   // 1024 SIMDs four times over)
-  int64_t n_wg = (s.n_items + kWavesPerWG - 1) / kWavesPerWG;
+  int64_t n_wg = s.n_items;
   if (n_wg > 4096) n_wg = 4096;
   hipLaunchKernelGGL((k_escalate<KIND, SPIN>), dim3((uint32_t)n_wg), dim3(kWavesPerWG * kWave),
                      0, st, x, y, n_ppl, rho, T, n_T, n_pts, f, s, list, count, pv, scale, out);
