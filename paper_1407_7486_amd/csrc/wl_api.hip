@@ -157,6 +157,17 @@ wl::Sched make_sched(const wl_ctx* ctx, const wl_ens* e, int32_t n_pts) {
   return s;
 }
 
+// Waves to an item of a wide batch (a power of two, one per loop): the
+// workgroup's 8 waves hold 8 / team items, a bundle.
+static int32_t wide_team(int64_t loops_per_sub) {
+  return loops_per_sub >= 8 ? 8 : loops_per_sub >= 4 ? 4 : loops_per_sub >= 2 ? 2 : 1;
+}
+
+static int64_t bundles(const wl::Sched& s) {
+  const int32_t per = kSplitWaves / wide_team(s.loops_per_sub);
+  return (s.n_items + per - 1) / per;
+}
+
 ReqPlan plan_request(const wl_ctx* ctx, const wl_ens* ens, const wl_request& q) {
   ReqPlan p;
   p.n_pts = q.n_rho * q.n_T;
@@ -183,8 +194,23 @@ bool build_batch(const wl_ens* ens, const wl_request* const* reqs, const FieldAr
   const int64_t G = ens->n_groups;
   *lay = BatchLayout();
   int64_t grid_n = 0;
+  // Wide (k_batch_wide) or narrow: an item per wave ends in a part-empty round
+  // of whole items (~0.4 of one); bundles cost 3%, more where a last round of
+  // loops leaves waves of a team idle, and in FP64, whose bundle kernel keeps
+  // fewer waves.  Rounds of the chip's wave slots, narrow and wide: 1: 1.64
+  // and 1.0 ms; 17: 30.2 and 31.0; 4 (plain FP32) 9.3 and 8.8; 6 with 10
+  // loops per row 19.2 and 21.0; 4 in FP64 28.8 and 32.7.
+  int64_t items_n = 0, uneven = 0;
   for (int32_t i = 0; i < n; ++i) {
-    lay->items += plans[i].s.n_items;
+    const int64_t lps = plans[i].s.loops_per_sub, team = wide_team(lps);
+    items_n += plans[i].s.n_items;
+    if (100 * ((lps + team - 1) / team * team) > 115 * lps) uneven += plans[i].s.n_items;
+  }
+  const int64_t round = 32 * (int64_t)ens->ctx->num_cu;
+  const int64_t limit = reqs[0]->precision == WL_FP64 ? 2 : 2 * uneven > items_n ? 3 : 10;
+  const bool wide = items_n < limit * round;
+  for (int32_t i = 0; i < n; ++i) {
+    lay->items += wide ? bundles(plans[i].s) : plans[i].s.n_items;
     lay->sums_n += G * plans[i].n_pts;
     lay->pts_n += plans[i].n_pts;
     lay->acc_n += G * plans[i].s.n_sub * plans[i].n_pts;
@@ -201,6 +227,7 @@ bool build_batch(const wl_ens* ens, const wl_request* const* reqs, const FieldAr
   char* hb = (char*)h_in;
   BatchHeader* hdr = (BatchHeader*)hb;
   hdr->n_reqs = n;
+  hdr->wide = wide ? 1 : 0;
   hdr->total_items = lay->items;
   hdr->total_sums = lay->sums_n;
   hdr->total_pts = lay->pts_n;
@@ -247,13 +274,14 @@ bool build_batch(const wl_ens* ens, const wl_request* const* reqs, const FieldAr
     e.n_chunks = pl.s.n_chunks;
     e.n_T = q.n_T;
     e.n_pts = pl.n_pts;
-    e.spin = q.spin;
+    e.spin = (int16_t)q.spin;
+    e.team = (int16_t)wide_team(pl.s.loops_per_sub);
     e.tile_begin = tiles;
     tiles += (pl.n_pts + kFinishPts - 1) / kFinishPts;
     desc[i] = e;
     lay->sums_begin.push_back(sums);
     lay->pts_begin.push_back(pts);
-    items += pl.s.n_items;
+    items += wide ? bundles(pl.s) : pl.s.n_items;
     sums += G * pl.n_pts;
     pts += pl.n_pts;
     acc += G * pl.s.n_sub * pl.n_pts;
@@ -892,15 +920,12 @@ int wl_average_batch(wl_ctx* ctx, const wl_ens* ens, const wl_request* reqs,
     if (!build_batch(ens, rq.data(), rf.data(), pl.data(), (int32_t)rq.size(), h_in.data(),
                      in_b, d_in, d_res, res_b, &lay))
       return fail(ctx, WL_EINVAL, "internal: batch layout exceeds its buffer");
-    const int64_t want_wg = (lay.items + kWavesPerWG - 1) / kWavesPerWG;
-    const int64_t max_wg = (int64_t)ctx->num_cu * 8;
     hipError_t e = hipMemcpyAsync(d_in, h_in.data(), lay.in_bytes, hipMemcpyHostToDevice,
                                   ctx->stream);
     if (e == hipSuccess)
       e = wl::launch_batch(prec, ens->d_seg, ens->d_seg64, ens->d_norm, ens->d_x, ens->d_y,
                            ens->n_ppl, d_in, ens->n_groups, ens->n_loops, ctx->d_counter,
-                           d_res, (int32_t)(want_wg < max_wg ? want_wg : max_wg),
-                           ctx->stream);
+                           d_res, ctx->num_cu, ctx->stream);
     std::vector<double> h_res(lay.head_bytes / sizeof(double));
     if (e == hipSuccess)
       e = hipMemcpyAsync(h_res.data(), d_res, h_res.size() * sizeof(double),

@@ -62,8 +62,9 @@ struct FieldArgs {
 // n_reqs ReqDesc.  The batch kernels read the counts from here, so one
 // captured launch sequence serves batches of any composition.
 struct BatchHeader {
-  int64_t n_reqs;
-  int64_t total_items;
+  int32_t n_reqs;
+  int32_t wide;         // units of work: 1 bundles (k_batch_wide), 0 items
+  int64_t total_items;  // units of work
   int64_t total_sums;
   int64_t total_pts;
   int64_t* esc_begin;  // [8][n_reqs + 1] first FP64 recomputation item per
@@ -88,16 +89,17 @@ struct ReqDesc {
   uint8_t* flags;       // [n_pts] grid points recomputed in FP64
   int32_t* list;        // [n_pts] the flagged points, compacted
   int32_t* count;       // [1] how many are flagged
-  int64_t item_begin;   // first item of this request in the batch
+  int64_t item_begin;   // first unit of work of this request in the batch
   int64_t loops_per_sub;
   int64_t sums_begin;   // offset of [G][n_pts] group sums in the batch
   int64_t pts_begin;    // offset of [n_pts] means / errors in the batch
   int32_t n_sub, n_chunks, n_T, n_pts;
-  int32_t spin;
+  int16_t spin;
+  int16_t team;         // waves per item (wide)
   int32_t tile_begin;   // first finishing tile (kFinishPts points) in the batch
 };
 
-constexpr int kWavesPerWG = 4;  // batch and per-loop kernels
+constexpr int kWavesPerWG = 4;  // recomputation and per-loop kernels
 constexpr int kWave = 64;
 constexpr int kFinishPts = 16;  // grid points per tile of the finishing kernels
 // most waves that an item's loops are dealt to (k_average, k_disc)
@@ -193,13 +195,13 @@ hipError_t launch_disc_finish(const double* d_part, double* d_sums, int32_t n_gr
 // flagged points and their results again, all reading `d_hdr` (BatchHeader
 // followed by the descriptors, whose pointers place every array).  Results at
 // d_res: [group sums | means | errors | scales | rounding estimates | flags |
-// ...] with the sizes from the header.  Grid sizes are fixed (n_wg persistent
-// workgroups) and d_counter holds kBatchCounters work counters, so the
+// ...] with the sizes from the header.  Grid sizes are fixed (persistent
+// workgroups filling n_cu compute units) and d_counter holds kBatchCounters work counters, so the
 // sequence can be captured once and replayed.
 hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg64,
                         const float2* d_norm, const float* d_x, const float* d_y,
                         int32_t n_ppl, const void* d_hdr, int32_t n_groups, int64_t n_loops,
-                        unsigned int* d_counter, double* d_res, int32_t n_wg,
+                        unsigned int* d_counter, double* d_res, int32_t n_cu,
                         hipStream_t stream);
 
 }  // namespace wl

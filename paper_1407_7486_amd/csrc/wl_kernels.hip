@@ -953,22 +953,6 @@ __device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
   loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, f.cphi), da, dv);
 }
 
-// The same, added to the sums of an item.
-template <int KIND, bool SPIN, int PREC>
-__device__ __forceinline__ void avg_loop(const float4* __restrict__ seg,
-                                         const double4* __restrict__ seg64, float2 nrm,
-                                         int32_t n_ppl, int64_t l, double rho, double s,
-                                         double T, const LaneF32& c, const FieldArgs& f,
-                                         float4* stage, const Tables64& tab, double& acc,
-                                         double& a, double& v) {
-  double w, da, dv;
-  loop_terms<KIND, SPIN, PREC>(seg, seg64, nrm, n_ppl, l, rho, s, T, c, f, stage, tab, w, da,
-                               dv);
-  acc += w;
-  a += da;
-  v += dv;
-}
-
 // The domain of a grid point: rho_cm >= 0 and T > 0, both finite.
 __device__ __forceinline__ bool grid_ok(double rho, double T) {
   return rho >= 0.0 && T > 0.0 && rho < INFINITY && T < INFINITY;
@@ -997,9 +981,84 @@ __device__ __forceinline__ ItemRange item_range(int64_t item, int32_t n_chunks,
   return r;
 }
 
-// One work item of a batch request.  Lane j owns grid point chunk*64 + j and
-// accumulates its w over the sub-range's loops in order; the sums land in
-// row gs of q.out, q.out_a and q.out_v.
+// One bundle of a batch request's work items by a workgroup of kSplitWaves
+// waves: a team of q.team waves per item (1, 2, 4 or 8, wide_team), the
+// item's loops dealt to the team as in k_average (same sums).  Lane j owns
+// grid point chunk*64 + j; the sums land in row gs of q.out, q.out_a and
+// q.out_v.  Every wave runs the same rounds.
+struct BatchShared {
+  Tables64 tab;  // FP64
+  float4 stage[kSplitWaves][kWave];  // compensated FP32
+  double terms[2][kSplitWaves][3][kWave];
+  unsigned int taken[2];
+};
+template <int KIND, bool SPIN, int PREC>
+__device__ __forceinline__ void run_bundle(const float4* __restrict__ seg,
+                                           const double4* __restrict__ seg64,
+                                           const float2* __restrict__ norm, int32_t n_ppl,
+                                           const ReqDesc& q, int32_t n_groups,
+                                           int64_t loops_per_group, int64_t bundle,
+                                           BatchShared& sh) {
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int32_t lane = threadIdx.x % kWave;
+  const int32_t n_pts = q.n_pts, n_T = q.n_T;
+  const int32_t team = q.team;
+  const int32_t part = wave % team;
+  const int64_t item = bundle * (kSplitWaves / team) + wave / team;
+  double(*terms)[kSplitWaves][3][kWave] =
+      (double(*)[kSplitWaves][3][kWave])(&sh.terms[0][wave / team * team]);
+  const bool live = item < (int64_t)n_groups * q.n_sub * q.n_chunks;
+  ItemRange r = item_range(live ? item : 0, q.n_chunks, q.n_sub, loops_per_group,
+                           q.loops_per_sub);
+  if (!live) r.l1 = r.l0;
+  const int32_t p = r.chunk * kWave + lane;
+  const bool valid = live && p < n_pts;
+  const int32_t pg = tile_point(p < n_pts ? p : n_pts - 1, n_T, n_pts);
+  const double rho = q.rho[pg / n_T];
+  const double T = q.T[pg % n_T];
+  const double s = sqrt(T);
+  const LaneF32 c = lane_consts(rho, s, T, q.f);
+  const double gs = PREC == 2 ? unit_scale64<KIND>(q.f) : 1.0;
+  const double rho_u = rho * gs, s_u = s * gs;
+
+  double acc = 0.0, a = 0.0, v = 0.0;
+  int32_t buf = 0;
+  for (int64_t k = 0; k < q.loops_per_sub; k += team) {
+    const int64_t l = r.l0 + k + part;
+    double w = 0.0, da = 0.0, dv = 0.0;
+    if (l < r.l1)
+      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, q.f,
+                                   sh.stage[wave], sh.tab, w, da, dv);
+    if (team == 1) {
+      acc += w;
+      a += da;
+      v += dv;
+      continue;
+    }
+    terms[buf][part][0][lane] = w;
+    terms[buf][part][1][lane] = da;
+    terms[buf][part][2][lane] = dv;
+    __syncthreads();
+    if (part == 0) {
+      const int64_t left = r.l1 - (r.l0 + k);
+      const int32_t n = left < team ? (int32_t)left : team;
+      for (int32_t i = 0; i < n; ++i) {
+        acc += terms[buf][i][0][lane];
+        a += terms[buf][i][1][lane];
+        v += terms[buf][i][2][lane];
+      }
+    }
+    buf ^= 1;
+  }
+  if (valid && part == 0) {
+    const int64_t o = r.gs * n_pts + pg;
+    q.out[o] = acc;
+    q.out_a[o] = a;
+    q.out_v[o] = v;
+  }
+}
+
+// One work item of a batch request by one wave: its loops in order.
 template <int KIND, bool SPIN, int PREC>
 __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
                                          const double4* __restrict__ seg64,
@@ -1021,9 +1080,14 @@ __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
   const double rho_u = rho * gs, s_u = s * gs;
 
   double acc = 0.0, a = 0.0, v = 0.0;
-  for (int64_t l = r.l0; l < r.l1; ++l)
-    avg_loop<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, q.f, stage, tab,
-                               acc, a, v);
+  for (int64_t l = r.l0; l < r.l1; ++l) {
+    double w, da, dv;
+    loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, q.f, stage,
+                                 tab, w, da, dv);
+    acc += w;
+    a += da;
+    v += dv;
+  }
   if (valid) {
     const int64_t o = r.gs * n_pts + pg;
     q.out[o] = acc;
@@ -1405,11 +1469,11 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
   const int32_t split = sc.split;
+  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
   __shared__ Tables64 tab;
   if constexpr (PREC == 2 && uses_tables<KIND>()) load_tables64(tab);
   float4* stage = split_lds + wave * kWave;
   double* terms = (double*)(split_lds + split * kWave);  // [2][split][3][kWave]
-  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
   const ItemRange r = item_range(item, sc.n_chunks, sc.n_sub, sc.loops_per_group,
                                  sc.loops_per_sub);
   const int32_t p = r.chunk * kWave + lane;
@@ -1536,11 +1600,11 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int32_t lane = threadIdx.x % kWave;
   const int32_t split = sc.split;
+  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
   __shared__ Tables64 tab;
   if constexpr (PREC == 2 && uses_tables<KIND>()) load_tables64(tab);
   float4* stage = split_lds + wave * kWave;
   double* terms = (double*)(split_lds + split * kWave);  // [2][split][3][kWave]
-  const int64_t item = remap_wg(blockIdx.x, sc.n_wg, sc.n_xcd);  // < n_items = n_wg
   const ItemRange r = item_range(item, sc.n_chunks, sc.n_sub, sc.loops_per_group,
                                  sc.loops_per_sub);
   const int32_t p = r.chunk * kWave + lane;
@@ -1619,37 +1683,93 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   }
 }
 
-// Next item of a persistent wavefront's work loop: the wave's own index for
-// the first one, then one increment of the counter per wave, whose old value
-// every lane receives.  (With an atomic for the first item too, 8192 waves
-// took 96 us to find an empty list: the atomics of one address follow one
-// another.)  Every lane executes the atomic (lane 0 adds 1, the others 0; the
-// compiler folds the wave's lanes into one memory operation), so that no
-// lane-dependent branch sits in the loop: around a branch on the lane the
-// compiler may send lanes 1..63 from the end of one item straight back to the
-// broadcast, where they then run without lane 0 and read a stale item.
-__device__ __forceinline__ int64_t first_item() {
-  return (int64_t)blockIdx.x * kWavesPerWG +
-         __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+// Items of a persistent workgroup's work loop: its own index first (with an
+// atomic for that too, 8192 waves took 96 us to find an empty list, since the
+// atomics of one address follow one another), then from a counter.  The first
+// wave asks for the next item before the workgroup works on the current one,
+// so that the atomic's latency is hidden: every lane of it executes the
+// atomic (lane 0 adds 1, the others 0; the compiler folds them into one
+// memory operation) and stores the same value, so that no lane-dependent
+// branch sits in the loop.  The value reaches the others through one of two
+// slots after the barrier that ends the current item: a wave may still read
+// the last one while the first wave, an item ahead, writes the next.
+__device__ __forceinline__ void ask_item(unsigned int* counter, unsigned int* taken,
+                                         int32_t turn) {
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) == 0) {
+    const unsigned int t = atomicAdd(counter, threadIdx.x % kWave == 0 ? 1u : 0u);
+    taken[turn] = (unsigned int)__builtin_amdgcn_readfirstlane((int)t);
+  }
 }
-__device__ __forceinline__ int64_t next_item(unsigned int* counter) {
-  const unsigned int t = atomicAdd(counter, threadIdx.x % kWave == 0 ? 1u : 0u);
-  return (int64_t)gridDim.x * kWavesPerWG +
-         (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+__device__ __forceinline__ int64_t next_item(const unsigned int* taken, int32_t& turn) {
+  __syncthreads();
+  const unsigned int t = (unsigned int)__builtin_amdgcn_readfirstlane((int)taken[turn]);
+  turn ^= 1;
+  return (int64_t)gridDim.x + (int64_t)t;
 }
 
-// Batched evaluation of uneven requests in one persistent launch.  Items of
-// all requests form one index space (request r owns [item_begin_r,
-// item_begin_r + n_items_r)); each wavefront repeatedly takes the next item
-// from a device counter until the counter passes the total, so every wave
-// exits once the work is handed out.  An item's output slot is fixed by its
-// index, so results do not depend on which wave ran it.
-// The FP32 batch kernel is held to 64 VGPRs (8 waves per SIMD instead of
-// 5 at its 86): more waves hide the scalar-load and dispatch latencies of
-// the persistent item loop better than the spills it costs (measured
-// 2.20e12 -> 2.50e12 segment-evals/s on a 128-request batch).  The FP64
-// one runs at the same 8 waves (64 VGPRs, six per-item values
-// spilled outside the walks).
+// Batched evaluation of uneven requests in one persistent launch.  The units
+// of work of all requests form one index space (request r owns
+// [item_begin_r, item_begin_{r+1})) handed out by a device counter until it
+// passes the total, so every wave exits once the work is handed out.  An
+// item's output slot is fixed by its index and its sums by its loops' order,
+// so results do not depend on who ran it.
+// Two forms, chosen on the host for a batch (hdr->wide); the other one's
+// launch ends at once:
+//   wide    a unit is a bundle, taken by a workgroup: an item's loops are
+//           dealt to a team of waves (run_bundle).  A burst of 8 requests of
+//           24 x 24 points on 1024 x 1024 loops: 1.64 -> 1.0 ms.
+//   narrow  a unit is an item, taken by a wave: no wave waits for another.
+//           8 requests of up to 128 x 64 points on 4096 x 1024 loops take
+//           30.2 ms, with bundles 31.0.
+// The FP32 kernels are held to 64 VGPRs (8 waves per SIMD instead of 5 at
+// their 86): more waves hide the scalar-load and dispatch latencies of the
+// persistent item loop better than the spills it costs (measured 2.20e12 ->
+// 2.50e12 segment-evals/s on a 128-request batch).
+__device__ __forceinline__ int32_t owner(const ReqDesc* __restrict__ reqs, int32_t n_reqs,
+                                         int64_t item) {
+  int32_t lo = 0, hi = n_reqs - 1;  // last r with item_begin <= item
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (reqs[mid].item_begin <= item) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+#define WL_EACH_VARIANT(X)                      \
+  switch (q.f.kind * 2 + q.spin) {              \
+    case 0: X(kConst, false); break;            \
+    case 1: X(kConst, true); break;             \
+    case 2: X(kSech2, false); break;            \
+    case 3: X(kSech2, true); break;             \
+    case 4: X(kGauss, false); break;            \
+    case 5: X(kGauss, true); break;             \
+    case 6: X(kRational, false); break;         \
+    default: X(kRational, true); break;         \
+  }
+constexpr int wide_waves(int prec) { return prec == 2 ? 6 : 8; }  // per SIMD
+template <int PREC>
+__global__ __launch_bounds__(kSplitWaves * kWave)
+__attribute__((amdgpu_waves_per_eu(wide_waves(PREC)))) void k_batch_wide(
+    const float4* __restrict__ seg, const double4* __restrict__ seg64,
+    const float2* __restrict__ norm, int32_t n_ppl, const BatchHeader* __restrict__ hdr,
+    unsigned int* __restrict__ counter, int32_t n_groups, int64_t loops_per_group) {
+  __shared__ BatchShared sh;
+  const ReqDesc* __restrict__ reqs =
+      (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
+  const int32_t n_reqs = hdr->n_reqs;
+  const int64_t total_items = hdr->total_items;
+  if (!hdr->wide || blockIdx.x >= total_items) return;
+  if constexpr (PREC == 2) load_tables64(sh.tab);
+  int32_t turn = 0;
+  for (int64_t item = blockIdx.x; item < total_items; item = next_item(sh.taken, turn)) {
+    ask_item(counter, sh.taken, turn);
+    const ReqDesc& q = reqs[owner(reqs, n_reqs, item)];
+    const int64_t li = item - q.item_begin;
+#define WL_ITEM(K, SP) \
+  run_bundle<K, SP, PREC>(seg, seg64, norm, n_ppl, q, n_groups, loops_per_group, li, sh)
+    WL_EACH_VARIANT(WL_ITEM)
+#undef WL_ITEM
+  }
+}
 template <int PREC>
 __global__ __launch_bounds__(kWavesPerWG * kWave)
 __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
@@ -1658,37 +1778,29 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
     unsigned int* __restrict__ counter, int64_t loops_per_group) {
   __shared__ float4 stage[kWavesPerWG][PREC == 0 ? kWave : 1];
   __shared__ Tables64 tab;
-  if constexpr (PREC == 2) load_tables64(tab);
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
+  const int32_t n_reqs = hdr->n_reqs;
   const int64_t total_items = hdr->total_items;
-  for (int64_t item = first_item(); item < total_items; item = next_item(counter)) {
-    // request owning the item: last r with item_begin <= item
-    int32_t lo = 0, hi = n_reqs - 1;
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (reqs[mid].item_begin <= item) lo = mid; else hi = mid - 1;
-    }
-    const ReqDesc& q = reqs[lo];
+  if (hdr->wide) return;
+  if constexpr (PREC == 2) load_tables64(tab);
+  for (int64_t item = (int64_t)blockIdx.x * kWavesPerWG + wave; item < total_items;) {
+    const ReqDesc& q = reqs[owner(reqs, n_reqs, item)];
     const int64_t li = item - q.item_begin;
-    switch (q.f.kind * 2 + q.spin) {
 #define WL_ITEM(K, SP) \
-  run_item<K, SP, PREC>(seg, seg64, norm, n_ppl, q, loops_per_group, li, stage[wave], \
-                        tab)
-      case 0: WL_ITEM(kConst, false); break;
-      case 1: WL_ITEM(kConst, true); break;
-      case 2: WL_ITEM(kSech2, false); break;
-      case 3: WL_ITEM(kSech2, true); break;
-      case 4: WL_ITEM(kGauss, false); break;
-      case 5: WL_ITEM(kGauss, true); break;
-      case 6: WL_ITEM(kRational, false); break;
-      default: WL_ITEM(kRational, true); break;
+  run_item<K, SP, PREC>(seg, seg64, norm, n_ppl, q, loops_per_group, li, stage[wave], tab)
+    WL_EACH_VARIANT(WL_ITEM)
 #undef WL_ITEM
-    }
+    // the wave's next item (no branch on the lane, as in ask_item: around one
+    // the compiler may send lanes 1..63 from the end of an item straight to
+    // the broadcast, where they run without lane 0 and read a stale value)
+    const unsigned int t = atomicAdd(counter, threadIdx.x % kWave == 0 ? 1u : 0u);
+    item = (int64_t)gridDim.x * kWavesPerWG +
+           (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)t);
   }
 }
+#undef WL_EACH_VARIANT
 
 // FP64 recomputation of the flagged grid points of a compensated-FP32
 // batch, one kernel per field kind and spin (a kernel holding every
@@ -1706,10 +1818,9 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
     int32_t n_groups, int64_t loops_per_group) {
   __shared__ EscShared sh;
   __shared__ unsigned int taken[2];
-  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
+  const int32_t n_reqs = hdr->n_reqs;
   const int64_t* __restrict__ esc_begin =
       hdr->esc_begin + (int64_t)(KIND * 2 + (SPIN ? 1 : 0)) * (n_reqs + 1);
   // the table is written by an earlier kernel, so its entries come in
@@ -1718,7 +1829,8 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
   if (blockIdx.x >= total) return;
   if constexpr (uses_tables<KIND>()) load_tables64(sh.tab);
   int32_t buf = 0, turn = 0;
-  for (int64_t item = blockIdx.x; item < total;) {
+  for (int64_t item = blockIdx.x; item < total; item = next_item(taken, turn)) {
+    ask_item(counter, taken, turn);
     // request owning the item: last r with esc_begin[r] <= item (a request
     // without items has the same entry as the next one and is passed over)
     int32_t lo = 0, hi = n_reqs - 1;
@@ -1732,17 +1844,6 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
                               item - wave_uniform(esc_begin[lo]), (int64_t)n_groups * q.n_sub,
                               q.n_sub, loops_per_group, q.loops_per_sub, q.list, cnt, q.out_v,
                               q.scale, q.out, sh, buf);
-    // the workgroup's next item, taken by its first wave (as next_item; every
-    // lane stores the same value).  Two slots: a wave may still read the last
-    // one while the first wave, an item ahead, writes the next.
-    if (wave == 0) {
-      const unsigned int t = atomicAdd(counter, threadIdx.x % kWave == 0 ? 1u : 0u);
-      taken[turn] = (unsigned int)__builtin_amdgcn_readfirstlane((int)t);
-    }
-    __syncthreads();
-    item = (int64_t)gridDim.x +
-           (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)taken[turn]);
-    turn ^= 1;
   }
 }
 
@@ -1758,7 +1859,7 @@ __global__ __launch_bounds__(kEscTile) void k_esc_begin(const BatchHeader* __res
   __shared__ int32_t variant[kEscTile];
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
+  const int32_t n_reqs = hdr->n_reqs;
   const int32_t t = threadIdx.x;
   int64_t* table = hdr->esc_begin + (int64_t)t * (n_reqs + 1);  // t < kVariants
   int64_t acc = 0;
@@ -1785,7 +1886,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_batch(
     const BatchHeader* __restrict__ hdr) {
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
+  const int32_t n_reqs = hdr->n_reqs;
   for (int32_t r = blockIdx.x; r < n_reqs; r += gridDim.x) {
     const ReqDesc& q = reqs[r];
     compact_flags(q.flags, q.n_pts, q.list, q.count);
@@ -1802,7 +1903,7 @@ __global__ __launch_bounds__(kFinPts * kFinSlots) void k_finish_batch(
     double* __restrict__ res) {
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
-  const int32_t n_reqs = (int32_t)hdr->n_reqs;
+  const int32_t n_reqs = hdr->n_reqs;
   const ReqDesc& last = reqs[n_reqs - 1];
   const int32_t total = last.tile_begin + (last.n_pts + kFinPts - 1) / kFinPts;
   double* mean = res + hdr->total_sums;
@@ -2372,7 +2473,7 @@ hipError_t launch_disc_finish(const double* d_part, double* d_sums, int32_t n_gr
 hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg64,
                         const float2* d_norm, const float* d_x, const float* d_y,
                         int32_t n_ppl, const void* d_hdr, int32_t n_groups, int64_t n_loops,
-                        unsigned int* d_counter, double* d_res, int32_t n_wg,
+                        unsigned int* d_counter, double* d_res, int32_t n_cu,
                         hipStream_t stream) {
   if (precision == 2 ? d_seg64 == nullptr : d_seg == nullptr) return hipErrorInvalidValue;
   const BatchHeader* hdr = (const BatchHeader*)d_hdr;
@@ -2380,23 +2481,25 @@ hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg
   hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBatchCounters), 0, stream, d_counter);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const dim3 blk(kWavesPerWG * kWave);
+  const dim3 blk(kWavesPerWG * kWave), split_blk(kSplitWaves * kWave);
+  // persistent workgroups: as many as the chip holds at the kernels' waves
+  // per SIMD (those without work exit at once)
+  const dim3 wide_wg(n_cu * 4 * wide_waves(precision) / kSplitWaves);
+  const dim3 item_wg(n_cu * 4 * 8 / kWavesPerWG), esc_wg(n_cu * 4 * kEscWaves / kWavesPerWG);
+#define WL_BATCH(PREC)                                                                     \
+  hipLaunchKernelGGL((k_batch_wide<PREC>), wide_wg, split_blk, 0, stream, d_seg, d_seg64,  \
+                     d_norm, n_ppl, hdr, d_counter, n_groups, lpg);                        \
+  if ((e = hipGetLastError()) != hipSuccess) return e;                                     \
+  hipLaunchKernelGGL((k_batch<PREC>), item_wg, blk, 0, stream, d_seg, d_seg64, d_norm,     \
+                     n_ppl, hdr, d_counter, lpg);                                          \
+  break
   switch (precision) {
-    case 0:
-      hipLaunchKernelGGL((k_batch<0>), dim3(n_wg), blk, 0, stream, d_seg, d_seg64, d_norm,
-                         n_ppl, hdr, d_counter, lpg);
-      break;
-    case 1:
-      hipLaunchKernelGGL((k_batch<1>), dim3(n_wg), blk, 0, stream, d_seg, d_seg64, d_norm,
-                         n_ppl, hdr, d_counter, lpg);
-      break;
-    case 2:
-      hipLaunchKernelGGL((k_batch<2>), dim3(n_wg), blk, 0, stream, d_seg, d_seg64, d_norm,
-                         n_ppl, hdr, d_counter, lpg);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case 0: WL_BATCH(0);
+    case 1: WL_BATCH(1);
+    case 2: WL_BATCH(2);
+    default: return hipErrorInvalidValue;
   }
+#undef WL_BATCH
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const dim3 fin(finish_threads(n_groups));
   hipLaunchKernelGGL((k_finish_batch<false>), dim3(512), fin, 0, stream, hdr, n_groups,
@@ -2408,7 +2511,7 @@ hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg
     hipLaunchKernelGGL(k_esc_begin, dim3(1), dim3(kEscTile), 0, stream, hdr, n_groups);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 #define WL_ESCB(K, SP, V)                                                              \
-  hipLaunchKernelGGL((k_escalate_batch<K, SP>), dim3(n_wg), blk, 0, stream, d_x, d_y, n_ppl, \
+  hipLaunchKernelGGL((k_escalate_batch<K, SP>), esc_wg, blk, 0, stream, d_x, d_y, n_ppl, \
                      hdr, d_counter + 1 + (V), n_groups, lpg);                          \
   if ((e = hipGetLastError()) != hipSuccess) return e;
     WL_ESCB(kConst, false, 0)

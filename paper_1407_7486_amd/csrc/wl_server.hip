@@ -99,8 +99,6 @@ void host_done(void* p) {
   static_cast<Slot*>(p)->done.store(true, std::memory_order_release);
 }
 
-int32_t persistent_wgs(const wl_server* s) { return s->ctx->num_cu * 8; }
-
 // Captures the device work of one batch of precision `prec` on slot `sl`.
 hipError_t capture(wl_server* s, Slot* sl, int prec) {
   const wl_ens* e = s->ens;
@@ -117,7 +115,7 @@ hipError_t capture(wl_server* s, Slot* sl, int prec) {
   if (r == hipSuccess)
     r = wl::launch_batch(prec, e->d_seg, e->d_seg64, e->d_norm, e->d_x, e->d_y, e->n_ppl,
                          sl->d_in, e->n_groups, e->n_loops, sl->d_counter,
-                         (double*)sl->d_res, persistent_wgs(s), sl->stream);
+                         (double*)sl->d_res, s->ctx->num_cu, sl->stream);
   hipGraph_t g = nullptr;
   st = hipStreamEndCapture(sl->stream, &g);
   if (r != hipSuccess) {

@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 RHO = np.linspace(0.0, 4.0, 128)
 T = np.geomspace(1e-2, 20.0, 64)
+T_RAGGED = T[::5]
 J, K = np.array([0, 3, 50, 90, 127]), np.arange(0, 64, 5)  # 5 x 13 = 65 points
 
 
@@ -60,6 +61,34 @@ def test_sums_do_not_depend_on_the_split(wl, per, n_ppl):
                     b = wl.wl_discretisation(ctx, ens, fld, RHO[J], T[K], spin, prec, mode)
                     for u, v in zip(a, b):
                         assert np.array_equal(u[..., J[:, None], K], v, equal_nan=True)
+    finally:
+        wl.wl_ensemble_free(ens)
+        wl.wl_destroy(ctx)
+
+
+@pytest.mark.parametrize("per,prec,big", [(1, 0, False), (3, 0, False), (5, 2, False),
+                                          (11, 1, False), (8, 2, True), (9, 0, True)])
+def test_batch_forms_equal_alone(wl, per, prec, big):
+    """A small batch deals an item's loops to a team of waves (1, 2, 4 or 8,
+    by the loops per row), a large one gives each wave an item: both equal
+    the request evaluated alone, bit for bit."""
+    print("[case] batch forms", per, prec, big, flush=True)
+    sys.stdout.flush()
+    G = 64
+    x, y = wlinputs.polygon_loops(G * per, 24, seed=3)
+    ctx = wl.wl_create(0, None)
+    ens = wl.wl_ensemble_upload(ctx, x, y, G)
+    try:
+        rho = np.linspace(0.0, 4.0, 160) if big else RHO[J]
+        T = np.geomspace(1e-2, 20.0, 160) if big else T_RAGGED
+        reqs = [dict(kind=1, eB0=2.0, lam=1.2, rho=rho, T=T, spin=1, precision=prec),
+                dict(kind=2, eB0=1.0, lam=0.7, rho=RHO[:3], T=T_RAGGED, spin=0,
+                     precision=prec)]
+        for q, b in zip(reqs, wl.wl_average_batch(ctx, ens, reqs, full=True)):
+            a = wl.wl_average_ex(ctx, ens, wl.field(q["kind"], q["eB0"], q["lam"]), q["rho"],
+                                 q["T"], q["spin"], prec)
+            for k in wl.RESULT_KEYS:
+                assert np.array_equal(a[k], b[k], equal_nan=True), k
     finally:
         wl.wl_ensemble_free(ens)
         wl.wl_destroy(ctx)
