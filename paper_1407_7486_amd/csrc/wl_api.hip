@@ -561,15 +561,12 @@ int wl_ensemble_generate(wl_ctx* ctx, uint64_t seed, int64_t first_loop, int64_t
     if (err == hipSuccess) err = hipEventRecord(ev0, ctx->stream);
   }
   if (err == hipSuccess)
-    err = wl::launch_generate(seed, first_loop, n_loops, n_ppl, e->d_x, e->d_y, ctx->stream);
+    err = wl::launch_generate(seed, first_loop, n_loops, n_ppl, e->d_x, e->d_y, e->d_seg,
+                              e->d_norm, ctx->stream);
   if (err == hipSuccess && ctx->timing) {
     err = hipEventRecord(ev1, ctx->stream);
     if (err == hipSuccess) ctx->n_timed++;
   }
-  if (err == hipSuccess) err = hipMemsetAsync(ctx->d_flag, 0, sizeof(int), ctx->stream);
-  if (err == hipSuccess)
-    err = wl::launch_prep(e->d_x, e->d_y, n_loops, n_ppl, e->d_seg, e->d_norm, ctx->d_flag,
-                           ctx->stream);
   if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
   if (err != hipSuccess) return cleanup(hip_fail(ctx, err, "ensemble generation"));
   *out = e;

@@ -25,10 +25,14 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "wl_fma64.h"
 #include "wl_internal.h"
+#include "wl_poly.h"
 
 namespace wl {
 namespace {
+
+constexpr int kGenThreads = 1024;  // most threads of a generating workgroup
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2,
                                               uint32_t c3, uint32_t k0, uint32_t k1,
@@ -53,100 +57,231 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
   out[3] = c3;
 }
 
+// log2(x) for x = w + 1/2, w a 32-bit word: x = m 2^e with m in [3/4, 3/2),
+// m = (1 + r) / c with c from the table of the nearest multiple of 1/128, r =
+// m c - 1 rounded once, and log2(1 + r) = r Q(r), Q of degree 5.  Around m =
+// 1 c is 1 and r exact, so the result keeps its relative accuracy there.
+__device__ __forceinline__ double log2_word(uint32_t w, const double2* tab) {
+  const double x = (double)w + 0.5;
+  // m in [3/4, 3/2): the exponent of x (4/3) decides between [1, 3/2) and [3/4, 1)
+  int e = (__double2hiint(x) >> 20) - 1023;
+  int hi = (__double2hiint(x) & 0x000fffff) | 0x3ff00000;
+  if (hi >= 0x3ff80000) {
+    hi -= 0x00100000;
+    e += 1;
+  }
+  const double m = __hiloint2double(hi, __double2loint(x));
+  const double2 c = tab[(int)rint(fma(128.0, m, -96.0))];
+  const double r = fma(m, c.x, -1.0);
+  return (double)e +
+         fma(r, horner_s_f64<WL_LOG2P1_WIDE_F64_DEG>(WL_LOG2P1_WIDE_F64, r), c.y);
+}
+
+// sqrt(x), x > 0 normal, to about an ulp: the hardware estimate of 1/sqrt and
+// one third-order step.
+__device__ __forceinline__ double root(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = fma(-g, y, 1.0);
+  return fma(g, e * fma(0.375, e, 0.5), g);
+}
+
+// cos(2 pi u) and sin(2 pi u), u in [0, 1): u = f + j/4, |f| <= 1/8 exact.
+__device__ __forceinline__ void sincos2pi(double u, double& s, double& c) {
+  const double j = rint(4.0 * u);
+  const double f = fma(-0.25, j, u);
+  const double v = f * f;
+  const double pc = horner_s_f64<WL_COS2PI_F64_DEG>(WL_COS2PI_F64, v);
+  const double ps = f * horner_s_f64<WL_SIN2PI_F64_DEG>(WL_SIN2PI_F64, v);
+  const int q = (int)j & 3;
+  const double a = (q & 1) ? ps : pc, b = (q & 1) ? pc : ps;
+  c = (q == 1 || q == 2) ? -a : a;
+  s = (q == 2 || q == 3) ? -b : b;
+}
+
+// Sums of x over the workgroup's threads (a fixed tree), to every thread.
+template <int N>
+__device__ __forceinline__ void block_sums(double (&x)[N], double (*part)[kGenThreads / 64]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    for (int off = 32; off > 0; off >>= 1) x[k] += __shfl_xor(x[k], off);
+  __syncthreads();  // part may still be read
+  if (threadIdx.x % 64 == 0)
+#pragma unroll
+    for (int k = 0; k < N; ++k) part[k][threadIdx.x / 64] = x[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    x[k] = 0.0;
+    for (uint32_t w = 0; w < blockDim.x / 64; ++w) x[k] += part[k][w];
+  }
+}
+
+// Place of point i in LDS: one double of padding per 32, so that the levels'
+// strides (powers of two) spread over the banks.
+__host__ __device__ constexpr int32_t place(int32_t i) { return i + (i >> 5); }
+
 // One workgroup per loop (grid-stride over loops), both coordinates in one
-// pass: the loop's N FP64 x and y values sit in LDS (16N bytes).  At each
-// level the threads take the Philox blocks of the level's new points: a
-// block feeds the (one or two) new points of that level whose ordinals it
-// covers, so that each block, logarithm and square root is computed once
-// (only a block straddling two levels is computed once per level).  A
-// barrier separates the levels.
-__global__ __launch_bounds__(256) void k_generate(uint64_t seed, int64_t first_loop,
-                                                  int64_t n_loops, int32_t n_ppl,
-                                                  float* __restrict__ out_x,
-                                                  float* __restrict__ out_y) {
-#pragma clang fp contract(off)
+// pass: the loop's N FP64 x and y values sit in LDS (16.5N bytes).
+//   1  every new point's displacement sigma_k z at its place: no point needs
+//      another one's, so all threads work on the Philox blocks, logarithms
+//      and cosines side by side (a block serves two points).
+//   2  the recursion level by level, one addition of the neighbours' midpoint
+//      per point, a barrier between levels (within one wave while a level has
+//      at most 64 new points).
+//   3  the centre of mass; the FP32 points, their segment quantities and the
+//      loop's norms, straight from LDS.
+// Measured at 16384 x 4096: 1.91 ms as one level of Box-Muller per barrier
+// with the library's log, cos and sin, and kernels of their own for the
+// segments and the norms; 0.74 ms in this form, 1.6 GB written.  What bounds it
+// now is the Philox and FP64 arithmetic of step 1.
+// The FMA contraction of the recursion is off, as in the CPU generator.
+__global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_generate(
+    uint64_t seed, int64_t first_loop, int64_t n_loops, int32_t n_ppl,
+    float* __restrict__ out_x, float* __restrict__ out_y, float4* __restrict__ seg,
+    float2* __restrict__ norm) {
   extern __shared__ double v[];
   double* vx = v;
-  double* vy = v + n_ppl;
-  __shared__ double part[2][256];
+  double* vy = v + place(n_ppl);
+  __shared__ double part[2][kGenThreads / 64];
+  __shared__ double2 tab[97];
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-  const double two_pi = 6.283185307179586476925286766559;
-  const double inv32 = 1.0 / 4294967296.0;
+  const int32_t t = threadIdx.x, nt = blockDim.x;
+  for (int32_t i = t; i < 97; i += nt)
+    tab[i] = make_double2(WL_LOG2_GEN_TAB[2 * i], WL_LOG2_GEN_TAB[2 * i + 1]);
+  __syncthreads();
   for (int64_t l = blockIdx.x; l < n_loops; l += gridDim.x) {
     const uint64_t gl = (uint64_t)(first_loop + l);
-    if (threadIdx.x == 0) {
+    if (t == 0) {
       vx[0] = 0.0;
       vy[0] = 0.0;
     }
+    // points 0 .. n_ppl - 2 over all levels: ordinal p belongs to level nk =
+    // 2^(floor(log2(p + 1)) + 1), where it is new point p + 1 - nk/2
+    for (int32_t bb = t; 2 * bb < n_ppl - 1; bb += nt) {
+      uint32_t w[4];
+      philox4x32_10((uint32_t)bb, (uint32_t)gl, (uint32_t)(gl >> 32), 0u, k0, k1, w);
+#pragma unroll 1
+      for (int pr = 0; pr < 2; ++pr) {
+        const int32_t p = 2 * bb + pr;
+        if (p >= n_ppl - 1) break;
+        const int32_t k = 32 - __clz(p + 1);  // nk = 2^k
+        const int32_t i = place((2 * (p + 1 - (1 << (k - 1))) + 1) * (n_ppl >> k));
+        // r = sqrt(-2 ln u1), u1 = (w + 1/2) 2^-32
+        const double r = root(1.3862943611198906 * (32.0 - log2_word(pr ? w[2] : w[0], tab)));
+        double s, c;
+        sincos2pi(((double)(pr ? w[3] : w[1]) + 0.5) * (1.0 / 4294967296.0), s, c);
+        // 1/sqrt(nk): 2^-k/2, its odd powers from 1/sqrt(2) as rounded
+        const double sigma = __hiloint2double(
+            ((k & 1) ? 0x3fe6a09e : 0x3ff00000) - ((k >> 1) << 20), (k & 1) ? 0x667f3bcc : 0);
+        vx[i] = sigma * (r * c);
+        vy[i] = sigma * (r * s);
+      }
+    }
     __syncthreads();
-    for (int32_t nk = 2; nk <= n_ppl; nk *= 2) {
-      const int32_t h = n_ppl / nk;
-      const double sigma = 1.0 / sqrt((double)nk);
-      // ordinals of this level's new points: o0 .. o1
-      const int64_t o0 = nk / 2 - 1, o1 = nk - 2;
-      for (int64_t bb = (o0 >> 1) + threadIdx.x; bb <= (o1 >> 1); bb += blockDim.x) {
-        uint32_t w[4];
-        philox4x32_10((uint32_t)bb, (uint32_t)gl, (uint32_t)(gl >> 32), 0u, k0, k1, w);
-        for (int pr = 0; pr < 2; ++pr) {
-          const int64_t p = 2 * bb + pr;  // ordinal of the new point
-          if (p < o0 || p > o1) continue;
-          const int32_t qi = (int32_t)(p - o0);
-          const int32_t i = (2 * qi + 1) * h;
-          const int32_t a = i - h;
-          const int32_t b = (i + h == n_ppl) ? 0 : i + h;
-          const double u1 = ((double)w[2 * pr] + 0.5) * inv32;
-          const double u2 = ((double)w[2 * pr + 1] + 0.5) * inv32;
-          const double r = sqrt(-2.0 * log(u1));
-          const double zx = r * cos(two_pi * u2);
-          const double zy = r * sin(two_pi * u2);
+    {
+#pragma clang fp contract(off)
+      for (int32_t half = 1; half < n_ppl; half *= 2) {
+        const int32_t h = n_ppl / (2 * half);
+        for (int32_t q = t; q < half; q += nt) {
+          const int32_t i = place((2 * q + 1) * h);
+          const int32_t a = place(2 * q * h);
+          const int32_t b = q + 1 == half ? 0 : place((2 * q + 2) * h);
           const double mx = 0.5 * (vx[a] + vx[b]);
           const double my = 0.5 * (vy[a] + vy[b]);
-          const double dx = sigma * zx;
-          const double dy = sigma * zy;
-          vx[i] = mx + dx;
-          vy[i] = my + dy;
+          vx[i] = mx + vx[i];
+          vy[i] = my + vy[i];
+        }
+        // levels of at most 64 points are one wave's work
+        if (half >= 64 || 2 * half >= n_ppl) {
+          __syncthreads();
+        } else if (2 * half > 64) {
+          __syncthreads();
+        } else {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
       }
-      __syncthreads();
     }
-    // centre of mass
-    double sx = 0.0, sy = 0.0;
-    for (int32_t i = threadIdx.x; i < n_ppl; i += blockDim.x) {
-      sx += vx[i];
-      sy += vy[i];
+    double sum[2] = {0.0, 0.0};
+    for (int32_t i = t; i < n_ppl; i += nt) {
+      sum[0] += vx[place(i)];
+      sum[1] += vy[place(i)];
     }
-    part[0][threadIdx.x] = sx;
-    part[1][threadIdx.x] = sy;
-    __syncthreads();
-    for (int32_t w = blockDim.x / 2; w > 0; w >>= 1) {
-      if ((int32_t)threadIdx.x < w) {
-        part[0][threadIdx.x] += part[0][threadIdx.x + w];
-        part[1][threadIdx.x] += part[1][threadIdx.x + w];
-      }
-      __syncthreads();
-    }
-    const double mean_x = part[0][0] / n_ppl, mean_y = part[1][0] / n_ppl;
+    block_sums(sum, part);
+    const double mean_x = sum[0] / n_ppl, mean_y = sum[1] / n_ppl;
     float* ox = out_x + l * n_ppl;
     float* oy = out_y + l * n_ppl;
-    for (int32_t i = threadIdx.x; i < n_ppl; i += blockDim.x) {
-      ox[i] = (float)(vx[i] - mean_x);
-      oy[i] = (float)(vy[i] - mean_y);
+    float4* os = seg + l * n_ppl;
+    double nrm[2] = {0.0, 0.0};
+    for (int32_t i = t; i < n_ppl; i += nt) {
+      const int32_t i0 = place(i), j = i + 1 == n_ppl ? 0 : place(i + 1);
+      const float x0 = (float)(vx[i0] - mean_x), y0 = (float)(vy[i0] - mean_y);
+      const float x1 = (float)(vx[j] - mean_x), y1 = (float)(vy[j] - mean_y);
+      const float4 q = seg_quantities(x0, y0, x1, y1);
+      ox[i] = x0;
+      oy[i] = y0;
+      os[i] = q;
+      nrm[0] += (double)q.w * (double)q.w;
+      nrm[1] += (double)q.z * (double)q.z;
     }
-    __syncthreads();  // v and part are reused by the next loop
+    block_sums(nrm, part);  // its barriers also end the reads of v
+    if (t == 0) norm[l] = make_float2((float)sqrt(nrm[0]), (float)sqrt(nrm[1]));
+  }
+}
+
+// Segment array and norms of uploaded loops, one workgroup per loop
+// (grid-stride): each point is read from memory once.  Flags non-finite
+// input.  65536 x 4096: 1.55 ms, 6.4 GB read and written (the segments and the
+// norms in kernels of their own, 2.00).
+__global__ __launch_bounds__(256) void k_prep(const float* __restrict__ X,
+                                              const float* __restrict__ Y, int64_t n_loops,
+                                              int32_t n_ppl, float4* __restrict__ seg,
+                                              float2* __restrict__ norm, int* __restrict__ bad) {
+  __shared__ double part[2][kGenThreads / 64];
+  for (int64_t l = blockIdx.x; l < n_loops; l += gridDim.x) {
+    const float* x = X + l * n_ppl;
+    const float* y = Y + l * n_ppl;
+    double nrm[2] = {0.0, 0.0};
+    for (int32_t i = threadIdx.x; i < n_ppl; i += blockDim.x) {
+      const int32_t j = i + 1 == n_ppl ? 0 : i + 1;
+      const float x0 = x[i], y0 = y[i];
+      if (!isfinite(x0) || !isfinite(y0)) *bad = 1;
+      const float4 q = seg_quantities(x0, y0, x[j], y[j]);
+      seg[l * n_ppl + i] = q;
+      nrm[0] += (double)q.w * (double)q.w;
+      nrm[1] += (double)q.z * (double)q.z;
+    }
+    block_sums(nrm, part);
+    if (threadIdx.x == 0) norm[l] = make_float2((float)sqrt(nrm[0]), (float)sqrt(nrm[1]));
   }
 }
 
 }  // namespace
 
 hipError_t launch_generate(uint64_t seed, int64_t first_loop, int64_t n_loops, int32_t n_ppl,
-                           float* d_x, float* d_y, hipStream_t stream) {
+                           float* d_x, float* d_y, float4* d_seg, float2* d_norm,
+                           hipStream_t stream) {
   const int64_t blocks = n_loops < 65536 ? n_loops : 65536;
-  const size_t lds = 2 * (size_t)n_ppl * sizeof(double);  // at most 128 KiB (N <= 8192)
+  const size_t lds = 2 * (size_t)place(n_ppl) * sizeof(double);  // at most 132 KiB (N <= 8192)
   hipError_t e = hipFuncSetAttribute((const void*)k_generate,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_generate, dim3((uint32_t)blocks), dim3(256), lds, stream, seed,
-                     first_loop, n_loops, n_ppl, d_x, d_y);
+  // four points per thread, one wave at least
+  int32_t threads = (n_ppl / 4 + 63) / 64 * 64;
+  if (threads < 64) threads = 64;
+  if (threads > kGenThreads) threads = kGenThreads;
+  hipLaunchKernelGGL(k_generate, dim3((uint32_t)blocks), dim3(threads), lds, stream, seed,
+                     first_loop, n_loops, n_ppl, d_x, d_y, d_seg, d_norm);
+  return hipGetLastError();
+}
+
+hipError_t launch_prep(const float* d_x, const float* d_y, int64_t n_loops, int32_t n_ppl,
+                       float4* d_seg, float2* d_norm, int* d_bad, hipStream_t stream) {
+  const int64_t blocks = n_loops < 65536 ? n_loops : 65536;
+  hipLaunchKernelGGL(k_prep, dim3((uint32_t)blocks), dim3(n_ppl <= 64 ? 64 : 256), 0, stream,
+                     d_x, d_y, n_loops, n_ppl, d_seg, d_norm, d_bad);
   return hipGetLastError();
 }
 

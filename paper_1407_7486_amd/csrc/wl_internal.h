@@ -105,19 +105,33 @@ constexpr int kFinishPts = 16;  // grid points per tile of the finishing kernels
 // most waves that an item's loops are dealt to (k_average, k_disc)
 constexpr int kSplitWaves = 8;
 
+// Per-segment unit quantities of the segment from
+// (x0, y0) to (x1, y1), formed in FP64 and rounded once to FP32.
+__device__ __forceinline__ float4 seg_quantities(float x0f, float y0f, float x1f, float y1f) {
+  const double x0 = x0f, y0 = y0f, x1 = x1f, y1 = y1f;
+  float4 o;
+  o.x = (float)(0.5 * (x0 + x1));
+  o.y = (float)(0.25 * (y0 + y1) * (y0 + y1));
+  o.z = (float)(y1 - y0);
+  o.w = (float)(x0 * y1 - y0 * x1);
+  return o;
+}
+
 // Launchers (wl_kernels.hip).  All enqueue on `stream` and return the HIP
 // launch status.
 // Segment array d_seg of every loop (flags non-finite input in *d_bad) and
-// the loop norms d_norm [n_loops] (sqrt(sum c^2), sqrt(sum d_y^2)).
+// the loop norms d_norm [n_loops] (sqrt(sum c^2), sqrt(sum d_y^2))
+// (wl_generate.hip).
 hipError_t launch_prep(const float* d_x, const float* d_y, int64_t n_loops,
                        int32_t n_ppl, float4* d_seg, float2* d_norm, int* d_bad,
                        hipStream_t stream);
 
 // d-loop generation (Sec. 2.1) into d_x, d_y [n_loops][n_ppl] (n_ppl a
-// power of two, at most 8192): loops first_loop .. first_loop+n_loops-1 of
-// the Philox stream keyed by `seed`.
+// power of two, at most 8192), with their segment array and norms: loops
+// first_loop .. first_loop+n_loops-1 of the Philox stream keyed by `seed`.
 hipError_t launch_generate(uint64_t seed, int64_t first_loop, int64_t n_loops, int32_t n_ppl,
-                           float* d_x, float* d_y, hipStream_t stream);
+                           float* d_x, float* d_y, float4* d_seg, float2* d_norm,
+                           hipStream_t stream);
 
 // FP64 segment array (m_x, m_y^2, d_y, c per segment, 32 bytes) of every
 // loop, used by the FP64 evaluation of whole loops.

@@ -33,6 +33,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "wl_fma64.h"
 #include "wl_internal.h"
 #include "wl_poly.h"
 
@@ -67,37 +68,6 @@ __device__ __forceinline__ double fma3_f64(double acc, double v, double c) {
   double r;
   asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "v"(v), "v"(c));
   return r;
-}
-
-// acc * v + c as the three-address v_fma_f64 with the coefficient c in a
-// scalar register pair.  Polynomial coefficients as vector operands are
-// loop-invariant values the compiler holds in vector registers across the
-// segment walk (two per coefficient: 53 in the FP64 walk's polynomials, 16
-// more in the per-loop cosine), which under a register budget are spilled to
-// scratch and reloaded for every loop or segment; as scalar operands they
-// sit in scalar registers (constant-memory loads, or two s_mov each) and the
-// FMA reads them directly.  (The two-address v_fmac_f64 would overwrite its
-// addend, so a coefficient addend would first be copied into a vector
-// register at every step.)
-__device__ __forceinline__ double fma3s_f64(double acc, double v, double c) {
-  double r;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "v"(v), "s"(c));
-  return r;
-}
-
-// Horner with every coefficient in scalar registers, for the per-loop
-// epilogue (between segment walks, where any vector register held across
-// the walk is spilled).  The first step is c[DEG] v (rounded) + c[DEG-1]:
-// an FMA of two constants would need two scalar operands, which a VOP3
-// instruction on this chip cannot read.
-template <int DEG>
-__device__ __forceinline__ double horner_s_f64(const double (&c)[DEG + 1], double v) {
-  double t, acc;
-  asm("v_mul_f64 %0, %1, %2" : "=v"(t) : "v"(v), "s"(c[DEG]));
-  asm("v_add_f64 %0, %1, %2" : "=v"(acc) : "v"(t), "s"(c[DEG - 1]));
-#pragma unroll
-  for (int k = DEG - 2; k >= 0; --k) acc = fma3s_f64(acc, v, c[k]);
-  return acc;
 }
 
 // Horner for the FP64 segment walk: the leading coefficient in a vector
@@ -2007,62 +1977,6 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
   }
 }
 
-// Loop norms sqrt(sum_i c_i^2), sqrt(sum_i d_y,i^2) of every loop's segment
-// array (the rounding estimate's geometry factors): one wavefront per loop,
-// lanes striding over its segments, FP64 sums combined across the wave.
-__global__ __launch_bounds__(256) void k_norms(const float4* __restrict__ seg,
-                                               int64_t n_loops, int32_t n_ppl,
-                                               float2* __restrict__ norm) {
-  const int32_t lane = threadIdx.x % kWave;
-  const int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  for (int64_t l = w0; l < n_loops; l += nw) {
-    double cc = 0.0, dd = 0.0;
-    for (int32_t i = lane; i < n_ppl; i += kWave) {
-      const float4 q = seg[l * n_ppl + i];
-      cc += (double)q.w * (double)q.w;
-      dd += (double)q.z * (double)q.z;
-    }
-    for (int32_t off = kWave / 2; off > 0; off >>= 1) {
-      cc += __shfl_xor(cc, off);
-      dd += __shfl_xor(dd, off);
-    }
-    if (lane == 0) norm[l] = make_float2((float)sqrt(cc), (float)sqrt(dd));
-  }
-}
-
-// Per-segment unit quantities (see wl_internal.h) of the segment from
-// (x0, y0) to (x1, y1), formed in FP64 and rounded once to FP32.
-__device__ __forceinline__ float4 seg_quantities(float x0f, float y0f, float x1f, float y1f) {
-  const double x0 = x0f, y0 = y0f, x1 = x1f, y1 = y1f;
-  float4 o;
-  o.x = (float)(0.5 * (x0 + x1));
-  o.y = (float)(0.25 * (y0 + y1) * (y0 + y1));
-  o.z = (float)(y1 - y0);
-  o.w = (float)(x0 * y1 - y0 * x1);
-  return o;
-}
-
-// Segment array of every loop (segment i: point i -> i+1 mod N); flags
-// non-finite input.
-__global__ __launch_bounds__(256) void k_prep(const float* __restrict__ X,
-                                              const float* __restrict__ Y,
-                                              int64_t n_loops, int32_t n_ppl,
-                                              float4* __restrict__ seg,
-                                              int* __restrict__ bad) {
-  const int64_t total = n_loops * n_ppl;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t l = t / n_ppl;
-    const int32_t i = (int32_t)(t % n_ppl);
-    const int32_t j = (i + 1 == n_ppl) ? 0 : i + 1;
-    const float x0f = X[l * n_ppl + i], y0f = Y[l * n_ppl + i];
-    const float x1f = X[l * n_ppl + j], y1f = Y[l * n_ppl + j];
-    if (!isfinite(x0f) || !isfinite(y0f)) *bad = 1;
-    seg[t] = seg_quantities(x0f, y0f, x1f, y1f);
-  }
-}
-
 // FP64 segment array of every loop (segment i: point i -> i+1 mod N).
 __global__ __launch_bounds__(256) void k_prep64(const float* __restrict__ X,
                                                 const float* __restrict__ Y,
@@ -2351,24 +2265,6 @@ hipError_t launch_pl_t(const FieldArgs& f, const float4* seg, const double4* seg
   }
 
 }  // namespace
-
-hipError_t launch_prep(const float* d_x, const float* d_y, int64_t n_loops,
-                       int32_t n_ppl, float4* d_seg, float2* d_norm, int* d_bad,
-                       hipStream_t stream) {
-  const int64_t total = n_loops * n_ppl;
-  int64_t blocks = (total + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_prep, dim3((uint32_t)blocks), dim3(256), 0, stream, d_x,
-                     d_y, n_loops, n_ppl, d_seg, d_bad);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // one wavefront per loop, four per workgroup
-  int64_t nb = (n_loops + 3) / 4;
-  if (nb > 65536) nb = 65536;
-  hipLaunchKernelGGL(k_norms, dim3((uint32_t)nb), dim3(256), 0, stream, d_seg, n_loops,
-                     n_ppl, d_norm);
-  return hipGetLastError();
-}
 
 hipError_t launch_prep64(const float* d_x, const float* d_y, int64_t n_loops,
                          int32_t n_ppl, double4* d_seg64, hipStream_t stream) {
