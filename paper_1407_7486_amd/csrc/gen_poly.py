@@ -24,12 +24,6 @@ and, for the FP64 segment walk's table-driven forms,
   log2(1 + r)/r on [-1/511, 1/511]     middle of 1 + E's interval of width
                                        1/256, r = (1 + E) c_j - 1)
 
-and for the loop generator's logarithm (log2 of m in [3/4, 3/2))
-
-  (c_j, -log2 c_j), j = 0 .. 96,      (c_j the double nearest 1/(1 + k/128),
-  log2(1 + r)/r on [-1/190, 1/190]     k = j - 32 = rint(128 (m - 1)),
-                                       r = m c_j - 1; c = 1 around m = 1)
-
 All are analytic on their intervals.  Coefficients come from Chebyshev
 interpolation of the exact function (mpmath, 60 digits) on the stated
 interval, converted to the monomial basis in v and rounded to the target
@@ -196,8 +190,3 @@ if __name__ == "__main__":
     inv = [mp.mpf(float(1 / (1 + (mp.mpf(j) + 0.5) / 256))) for j in range(128)]
     emit_table("WL_LOG2_TAB", [v for c in inv for v in (c, 1 + mp.log(c, 2))],
                "pairs c_j, 1 + log2 c_j")
-    emit("WL_LOG2P1_WIDE_F64", log2p1_exact, -1 / 190, 1 / 190, 5, np.float64, "double", "",
-         const_mem=False)
-    inv = [mp.mpf(float(1 / (1 + mp.mpf(j - 32) / 128))) for j in range(97)]
-    emit_table("WL_LOG2_GEN_TAB", [v for c in inv for v in (c, -mp.log(c, 2))],
-               "pairs c_j, -log2 c_j")

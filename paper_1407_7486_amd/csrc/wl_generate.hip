@@ -25,14 +25,13 @@
 #include <math.h>
 #include <stdint.h>
 
-#include "wl_fma64.h"
 #include "wl_internal.h"
-#include "wl_poly.h"
 
 namespace wl {
 namespace {
 
 constexpr int kGenThreads = 1024;  // most threads of a generating workgroup
+constexpr int kSumThreads = 256;   // strides of the centre of mass sums
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2,
                                               uint32_t c3, uint32_t k0, uint32_t k1,
@@ -55,48 +54,6 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
   out[1] = c1;
   out[2] = c2;
   out[3] = c3;
-}
-
-// log2(x) for x = w + 1/2, w a 32-bit word: x = m 2^e with m in [3/4, 3/2),
-// m = (1 + r) / c with c from the table of the nearest multiple of 1/128, r =
-// m c - 1 rounded once, and log2(1 + r) = r Q(r), Q of degree 5.  Around m =
-// 1 c is 1 and r exact, so the result keeps its relative accuracy there.
-__device__ __forceinline__ double log2_word(uint32_t w, const double2* tab) {
-  const double x = (double)w + 0.5;
-  // m in [3/4, 3/2): the exponent of x (4/3) decides between [1, 3/2) and [3/4, 1)
-  int e = (__double2hiint(x) >> 20) - 1023;
-  int hi = (__double2hiint(x) & 0x000fffff) | 0x3ff00000;
-  if (hi >= 0x3ff80000) {
-    hi -= 0x00100000;
-    e += 1;
-  }
-  const double m = __hiloint2double(hi, __double2loint(x));
-  const double2 c = tab[(int)rint(fma(128.0, m, -96.0))];
-  const double r = fma(m, c.x, -1.0);
-  return (double)e +
-         fma(r, horner_s_f64<WL_LOG2P1_WIDE_F64_DEG>(WL_LOG2P1_WIDE_F64, r), c.y);
-}
-
-// sqrt(x), x > 0 normal, to about an ulp: the hardware estimate of 1/sqrt and
-// one third-order step.
-__device__ __forceinline__ double root(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double g = x * y;
-  const double e = fma(-g, y, 1.0);
-  return fma(g, e * fma(0.375, e, 0.5), g);
-}
-
-// cos(2 pi u) and sin(2 pi u), u in [0, 1): u = f + j/4, |f| <= 1/8 exact.
-__device__ __forceinline__ void sincos2pi(double u, double& s, double& c) {
-  const double j = rint(4.0 * u);
-  const double f = fma(-0.25, j, u);
-  const double v = f * f;
-  const double pc = horner_s_f64<WL_COS2PI_F64_DEG>(WL_COS2PI_F64, v);
-  const double ps = f * horner_s_f64<WL_SIN2PI_F64_DEG>(WL_SIN2PI_F64, v);
-  const int q = (int)j & 3;
-  const double a = (q & 1) ? ps : pc, b = (q & 1) ? pc : ps;
-  c = (q == 1 || q == 2) ? -a : a;
-  s = (q == 2 || q == 3) ? -b : b;
 }
 
 // Sums of x over the workgroup's threads (a fixed tree), to every thread.
@@ -131,25 +88,28 @@ __host__ __device__ constexpr int32_t place(int32_t i) { return i + (i >> 5); }
 //      at most 64 new points).
 //   3  the centre of mass; the FP32 points, their segment quantities and the
 //      loop's norms, straight from LDS.
-// Measured at 16384 x 4096: 1.91 ms as one level of Box-Muller per barrier
-// with the library's log, cos and sin, and kernels of their own for the
-// segments and the norms; 0.74 ms in this form, 1.6 GB written.  What bounds it
-// now is the Philox and FP64 arithmetic of step 1.
-// The FMA contraction of the recursion is off, as in the CPU generator.
+// Measured at 16384 x 4096: 1.91 ms with the normals of a level computed
+// between its barriers, and kernels of their own for the segments and the
+// norms; 1.00 ms in this form, 1.6 GB written.  What bounds it now is the
+// arithmetic of step 1.  (Its log, cos and sin stay the library's, and the
+// sums' order that of 256 threads: an FP32 coordinate on the edge of a
+// rounding would fall the other way with any other last bit, and a plain FP32
+// evaluation of an ill-conditioned mean shows that.)
+// The FMA contraction is off, as in the CPU generator.
 __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_generate(
     uint64_t seed, int64_t first_loop, int64_t n_loops, int32_t n_ppl,
     float* __restrict__ out_x, float* __restrict__ out_y, float4* __restrict__ seg,
     float2* __restrict__ norm) {
+#pragma clang fp contract(off)
   extern __shared__ double v[];
   double* vx = v;
   double* vy = v + place(n_ppl);
   __shared__ double part[2][kGenThreads / 64];
-  __shared__ double2 tab[97];
+  __shared__ double sum[2][kSumThreads];
+  const double two_pi = 6.283185307179586476925286766559;
+  const double inv32 = 1.0 / 4294967296.0;
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
   const int32_t t = threadIdx.x, nt = blockDim.x;
-  for (int32_t i = t; i < 97; i += nt)
-    tab[i] = make_double2(WL_LOG2_GEN_TAB[2 * i], WL_LOG2_GEN_TAB[2 * i + 1]);
-  __syncthreads();
   for (int64_t l = blockIdx.x; l < n_loops; l += gridDim.x) {
     const uint64_t gl = (uint64_t)(first_loop + l);
     if (t == 0) {
@@ -167,50 +127,59 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(8))
         if (p >= n_ppl - 1) break;
         const int32_t k = 32 - __clz(p + 1);  // nk = 2^k
         const int32_t i = place((2 * (p + 1 - (1 << (k - 1))) + 1) * (n_ppl >> k));
-        // r = sqrt(-2 ln u1), u1 = (w + 1/2) 2^-32
-        const double r = root(1.3862943611198906 * (32.0 - log2_word(pr ? w[2] : w[0], tab)));
-        double s, c;
-        sincos2pi(((double)(pr ? w[3] : w[1]) + 0.5) * (1.0 / 4294967296.0), s, c);
+        const double u1 = ((double)(pr ? w[2] : w[0]) + 0.5) * inv32;
+        const double u2 = ((double)(pr ? w[3] : w[1]) + 0.5) * inv32;
+        const double r = sqrt(-2.0 * log(u1));
         // 1/sqrt(nk): 2^-k/2, its odd powers from 1/sqrt(2) as rounded
         const double sigma = __hiloint2double(
             ((k & 1) ? 0x3fe6a09e : 0x3ff00000) - ((k >> 1) << 20), (k & 1) ? 0x667f3bcc : 0);
-        vx[i] = sigma * (r * c);
-        vy[i] = sigma * (r * s);
+        const double zx = r * cos(two_pi * u2);
+        const double zy = r * sin(two_pi * u2);
+        vx[i] = sigma * zx;
+        vy[i] = sigma * zy;
       }
     }
     __syncthreads();
-    {
-#pragma clang fp contract(off)
-      for (int32_t half = 1; half < n_ppl; half *= 2) {
-        const int32_t h = n_ppl / (2 * half);
-        for (int32_t q = t; q < half; q += nt) {
-          const int32_t i = place((2 * q + 1) * h);
-          const int32_t a = place(2 * q * h);
-          const int32_t b = q + 1 == half ? 0 : place((2 * q + 2) * h);
-          const double mx = 0.5 * (vx[a] + vx[b]);
-          const double my = 0.5 * (vy[a] + vy[b]);
-          vx[i] = mx + vx[i];
-          vy[i] = my + vy[i];
-        }
-        // levels of at most 64 points are one wave's work
-        if (half >= 64 || 2 * half >= n_ppl) {
-          __syncthreads();
-        } else if (2 * half > 64) {
-          __syncthreads();
-        } else {
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+    for (int32_t half = 1; half < n_ppl; half *= 2) {
+      const int32_t h = n_ppl / (2 * half);
+      for (int32_t q = t; q < half; q += nt) {
+        const int32_t i = place((2 * q + 1) * h);
+        const int32_t a = place(2 * q * h);
+        const int32_t b = q + 1 == half ? 0 : place((2 * q + 2) * h);
+        const double mx = 0.5 * (vx[a] + vx[b]);
+        const double my = 0.5 * (vy[a] + vy[b]);
+        vx[i] = mx + vx[i];
+        vy[i] = my + vy[i];
+      }
+      // while this level and the next have at most 64 points, one wave works
+      // on both
+      if (half >= 64 || 2 * half >= n_ppl) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       }
     }
-    double sum[2] = {0.0, 0.0};
-    for (int32_t i = t; i < n_ppl; i += nt) {
-      sum[0] += vx[place(i)];
-      sum[1] += vy[place(i)];
+    // kSumThreads strided sums over the points, added as a tree
+    for (int32_t q = t; q < kSumThreads; q += nt) {
+      double sx = 0.0, sy = 0.0;
+      for (int32_t i = q; i < n_ppl; i += kSumThreads) {
+        sx += vx[place(i)];
+        sy += vy[place(i)];
+      }
+      sum[0][q] = sx;
+      sum[1][q] = sy;
     }
-    block_sums(sum, part);
-    const double mean_x = sum[0] / n_ppl, mean_y = sum[1] / n_ppl;
+    __syncthreads();
+    for (int32_t w = kSumThreads / 2; w > 0; w >>= 1) {
+      for (int32_t q = t; q < w; q += nt) {
+        sum[0][q] += sum[0][q + w];
+        sum[1][q] += sum[1][q + w];
+      }
+      __syncthreads();
+    }
+    const double mean_x = sum[0][0] / n_ppl, mean_y = sum[1][0] / n_ppl;
     float* ox = out_x + l * n_ppl;
     float* oy = out_y + l * n_ppl;
     float4* os = seg + l * n_ppl;
@@ -226,7 +195,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(8))
       nrm[0] += (double)q.w * (double)q.w;
       nrm[1] += (double)q.z * (double)q.z;
     }
-    block_sums(nrm, part);  // its barriers also end the reads of v
+    block_sums(nrm, part);  // its barriers also end the reads of v and sum
     if (t == 0) norm[l] = make_float2((float)sqrt(nrm[0]), (float)sqrt(nrm[1]));
   }
 }
@@ -268,8 +237,7 @@ hipError_t launch_generate(uint64_t seed, int64_t first_loop, int64_t n_loops, i
   hipError_t e = hipFuncSetAttribute((const void*)k_generate,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  // four points per thread, one wave at least
-  int32_t threads = (n_ppl / 4 + 63) / 64 * 64;
+  int32_t threads = n_ppl / 4;  // four points per thread, whole waves
   if (threads < 64) threads = 64;
   if (threads > kGenThreads) threads = kGenThreads;
   hipLaunchKernelGGL(k_generate, dim3((uint32_t)blocks), dim3(threads), lds, stream, seed,
