@@ -161,7 +161,10 @@ int wl_ensemble_download(const wl_ens* ens, float* y_x, float* y_y, int64_t loop
                          int64_t n_loops);
 
 /* Free an ensemble (NULL allowed).  Must be called before wl_destroy of the
- * context that created it. */
+ * context that created it.  The context keeps the device memory of freed
+ * ensembles (points and FP32 segments, at most 8 GiB in all) for the next
+ * ones; it goes back with wl_destroy, and before an allocation of the
+ * library fails. */
 int wl_ensemble_free(wl_ens* ens);
 
 /* Shape of an uploaded ensemble (any output pointer may be NULL). */

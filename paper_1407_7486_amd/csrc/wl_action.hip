@@ -223,11 +223,9 @@ int wl_action(wl_ctx* ctx, const wl_action_spec* sp, const wl_field* field, int3
   const int64_t sums_n = flags == WL_HOST_PTR ? G * nr * nt : 0;
   const int64_t dens_n = (G + 1) * nr, act_n = G + 1;
   const size_t need = (size_t)(sums_n + dens_n + act_n + 2 * nr + 2) * sizeof(double);
-  void* buf = nullptr;
-  if (hipMalloc(&buf, need) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(ctx, WL_ENOMEM, "hipMalloc(%zu bytes) for the action failed", need);
-  }
+  const Work work(ctx, need, "the action");
+  void* buf = work.p;
+  if (!buf) return WL_ENOMEM;
   double* d_sums = flags == WL_HOST_PTR ? (double*)buf : (double*)group_sums;
   double* d_dens = (double*)buf + sums_n;
   double* d_act = d_dens + dens_n;
@@ -235,29 +233,32 @@ int wl_action(wl_ctx* ctx, const wl_action_spec* sp, const wl_field* field, int3
   double* d_derr = d_dmean + nr;
   double* d_am = d_derr + nr;
   hipError_t e = hipSuccess;
-  if (flags == WL_HOST_PTR)
-    e = hipMemcpyAsync(d_sums, group_sums, sums_n * sizeof(double), hipMemcpyHostToDevice,
-                       ctx->stream);
+  if (flags == WL_HOST_PTR) {
+    const Piece in{(void*)group_sums, 0, sums_n * sizeof(double)};
+    e = copy_in(ctx, d_sums, &in, 1);
+  }
   if (e == hipSuccess)
     e = wl::launch_action(*sp, field->kind, field->eB0, field->lambda, spin, d_sums,
                           n_groups, n_loops, d_dens, d_act, d_dmean, d_derr, d_am,
                           ctx->stream);
-  const hipMemcpyKind k =
-      flags == WL_HOST_PTR ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
-  auto put = [&](double* dst, const double* src, int64_t n) {
-    if (e == hipSuccess && dst) e = hipMemcpyAsync(dst, src, n * sizeof(double), k, ctx->stream);
-  };
-  put(out->density, d_dens, G * nr);
-  put(out->density_mean, d_dmean, nr);
-  put(out->density_err, d_derr, nr);
-  put(out->action, d_act, G);
-  put(out->action_mean, d_am, 1);
-  put(out->action_err, d_am + 1, 1);
-  put(out->lcf_density, d_dens + G * nr, nr);
-  put(out->lcf_action, d_act + G, 1);
-  // the scratch buffer is freed once the work has finished
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  (void)hipFree(buf);
+  // results from d_dens on: densities (the LCF row last), actions, statistics
+  const size_t D = sizeof(double);
+  const Piece out_p[] = {{out->density, 0, G * nr * D},
+                         {out->lcf_density, G * nr * D, nr * D},
+                         {out->action, dens_n * D, G * D},
+                         {out->lcf_action, (dens_n + G) * D, D},
+                         {out->density_mean, (dens_n + act_n) * D, nr * D},
+                         {out->density_err, (dens_n + act_n + nr) * D, nr * D},
+                         {out->action_mean, (dens_n + act_n + 2 * nr) * D, D},
+                         {out->action_err, (dens_n + act_n + 2 * nr + 1) * D, D}};
+  if (e == hipSuccess && flags == WL_HOST_PTR) e = copy_out(ctx, d_dens, out_p, 8);
+  if (flags == WL_DEVICE_PTR) {
+    for (const Piece& p : out_p)
+      if (e == hipSuccess && p.host)
+        e = hipMemcpyAsync(p.host, (const char*)d_dens + p.off, p.bytes,
+                           hipMemcpyDeviceToDevice, ctx->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  }
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_action");
   return WL_OK;
 }

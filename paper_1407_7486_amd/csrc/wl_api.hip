@@ -31,6 +31,23 @@ int hip_fail(wl_ctx* ctx, hipError_t e, const char* what) {
   return fail(ctx, WL_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+hipError_t dev_malloc(wl_ctx* ctx, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  {
+    std::lock_guard<std::mutex> lock(ctx->cache_mu);
+    for (const auto& b : ctx->ens_cache) (void)hipFree(b.first);
+    ctx->ens_cache.clear();
+  }
+  e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  }
+  return e;
+}
+
 static int ensure(wl_ctx* ctx, void** p, size_t* have, size_t need, const char* what) {
   if (need <= *have) return WL_OK;
   if (*p) {
@@ -41,14 +58,177 @@ static int ensure(wl_ctx* ctx, void** p, size_t* have, size_t need, const char* 
     *p = nullptr;
     *have = 0;
   }
-  hipError_t e = hipMalloc(p, need);
-  if (e != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
+  if (dev_malloc(ctx, p, need) != hipSuccess)
     return fail(ctx, WL_ENOMEM, "hipMalloc(%zu bytes) for %s failed", need, what);
-  }
   *have = need;
   return WL_OK;
+}
+
+Work::Work(wl_ctx* ctx, size_t bytes, const char* what) {
+  if (bytes <= kWorkKeep) {
+    if (ensure(ctx, &ctx->d_work, &ctx->work_bytes, bytes, what) == WL_OK) p = ctx->d_work;
+    return;
+  }
+  temporary = true;
+  if (dev_malloc(ctx, &p, bytes) != hipSuccess) {
+    p = nullptr;
+    fail(ctx, WL_ENOMEM, "hipMalloc(%zu bytes) for %s failed", bytes, what);
+  }
+}
+
+Work::~Work() {
+  if (temporary && p) (void)hipFree(p);
+}
+
+// The staging buffer, free of copies in flight.
+static hipError_t pin_ready(wl_ctx* ctx) {
+  if (!ctx->h_pin) {
+    hipError_t e = hipHostMalloc((void**)&ctx->h_pin, 2 * kPinHalf, hipHostMallocDefault);
+    for (int k = 0; k < 2 && e == hipSuccess; ++k)
+      e = hipEventCreateWithFlags(&ctx->pin_ev[k], hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+  }
+  if (ctx->pin_busy) {
+    const hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess) return e;
+    ctx->pin_busy = false;
+  }
+  return hipSuccess;
+}
+
+hipError_t copy_in(wl_ctx* ctx, void* d_base, const Piece* pieces, int n) {
+  hipError_t e = pin_ready(ctx);
+  if (e != hipSuccess) return e;
+  // halves are filled in turn; pieces that lie side by side on the device and
+  // fit a half together travel in one copy
+  int half = 0;
+  bool used[2] = {false, false};
+  size_t fill = 0, start = 0;  // staged bytes of the half, their device offset
+  auto flush = [&]() {
+    if (fill == 0) return hipSuccess;
+    hipError_t r = hipMemcpyAsync((char*)d_base + start, ctx->h_pin + half * kPinHalf, fill,
+                                  hipMemcpyHostToDevice, ctx->stream);
+    ctx->pin_busy = true;
+    if (r == hipSuccess) r = hipEventRecord(ctx->pin_ev[half], ctx->stream);
+    used[half] = true;
+    half ^= 1;
+    if (r == hipSuccess && used[half]) r = hipEventSynchronize(ctx->pin_ev[half]);
+    fill = 0;
+    return r;
+  };
+  for (int i = 0; i < n && e == hipSuccess; ++i) {
+    size_t done = 0;
+    while (done < pieces[i].bytes && e == hipSuccess) {
+      const size_t off = pieces[i].off + done;
+      if (fill > 0 && (off != start + fill || fill == kPinHalf)) e = flush();
+      if (e != hipSuccess) break;
+      if (fill == 0) start = off;
+      const size_t left = pieces[i].bytes - done, room = kPinHalf - fill;
+      const size_t take = left < room ? left : room;
+      memcpy(ctx->h_pin + half * kPinHalf + fill, (const char*)pieces[i].host + done, take);
+      fill += take;
+      done += take;
+    }
+  }
+  if (e == hipSuccess) e = flush();
+  return e;
+}
+
+hipError_t copy_out(wl_ctx* ctx, const void* d_base, const Piece* pieces, int n) {
+  size_t lo = SIZE_MAX, hi = 0;
+  for (int i = 0; i < n; ++i)
+    if (pieces[i].host && pieces[i].bytes) {
+      if (pieces[i].off < lo) lo = pieces[i].off;
+      if (pieces[i].off + pieces[i].bytes > hi) hi = pieces[i].off + pieces[i].bytes;
+    }
+  if (hi == 0) return hipStreamSynchronize(ctx->stream);
+  // (copy_in's copies are ahead on the same stream: their half may be reused)
+  hipError_t e = ctx->h_pin ? hipSuccess : pin_ready(ctx);
+  if (e != hipSuccess) return e;
+  ctx->pin_busy = true;
+  auto ask = [&](size_t c) {  // chunk c of [lo, hi) into its half
+    const size_t a = lo + c * kPinHalf, b = a + kPinHalf < hi ? a + kPinHalf : hi;
+    hipError_t r = hipMemcpyAsync(ctx->h_pin + (c & 1) * kPinHalf, (const char*)d_base + a,
+                                  b - a, hipMemcpyDeviceToHost, ctx->stream);
+    if (r == hipSuccess) r = hipEventRecord(ctx->pin_ev[c & 1], ctx->stream);
+    return r;
+  };
+  const size_t chunks = (hi - lo + kPinHalf - 1) / kPinHalf;
+  e = ask(0);
+  int first = 0;  // pieces before it are complete
+  for (size_t c = 0; c < chunks && e == hipSuccess; ++c) {
+    if (c + 1 < chunks) e = ask(c + 1);
+    if (e == hipSuccess) e = hipEventSynchronize(ctx->pin_ev[c & 1]);
+    if (e != hipSuccess) break;
+    const size_t a = lo + c * kPinHalf, b = a + kPinHalf < hi ? a + kPinHalf : hi;
+    for (int i = first; i < n; ++i) {
+      const Piece& q = pieces[i];
+      if (q.off >= b) break;
+      if (q.off + q.bytes <= b && i == first) ++first;
+      if (!q.host || q.off + q.bytes <= a) continue;
+      const size_t from = q.off > a ? q.off : a;
+      const size_t to = q.off + q.bytes < b ? q.off + q.bytes : b;
+      memcpy((char*)q.host + (from - q.off), ctx->h_pin + (c & 1) * kPinHalf + (from - a),
+             to - from);
+    }
+  }
+  if (e == hipSuccess) ctx->pin_busy = false;
+  return e;
+}
+
+// Device block of an ensemble: a kept one that fits without wasting more than
+// a quarter of it, or a new allocation.  (hipMalloc and hipFree of a GB take
+// 1 ms here and, after some hundred GB of them, 20 to 40: 16384 x 4096 points
+// generated, evaluated and freed again and again took 8 to 45 ms, 3.4 with the
+// block kept.)
+constexpr size_t kEnsCacheBytes = (size_t)8 << 30;
+static void* ens_block(wl_ctx* ctx, size_t bytes, size_t* got) {
+  {
+    std::lock_guard<std::mutex> lock(ctx->cache_mu);
+    for (size_t i = 0; i < ctx->ens_cache.size(); ++i) {
+      const auto b = ctx->ens_cache[i];
+      if (b.second >= bytes && b.second - bytes <= b.second / 4) {
+        ctx->ens_cache.erase(ctx->ens_cache.begin() + i);
+        *got = b.second;
+        return b.first;
+      }
+    }
+  }
+  void* p = nullptr;
+  *got = bytes;
+  return dev_malloc(ctx, &p, bytes) == hipSuccess ? p : nullptr;
+}
+// Takes back a block that no enqueued work uses: the oldest kept ones go when
+// it takes them over the bound.
+static void ens_block_free(wl_ctx* ctx, void* p, size_t bytes) {
+  if (!p) return;
+  if (bytes > kEnsCacheBytes) {
+    (void)hipFree(p);
+    return;
+  }
+  std::lock_guard<std::mutex> lock(ctx->cache_mu);
+  size_t held = bytes;
+  for (const auto& b : ctx->ens_cache) held += b.second;
+  while (held > kEnsCacheBytes) {
+    held -= ctx->ens_cache.front().second;
+    (void)hipFree(ctx->ens_cache.front().first);
+    ctx->ens_cache.erase(ctx->ens_cache.begin());
+  }
+  ctx->ens_cache.emplace_back(p, bytes);
+}
+// The arrays of an ensemble of the given shape, in one block.
+static bool ens_alloc(wl_ctx* ctx, wl_ens* e) {
+  const size_t npts = (size_t)(e->n_loops * e->n_ppl);
+  auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  const size_t x = up(npts * sizeof(float)), s = up(npts * sizeof(float4));
+  e->block = ens_block(ctx, 2 * x + s + (size_t)e->n_loops * sizeof(float2), &e->block_bytes);
+  if (!e->block) return false;
+  char* p = (char*)e->block;
+  e->d_seg = (float4*)p;
+  e->d_x = (float*)(p + s);
+  e->d_y = (float*)(p + s + x);
+  e->d_norm = (float2*)(p + s + 2 * x);
+  return true;
 }
 
 int check_field(wl_ctx* ctx, const wl_field* f, wl::FieldArgs* a) {
@@ -333,11 +513,8 @@ hipError_t ensure_seg64(const wl_ens* ens, hipStream_t stream) {
   if (ens->d_seg64) return hipSuccess;
   const int64_t nseg = ens->n_loops * ens->n_ppl;
   double4* d = nullptr;
-  hipError_t e = hipMalloc((void**)&d, nseg * sizeof(double4));
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return hipErrorOutOfMemory;
-  }
+  hipError_t e = dev_malloc(ens->ctx, (void**)&d, nseg * sizeof(double4));
+  if (e != hipSuccess) return hipErrorOutOfMemory;
   e = launch_prep64(ens->d_x, ens->d_y, ens->n_loops, ens->n_ppl, d, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
@@ -447,6 +624,11 @@ int wl_destroy(wl_ctx* ctx) {
     if (ctx->d_flag) (void)hipFree(ctx->d_flag);
     if (ctx->d_counter) (void)hipFree(ctx->d_counter);
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
+    if (ctx->d_work) (void)hipFree(ctx->d_work);
+    for (const auto& b : ctx->ens_cache) (void)hipFree(b.first);
+    if (ctx->h_pin) (void)hipHostFree(ctx->h_pin);
+    for (hipEvent_t ev : ctx->pin_ev)
+      if (ev) (void)hipEventDestroy(ev);
     for (auto& pr : ctx->events) {
       (void)hipEventDestroy(pr.first);
       (void)hipEventDestroy(pr.second);
@@ -482,21 +664,16 @@ int wl_ensemble_upload(wl_ctx* ctx, const float* y_x, const float* y_y,
   e->n_ppl = n_ppl;
   e->n_groups = n_groups;
   auto cleanup = [&](int code) {
-    if (e->d_x) (void)hipFree(e->d_x);
-    if (e->d_y) (void)hipFree(e->d_y);
-    if (e->d_seg) (void)hipFree(e->d_seg);
-    if (e->d_norm) (void)hipFree(e->d_norm);
+    if (e->block) {
+      (void)hipStreamSynchronize(ctx->stream);
+      (void)hipFree(e->block);
+    }
     delete e;
     return code;
   };
-  if (hipMalloc((void**)&e->d_x, npts * sizeof(float)) != hipSuccess ||
-      hipMalloc((void**)&e->d_y, npts * sizeof(float)) != hipSuccess ||
-      hipMalloc((void**)&e->d_seg, npts * sizeof(float4)) != hipSuccess ||
-      hipMalloc((void**)&e->d_norm, n_loops * sizeof(float2)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (!ens_alloc(ctx, e))
     return cleanup(fail(ctx, WL_ENOMEM, "device allocation of %lld points failed",
                         (long long)npts));
-  }
   const hipMemcpyKind kind =
       flags == WL_DEVICE_PTR ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
   hipError_t err = hipMemcpyAsync(e->d_x, y_x, npts * sizeof(float), kind, ctx->stream);
@@ -539,21 +716,16 @@ int wl_ensemble_generate(wl_ctx* ctx, uint64_t seed, int64_t first_loop, int64_t
   e->n_ppl = n_ppl;
   e->n_groups = n_groups;
   auto cleanup = [&](int code) {
-    if (e->d_x) (void)hipFree(e->d_x);
-    if (e->d_y) (void)hipFree(e->d_y);
-    if (e->d_seg) (void)hipFree(e->d_seg);
-    if (e->d_norm) (void)hipFree(e->d_norm);
+    if (e->block) {
+      (void)hipStreamSynchronize(ctx->stream);
+      (void)hipFree(e->block);
+    }
     delete e;
     return code;
   };
-  if (hipMalloc((void**)&e->d_x, npts * sizeof(float)) != hipSuccess ||
-      hipMalloc((void**)&e->d_y, npts * sizeof(float)) != hipSuccess ||
-      hipMalloc((void**)&e->d_seg, npts * sizeof(float4)) != hipSuccess ||
-      hipMalloc((void**)&e->d_norm, n_loops * sizeof(float2)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (!ens_alloc(ctx, e))
     return cleanup(fail(ctx, WL_ENOMEM, "device allocation of %lld points failed",
                         (long long)npts));
-  }
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipError_t err = hipSuccess;
   if (ctx->timing) {
@@ -602,10 +774,7 @@ int wl_ensemble_free(wl_ens* ens) {
   DeviceGuard g(ens->ctx->device);
   if (ens->ctx->stream) (void)hipStreamSynchronize(ens->ctx->stream);
   else (void)hipDeviceSynchronize();
-  (void)hipFree(ens->d_x);
-  (void)hipFree(ens->d_y);
-  (void)hipFree(ens->d_seg);
-  (void)hipFree(ens->d_norm);
+  ens_block_free(ens->ctx, ens->block, ens->block_bytes);
   if (ens->d_sub) (void)hipFree(ens->d_sub);
   if (ens->d_seg64) (void)hipFree(ens->d_seg64);
   if (ens->d_sub64) (void)hipFree(ens->d_sub64);
@@ -761,6 +930,14 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
   return WL_OK;
 }
 
+// Host grids to d_rho [n_rho], then [n_T] right behind it.
+static hipError_t grids_in(wl_ctx* ctx, double* d_rho, const double* rho, int32_t n_rho,
+                           const double* T, int32_t n_T) {
+  const size_t rb = n_rho * sizeof(double);
+  const Piece p[] = {{(void*)rho, 0, rb}, {(void*)T, rb, n_T * sizeof(double)}};
+  return copy_in(ctx, d_rho, p, 2);
+}
+
 static int average_impl(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
                         const double* rho, int32_t n_rho, const double* T, int32_t n_T,
                         int32_t spin, int32_t precision, int32_t flags, const wl_result* out,
@@ -809,27 +986,19 @@ static int average_impl(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
   o.scale = o.err + n_pts;
   o.fp_err = o.scale + n_pts;
   o.escalated = (uint8_t*)(o.fp_err + n_pts);
-  hipError_t e = hipMemcpyAsync(d_rho, rho, n_rho * sizeof(double), hipMemcpyHostToDevice,
-                                ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_T, T, n_T * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
+  hipError_t e = grids_in(ctx, d_rho, rho, n_rho, T, n_T);
   if (e != hipSuccess) return hip_fail(ctx, e, "grid upload");
   if ((rc = average_device(ctx, ens, fa, d_rho, n_rho, d_T, n_T, spin, precision, o)))
     return rc;
-  const struct {
-    void* host;
-    const void* dev;
-    size_t bytes;
-  } copies[] = {{out->group_sums, o.sums, sums_n * sizeof(double)},
-                {out->mean, o.mean, n_pts * sizeof(double)},
-                {out->err, o.err, n_pts * sizeof(double)},
-                {out->scale, o.scale, n_pts * sizeof(double)},
-                {out->fp_err, o.fp_err, n_pts * sizeof(double)},
-                {out->escalated, o.escalated, (size_t)n_pts}};
-  for (const auto& c : copies)
-    if (e == hipSuccess && c.host)
-      e = hipMemcpyAsync(c.host, c.dev, c.bytes, hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  auto off = [&](const void* p) { return (size_t)((const char*)p - (const char*)ctx->d_out); };
+  const size_t pt = n_pts * sizeof(double);
+  const Piece pieces[] = {{out->group_sums, off(o.sums), sums_n * sizeof(double)},
+                          {out->mean, off(o.mean), pt},
+                          {out->err, off(o.err), pt},
+                          {out->scale, off(o.scale), pt},
+                          {out->fp_err, off(o.fp_err), pt},
+                          {out->escalated, off(o.escalated), (size_t)n_pts}};
+  e = copy_out(ctx, ctx->d_out, pieces, 6);
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_average");
   return WL_OK;
 }
@@ -917,20 +1086,31 @@ int wl_average_batch(wl_ctx* ctx, const wl_ens* ens, const wl_request* reqs,
     if (!build_batch(ens, rq.data(), rf.data(), pl.data(), (int32_t)rq.size(), h_in.data(),
                      in_b, d_in, d_res, res_b, &lay))
       return fail(ctx, WL_EINVAL, "internal: batch layout exceeds its buffer");
-    hipError_t e = hipMemcpyAsync(d_in, h_in.data(), lay.in_bytes, hipMemcpyHostToDevice,
-                                  ctx->stream);
+    const Piece in{h_in.data(), 0, lay.in_bytes};
+    hipError_t e = copy_in(ctx, d_in, &in, 1);
     if (e == hipSuccess)
       e = wl::launch_batch(prec, ens->d_seg, ens->d_seg64, ens->d_norm, ens->d_x, ens->d_y,
                            ens->n_ppl, d_in, ens->n_groups, ens->n_loops, ctx->d_counter,
                            d_res, ctx->num_cu, ctx->stream);
-    std::vector<double> h_res(lay.head_bytes / sizeof(double));
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h_res.data(), d_res, h_res.size() * sizeof(double),
-                         hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    // every request's arrays, in the order of the result region's head
+    std::vector<Piece> pieces;
+    pieces.reserve(6 * rq.size());
+    const size_t n_rq = rq.size(), G = ens->n_groups;
+    for (size_t i = 0; i < n_rq; ++i)
+      pieces.push_back({rq[i]->group_sums, 8 * (size_t)lay.sums_begin[i],
+                        8 * G * (size_t)pl[i].n_pts});
+    for (size_t k = 0; k < 5; ++k)
+      for (size_t i = 0; i < n_rq; ++i) {
+        double* const dst[] = {rq[i]->mean, rq[i]->err, rq[i]->scale, rq[i]->fp_err};
+        const size_t at = 8 * (size_t)(lay.sums_n + (int64_t)k * lay.pts_n);
+        if (k < 4)
+          pieces.push_back({dst[k], at + 8 * (size_t)lay.pts_begin[i], 8 * (size_t)pl[i].n_pts});
+        else
+          pieces.push_back({rq[i]->escalated, at + (size_t)lay.pts_begin[i],
+                            (size_t)pl[i].n_pts});
+      }
+    if (e == hipSuccess) e = copy_out(ctx, d_res, pieces.data(), (int)pieces.size());
     if (e != hipSuccess) return hip_fail(ctx, e, "wl_average_batch");
-    for (size_t i = 0; i < rq.size(); ++i)
-      scatter_results(*rq[i], lay, (int32_t)i, h_res.data(), ens->n_groups);
   }
   return WL_OK;
 }
@@ -941,8 +1121,7 @@ static int ensure_sub(wl_ctx* ctx, const wl_ens* ens) {
   if (ens->d_sub) return WL_OK;
   const int64_t npts = ens->n_loops * ens->n_ppl;
   float4* d = nullptr;
-  if (hipMalloc((void**)&d, npts * sizeof(float4)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (dev_malloc(ctx, (void**)&d, npts * sizeof(float4)) != hipSuccess) {
     return fail(ctx, WL_ENOMEM, "device allocation of the sub-loop segments (%lld bytes) failed",
                 (long long)(npts * (int64_t)sizeof(float4)));
   }
@@ -962,8 +1141,7 @@ static int ensure_sub64(wl_ctx* ctx, const wl_ens* ens) {
   if (ens->d_sub64) return WL_OK;
   const int64_t npts = ens->n_loops * ens->n_ppl;
   double4* d = nullptr;
-  if (hipMalloc((void**)&d, npts * sizeof(double4)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (dev_malloc(ctx, (void**)&d, npts * sizeof(double4)) != hipSuccess) {
     return fail(ctx, WL_ENOMEM,
                 "device allocation of the FP64 sub-loop segments (%lld bytes) failed",
                 (long long)(npts * (int64_t)sizeof(double4)));
@@ -1068,22 +1246,14 @@ static int per_loop_impl(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& fa
   double* d_ph = (double*)ctx->d_out;
   double* d_sp = d_ph + each;
   double* d_w = d_sp + each;
-  hipError_t e = hipMemcpyAsync(d_rho, rho, n_rho * sizeof(double), hipMemcpyHostToDevice,
-                                ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_T, T, n_T * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
+  hipError_t e = grids_in(ctx, d_rho, rho, n_rho, T, n_T);
   if (e == hipSuccess)
     e = wl::launch_per_loop(precision, spin, fa, seg, seg64, ens->d_x, ens->d_y, ens->n_ppl, sl,
                             d_rho, d_T, n_T, (int32_t)n_pts, loop0, n_loops, d_ph, d_sp, d_w,
                             ctx->stream);
-  if (e == hipSuccess && phase)
-    e = hipMemcpyAsync(phase, d_ph, each * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess && spin_exp)
-    e = hipMemcpyAsync(spin_exp, d_sp, each * sizeof(double), hipMemcpyDeviceToHost,
-                       ctx->stream);
-  if (e == hipSuccess && w)
-    e = hipMemcpyAsync(w, d_w, each * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  const size_t eb = each * sizeof(double);
+  const Piece pieces[] = {{phase, 0, eb}, {spin_exp, eb, eb}, {w, 2 * eb, eb}};
+  if (e == hipSuccess) e = copy_out(ctx, d_ph, pieces, 3);
   if (e != hipSuccess) return hip_fail(ctx, e, "per-loop evaluation");
   return WL_OK;
 }
@@ -1130,10 +1300,7 @@ int wl_discretisation(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
   double* d_err = d_mean + 4 * n_pts;
   double* d_delta = d_err + 4 * n_pts;
   if (!level_out) level_out = d_sums;
-  hipError_t e = hipMemcpyAsync(d_rho, rho, n_rho * sizeof(double), hipMemcpyHostToDevice,
-                                ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_T, T, n_T * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
+  hipError_t e = grids_in(ctx, d_rho, rho, n_rho, T, n_T);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (e == hipSuccess && ctx->timing) {
     e = next_events(ctx, &ev0, &ev1);
@@ -1150,19 +1317,12 @@ int wl_discretisation(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
   if (e == hipSuccess)
     e = wl::launch_disc_finish(level_out, d_sums, (int32_t)G, s.n_sub, (int32_t)n_pts,
                                ens->n_loops, d_mean, d_err, d_delta, ctx->stream);
-  if (e == hipSuccess && group_sums)
-    e = hipMemcpyAsync(group_sums, d_sums, sums_n * sizeof(double), hipMemcpyDeviceToHost,
-                       ctx->stream);
-  if (e == hipSuccess && mean)
-    e = hipMemcpyAsync(mean, d_mean, 4 * n_pts * sizeof(double), hipMemcpyDeviceToHost,
-                       ctx->stream);
-  if (e == hipSuccess && err)
-    e = hipMemcpyAsync(err, d_err, 4 * n_pts * sizeof(double), hipMemcpyDeviceToHost,
-                       ctx->stream);
-  if (e == hipSuccess && delta)
-    e = hipMemcpyAsync(delta, d_delta, n_pts * sizeof(double), hipMemcpyDeviceToHost,
-                       ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  const size_t sb = sums_n * sizeof(double), pb = n_pts * sizeof(double);
+  const Piece pieces[] = {{group_sums, 0, sb},
+                          {mean, sb, 4 * pb},
+                          {err, sb + 4 * pb, 4 * pb},
+                          {delta, sb + 8 * pb, pb}};
+  if (e == hipSuccess) e = copy_out(ctx, d_sums, pieces, 4);
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_discretisation");
   return WL_OK;
 }

@@ -266,20 +266,19 @@ int wl_correlation(wl_ctx* ctx, const double* values, int64_t n_units, int32_t n
   const int64_t out_n = flags == WL_HOST_PTR ? sz : 0;
   const size_t need =
       (size_t)(vals_n + out_n + n_split * sz + (int64_t)mean_rows * n_pts + n_pts) * sizeof(double);
-  void* buf = nullptr;
-  if (hipMalloc(&buf, need) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(ctx, WL_ENOMEM, "hipMalloc(%zu bytes) for the correlation failed", need);
-  }
+  const Work work(ctx, need, "the correlation");
+  void* buf = work.p;
+  if (!buf) return WL_ENOMEM;
   double* d_x = flags == WL_HOST_PTR ? (double*)buf : (double*)values;
   double* d_out = flags == WL_HOST_PTR ? (double*)buf + vals_n : corr;
   double* d_part = (double*)buf + vals_n + out_n;
   double* d_mp = d_part + n_split * sz;
   double* d_mu = d_mp + (int64_t)mean_rows * n_pts;
   hipError_t e = hipSuccess;
-  if (flags == WL_HOST_PTR)
-    e = hipMemcpyAsync(d_x, values, vals_n * sizeof(double), hipMemcpyHostToDevice,
-                       ctx->stream);
+  if (flags == WL_HOST_PTR) {
+    const Piece in{(void*)values, 0, vals_n * sizeof(double)};
+    e = copy_in(ctx, d_x, &in, 1);
+  }
   const dim3 cb((n_pts + 255) / 256, mean_rows);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_col_partial, cb, dim3(256), 0, ctx->stream, d_x, n_units, n_pts,
@@ -310,10 +309,8 @@ int wl_correlation(wl_ctx* ctx, const double* values, int64_t n_units, int32_t n
                        d_part, (int32_t)n_split, n_pts, d_out);
     e = hipGetLastError();
   }
-  if (e == hipSuccess && flags == WL_HOST_PTR)
-    e = hipMemcpyAsync(corr, d_out, sz * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  (void)hipFree(buf);
+  const Piece out{flags == WL_HOST_PTR ? corr : nullptr, 0, sz * sizeof(double)};
+  if (e == hipSuccess) e = copy_out(ctx, d_out, &out, 1);
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_correlation");
   return WL_OK;
 }
@@ -355,40 +352,37 @@ int wl_regroup(wl_ctx* ctx, const double* per_unit, int64_t n_units, int32_t n_p
   const int64_t xn = host ? n_units * n_pts : 0, pn = host ? (int64_t)n_perms * n_units : 0;
   const int64_t qn = host && point_perm ? n_pts : 0, sn = host ? (int64_t)n_groups * n_pts : 0;
   const size_t need = (size_t)(xn + sn) * sizeof(double) + (size_t)pn * sizeof(int64_t) +
-                      (size_t)qn * sizeof(int32_t) + 16;
-  void* buf = nullptr;
-  if (hipMalloc(&buf, need) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(ctx, WL_ENOMEM, "hipMalloc(%zu bytes) for the regrouping failed", need);
-  }
+                      (size_t)qn * sizeof(int32_t) + 24;
+  const Work work(ctx, need, "the regrouping");
+  void* buf = work.p;
+  if (!buf) return WL_ENOMEM;
+  // [values | permutations | point permutations | sums | index flag]
   double* d_x = host ? (double*)buf : (double*)per_unit;
-  double* d_s = host ? (double*)buf + xn : sums;
-  int64_t* d_p = host ? (int64_t*)((double*)buf + xn + sn) : (int64_t*)perms;
+  int64_t* d_p = host ? (int64_t*)((double*)buf + xn) : (int64_t*)perms;
   int32_t* d_q = host ? (point_perm ? (int32_t*)(d_p + pn) : nullptr) : (int32_t*)point_perm;
+  const size_t in_bytes = (size_t)(xn + pn) * 8 + (((size_t)qn * 4 + 7) & ~(size_t)7);
+  double* d_out = (double*)((char*)buf + in_bytes);
+  double* d_s = host ? d_out : sums;
+  int* d_bad = (int*)(d_out + sn);
   hipError_t e = hipSuccess;
   if (host) {
-    e = hipMemcpyAsync(d_x, per_unit, xn * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(d_p, perms, pn * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess && d_q)
-      e = hipMemcpyAsync(d_q, point_perm, qn * sizeof(int32_t), hipMemcpyHostToDevice,
-                         ctx->stream);
+    const Piece in[] = {{(void*)per_unit, 0, xn * sizeof(double)},
+                        {(void*)perms, xn * sizeof(double), pn * sizeof(int64_t)},
+                        {(void*)point_perm, (xn + pn) * sizeof(double), qn * sizeof(int32_t)}};
+    e = copy_in(ctx, buf, in, point_perm ? 3 : 2);
   }
-  if (e == hipSuccess) e = hipMemsetAsync(ctx->d_flag, 0, sizeof(int), ctx->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(d_bad, 0, sizeof(int), ctx->stream);
   const int64_t total = (int64_t)n_groups * n_pts;
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_regroup, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0,
                        ctx->stream, d_x, n_units, n_pts, d_p, n_perms, d_q, n_groups, d_s,
-                       ctx->d_flag);
+                       d_bad);
     e = hipGetLastError();
   }
   int bad = 0;
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(&bad, ctx->d_flag, sizeof(int), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess && host)
-    e = hipMemcpyAsync(sums, d_s, sn * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  (void)hipFree(buf);
+  const Piece out[] = {{host ? sums : nullptr, 0, sn * sizeof(double)},
+                       {&bad, sn * sizeof(double), sizeof(int)}};
+  if (e == hipSuccess) e = copy_out(ctx, d_out, out, 2);
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_regroup");
   if (bad) return fail(ctx, WL_EINVAL, "perms or point_perm hold an index out of range");
   return WL_OK;

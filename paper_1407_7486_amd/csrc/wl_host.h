@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -28,6 +29,18 @@ struct wl_ctx {
   void* d_batch = nullptr;  // batched evaluation: descriptors, grids, results
   size_t batch_bytes = 0;
   unsigned int* d_counter = nullptr;  // work counters of persistent launches
+  void* d_work = nullptr;  // scratch of the correlation, regroup and action calls
+  size_t work_bytes = 0;
+  // pinned staging of host arrays (two halves of kPinHalf; see copy_in,
+  // copy_out); `pin_busy` while copies from or to it may be in flight
+  char* h_pin = nullptr;
+  hipEvent_t pin_ev[2] = {nullptr, nullptr};
+  bool pin_busy = false;
+  // device blocks of freed ensembles kept for the next ones, at most
+  // kEnsCacheBytes in all; given back by wl_destroy and when an allocation
+  // fails (also one of a server's thread, hence the lock)
+  std::vector<std::pair<void*, size_t>> ens_cache;
+  std::mutex cache_mu;
   // device address of the allocation-free entry point's static scratch
   // array on this context's device (nullptr if it could not be obtained;
   // noalloc_status then holds the HIP error)
@@ -45,6 +58,8 @@ struct wl_ens {
   int64_t n_loops = 0;
   int32_t n_ppl = 0;
   int32_t n_groups = 0;
+  void* block = nullptr;  // one allocation of d_x, d_y, d_seg and d_norm
+  size_t block_bytes = 0;
   float* d_x = nullptr;
   float* d_y = nullptr;
   float4* d_seg = nullptr;
@@ -73,6 +88,40 @@ Sched make_sched(const wl_ctx* ctx, const wl_ens* e, int32_t n_pts);
 // FP64 segment array of an ensemble, built on first use on `stream`
 // (thread-safe; hipErrorOutOfMemory when the allocation fails).
 hipError_t ensure_seg64(const wl_ens* ens, hipStream_t stream);
+// hipMalloc that gives the context's kept ensemble blocks back and tries again
+// before it fails.
+hipError_t dev_malloc(wl_ctx* ctx, void** p, size_t bytes);
+
+// Device scratch of one call: the context's kept buffer (grown on demand) up
+// to kWorkKeep bytes, beyond that an allocation freed by the destructor.
+// p is NULL (and the context's message set) when the allocation fails.
+constexpr size_t kWorkKeep = (size_t)1 << 30;
+struct Work {
+  void* p = nullptr;
+  bool temporary = false;
+  Work(wl_ctx* ctx, size_t bytes, const char* what);
+  ~Work();
+  Work(const Work&) = delete;
+  Work& operator=(const Work&) = delete;
+};
+
+// Host arrays to and from device memory through the context's pinned staging
+// (a pageable copy goes through the runtime's own, piece by piece and each
+// with a wait).  A piece is [host, host + bytes) <-> device offset `off`.
+struct Piece {
+  void* host;
+  size_t off, bytes;
+};
+constexpr size_t kPinHalf = (size_t)8 << 20;
+// Enqueues the copies of the pieces to d_base + off on the ctx stream; the
+// host arrays may be reused on return.
+hipError_t copy_in(wl_ctx* ctx, void* d_base, const Piece* pieces, int n);
+// Copies d_base + off to the pieces after the work enqueued on the ctx stream
+// and waits for it: on return everything enqueued is complete.  The pieces'
+// offsets ascend (bytes between them are copied along); empty ones (host
+// NULL or no bytes) are skipped.
+hipError_t copy_out(wl_ctx* ctx, const void* d_base, const Piece* pieces, int n);
+
 // Event pair for the next timed launch of ctx (pooled; created on first use).
 hipError_t next_events(wl_ctx* ctx, hipEvent_t* a, hipEvent_t* b);
 

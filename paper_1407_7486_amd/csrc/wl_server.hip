@@ -4,8 +4,9 @@
 // A scheduler thread owns `slots` batch slots.  Each slot has its own stream
 // (default priority), pinned host staging, a device region for descriptors,
 // grids and results, a work counter, and one captured hipGraph per precision
-// (H2D of the staging -> counter reset -> persistent batch kernel ->
-// sub-range reduction -> statistics).  The batch kernels read the batch's
+// (counter reset -> persistent batch kernel -> results -> FP64 recomputation
+// of the flagged points -> their results), launched behind a copy of the
+// batch's staging.  The batch kernels read the batch's
 // composition from device memory, so a slot's graph is replayed for every
 // batch.  Requests are admitted first-come first-served into a free slot
 // while their partial-sum memory (group sums, sub-range partials, means,
@@ -56,6 +57,7 @@ struct Slot {
   hipGraph_t graph[3] = {nullptr, nullptr, nullptr};
   bool busy = false;
   std::atomic<bool> done{false};
+  std::condition_variable* wake = nullptr;  // the scheduler's
   std::vector<Ticket*> reqs;
   wl::BatchLayout lay;
   int prec = 0;
@@ -95,8 +97,12 @@ int sfail(wl_server* s, int code, const char* fmt, ...) {
 }
 
 void host_done(void* p) {
-  // runs on a HIP runtime thread: no HIP calls, no locks
-  static_cast<Slot*>(p)->done.store(true, std::memory_order_release);
+  // runs on a HIP runtime thread: no HIP calls, no locks (a wake-up that falls
+  // between the scheduler's check and its wait is made up by its poll)
+  Slot* sl = static_cast<Slot*>(p);
+  std::condition_variable* cv = sl->wake;
+  sl->done.store(true, std::memory_order_release);
+  cv->notify_all();
 }
 
 // Captures the device work of one batch of precision `prec` on slot `sl`.
@@ -110,12 +116,10 @@ hipError_t capture(wl_server* s, Slot* sl, int prec) {
   }
   hipError_t st = hipStreamBeginCapture(sl->stream, hipStreamCaptureModeThreadLocal);
   if (st != hipSuccess) return st;
-  hipError_t r = hipMemcpyAsync(sl->d_in, sl->h_in, s->cfg.input_bytes, hipMemcpyHostToDevice,
-                                sl->stream);
-  if (r == hipSuccess)
-    r = wl::launch_batch(prec, e->d_seg, e->d_seg64, e->d_norm, e->d_x, e->d_y, e->n_ppl,
-                         sl->d_in, e->n_groups, e->n_loops, sl->d_counter,
-                         (double*)sl->d_res, s->ctx->num_cu, sl->stream);
+  const hipError_t r =
+      wl::launch_batch(prec, e->d_seg, e->d_seg64, e->d_norm, e->d_x, e->d_y, e->n_ppl,
+                       sl->d_in, e->n_groups, e->n_loops, sl->d_counter, (double*)sl->d_res,
+                       s->ctx->num_cu, sl->stream);
   hipGraph_t g = nullptr;
   st = hipStreamEndCapture(sl->stream, &g);
   if (r != hipSuccess) {
@@ -188,6 +192,10 @@ hipError_t launch_slot(wl_server* s, Slot* sl, Slot* prev) {
   const Clock::time_point now = Clock::now();
   for (Ticket* t : sl->reqs) t->t_launch = now;
   if (e == hipSuccess && prev) e = hipStreamWaitEvent(sl->stream, prev->ev_done, 0);
+  // the staging's used part, ahead of the graph (as a node of it the copy
+  // would have the size of the whole staging: 160 us for 8 MiB)
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(sl->d_in, sl->h_in, sl->lay.in_bytes, hipMemcpyHostToDevice, sl->stream);
   if (e == hipSuccess) e = hipGraphLaunch(sl->exec[sl->prec], sl->stream);
   const size_t out_b = sl->lay.head_bytes;
   if (e == hipSuccess)
@@ -250,8 +258,8 @@ void scheduler(wl_server* s) {
       }
     }
     if (s->stop && s->pending.empty() && !any_busy) break;
-    // completions are signalled by a flag (no lock in the HIP callback), so
-    // poll them at a short interval while batches are in flight
+    // completions are signalled by a flag and a wake-up without the lock (see
+    // host_done), so poll them as well while batches are in flight
     s->cv.wait_for(lk, any_busy ? std::chrono::microseconds(200)
                                 : std::chrono::milliseconds(20));
   }
@@ -293,11 +301,12 @@ int wl_server_create(wl_ctx* ctx, const wl_ens* ens, const wl_server_config* cfg
   s->cfg = c;
   for (int i = 0; i < c.slots; ++i) {
     auto sl = std::make_unique<Slot>();
+    sl->wake = &s->cv;
     hipError_t e = hipStreamCreateWithFlags(&sl->stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipHostMalloc(&sl->h_in, c.input_bytes, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void**)&sl->h_res, c.result_bytes, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMalloc(&sl->d_in, c.input_bytes);
-    if (e == hipSuccess) e = hipMalloc(&sl->d_res, c.result_bytes);
+    if (e == hipSuccess) e = wl::dev_malloc(ctx, &sl->d_in, c.input_bytes);
+    if (e == hipSuccess) e = wl::dev_malloc(ctx, &sl->d_res, c.result_bytes);
     if (e == hipSuccess)
       e = hipMalloc((void**)&sl->d_counter, wl::kBatchCounters * sizeof(unsigned int));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl->ev_done, hipEventDisableTiming);
