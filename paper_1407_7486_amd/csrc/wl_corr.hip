@@ -27,29 +27,47 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int kTile = 128;  // output tile edge
 constexpr int kBK = 16;     // samples per LDS stage
 
-// Column sums of rows [r*chunk, (r+1)*chunk) into part[r][p].
-__global__ __launch_bounds__(256) void k_col_partial(const double* __restrict__ X,
-                                                     int64_t n_units, int32_t n_pts,
-                                                     int64_t chunk, double* __restrict__ part) {
-  const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
+// Column means, as the first row's value plus the mean deviation from it (so
+// that a constant column is centred to exact zeros).  Block (c, r): columns
+// 16 c .. 16 c + 15 of rows [r chunk, (r+1) chunk), 64 slots of rows side by
+// side, added as a tree; the deviations' sum goes to part[r], or with one
+// block of rows the mean to mu.  (One thread per column walking 4096 rows took
+// 0.50 ms for 2048 rows of 192 columns: a serial chain of row reads on one
+// compute unit; this takes 6 us.)
+constexpr int kMeanCols = 16, kMeanSlots = 64;
+__global__ __launch_bounds__(kMeanCols * kMeanSlots) void k_col_partial(
+    const double* __restrict__ X, int64_t n_units, int32_t n_pts, int64_t chunk,
+    double* __restrict__ part, double* __restrict__ mu) {
+  __shared__ double red[kMeanSlots][kMeanCols];
+  const int32_t c = threadIdx.x % kMeanCols, q = threadIdx.x / kMeanCols;
+  const int32_t p = blockIdx.x * kMeanCols + c;
+  const int32_t pc = p < n_pts ? p : n_pts - 1;
   const int64_t r = blockIdx.y;
-  if (p >= n_pts) return;
   const int64_t k0 = r * chunk;
-  int64_t k1 = k0 + chunk;
-  if (k1 > n_units) k1 = n_units;
+  const int64_t k1 = k0 + chunk < n_units ? k0 + chunk : n_units;
+  const double x0 = X[pc];
   double s = 0.0;
-  for (int64_t k = k0; k < k1; ++k) s += X[k * n_pts + p];
-  part[r * n_pts + p] = s;
+#pragma unroll 4
+  for (int64_t k = k0 + q; k < k1; k += kMeanSlots) s += X[k * n_pts + pc] - x0;
+  red[q][c] = s;
+  for (int32_t h = kMeanSlots / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if (q < h) red[q][c] += red[q + h][c];
+  }
+  if (q != 0 || p >= n_pts) return;
+  if (gridDim.y == 1) mu[p] = x0 + red[0][c] / (double)n_units;
+  else part[r * n_pts + p] = red[0][c];
 }
 
-__global__ __launch_bounds__(256) void k_col_mean(const double* __restrict__ part, int32_t n_rows,
-                                                  int32_t n_pts, int64_t n_units,
-                                                  double* __restrict__ mu) {
+__global__ __launch_bounds__(256) void k_col_mean(const double* __restrict__ X,
+                                                  const double* __restrict__ part,
+                                                  int32_t n_rows, int32_t n_pts,
+                                                  int64_t n_units, double* __restrict__ mu) {
   const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n_pts) return;
   double s = 0.0;
   for (int32_t r = 0; r < n_rows; ++r) s += part[(int64_t)r * n_pts + p];
-  mu[p] = s / (double)n_units;
+  mu[p] = X[p] + s / (double)n_units;
 }
 
 // Tile (bm, bn), bn >= bm, of the upper triangle from its linear index.
@@ -186,6 +204,7 @@ __global__ __launch_bounds__(256) void k_corr(const double* __restrict__ part, i
   const int32_t a = p < q ? p : q, b = p < q ? q : p;
   const int64_t sz = (int64_t)n_pts * n_pts;
   double c = 0.0, da = 0.0, db = 0.0;
+#pragma unroll 4
   for (int32_t s = 0; s < n_split; ++s) {
     c += part[s * sz + (int64_t)a * n_pts + b];
     da += part[s * sz + (int64_t)a * n_pts + a];
@@ -248,18 +267,27 @@ int wl_correlation(wl_ctx* ctx, const double* values, int64_t n_units, int32_t n
   const int32_t n_tiles = (n_pts + kTile - 1) / kTile;
   const int32_t tiles = n_tiles * (n_tiles + 1) / 2;
   // split the samples so that ~16 workgroups per CU have work (the last
-  // round of a launch is then a small share of it), in chunks of at least
-  // 256 samples, with at most 4 GiB of partials
+  // round of a launch is then a small share of it) in at most 8 splits, or,
+  // for few tiles, so that the chip is filled once (2 workgroups per CU) in at
+  // most 64; chunks of at least 64 samples, at most 4 GiB of partials (2048
+  // samples of 192 points: 47 us in 8 splits of 256 samples, 16 in 32 of 64)
   int64_t n_split = (16 * (int64_t)ctx->num_cu + tiles - 1) / tiles;
   if (n_split > 8) n_split = 8;
+  int64_t fill = 2 * (int64_t)ctx->num_cu / tiles;
+  if (fill > 64) fill = 64;
+  if (fill > n_split) n_split = fill;
   while (n_split > 1 && n_split * (int64_t)n_pts * n_pts * 8 > ((int64_t)4 << 30)) --n_split;
-  const int64_t max_split = (n_units + 255) / 256;
+  const int64_t max_split = (n_units + 63) / 64;
   if (n_split > max_split) n_split = max_split;
   if (n_split < 1) n_split = 1;
   int64_t k_chunk = (n_units + n_split - 1) / n_split;
   k_chunk = (k_chunk + kBK - 1) / kBK * kBK;
   n_split = (n_units + k_chunk - 1) / k_chunk;
-  const int32_t mean_rows = (int32_t)((n_units + 4095) / 4096 < 256 ? (n_units + 4095) / 4096 : 256);
+  // blocks of rows of the means: of at least 2048 rows, up to ~1024 blocks
+  const int32_t mean_cols = (n_pts + kMeanCols - 1) / kMeanCols;
+  int64_t mean_rows = (n_units + 2047) / 2048;
+  if (mean_rows > (1024 + mean_cols - 1) / mean_cols)
+    mean_rows = (1024 + mean_cols - 1) / mean_cols;
   const int64_t mean_chunk = (n_units + mean_rows - 1) / mean_rows;
   const int64_t sz = (int64_t)n_pts * n_pts;
   const int64_t vals_n = flags == WL_HOST_PTR ? n_units * n_pts : 0;
@@ -279,15 +307,15 @@ int wl_correlation(wl_ctx* ctx, const double* values, int64_t n_units, int32_t n
     const Piece in{(void*)values, 0, vals_n * sizeof(double)};
     e = copy_in(ctx, d_x, &in, 1);
   }
-  const dim3 cb((n_pts + 255) / 256, mean_rows);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_col_partial, cb, dim3(256), 0, ctx->stream, d_x, n_units, n_pts,
-                       mean_chunk, d_mp);
+    hipLaunchKernelGGL(k_col_partial, dim3(mean_cols, (uint32_t)mean_rows),
+                       dim3(kMeanCols * kMeanSlots), 0, ctx->stream, d_x, n_units, n_pts,
+                       mean_chunk, d_mp, d_mu);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_col_mean, dim3((n_pts + 255) / 256), dim3(256), 0, ctx->stream, d_mp,
-                       mean_rows, n_pts, n_units, d_mu);
+  if (e == hipSuccess && mean_rows > 1) {
+    hipLaunchKernelGGL(k_col_mean, dim3((n_pts + 255) / 256), dim3(256), 0, ctx->stream, d_x,
+                       d_mp, (int32_t)mean_rows, n_pts, n_units, d_mu);
     e = hipGetLastError();
   }
   hipEvent_t ev0 = nullptr, ev1 = nullptr;

@@ -1310,6 +1310,7 @@ __device__ __forceinline__ void add_in_order(const double (&S)[N], double (&tot)
   __syncthreads();
   if (q < N) {
     const double* r = round[buf][q] + pt;
+#pragma unroll 8
     for (int32_t j = 0; j < n; ++j) tot[0] += r[j * kFinPts];
   }
   buf ^= 1;
