@@ -867,6 +867,38 @@ static size_t eval_scratch_bytes(const wl::Sched& s, int64_t n_groups, int32_t n
          4 * ((size_t)n_pts + 1);
 }
 
+// Waves to a loop (launch_walk), or 0: a wave per loop (launch_average), by
+// the walks (loops x chunks) per SIMD.  Up to one walk, 8 waves: sech^2 spinor
+// at 1003 points 111 -> 62 us, rational 53 -> 42, constant 34 -> 27; loops of
+// under 256 points have too few blocks for 8, and below 128 (384 for the
+// fields whose block costs little) the terms' pass costs more (130 points:
+// constant 10.2 -> 12.9 us, sech^2 20.8 -> 17.4).  Beyond, only the fields with
+// costly blocks gain, with 4 waves (rational 56 -> 65 us at 2 walks).  Rows
+// of even rounds: up to 3 walks (sech^2 118 -> 85 us at 1.5, Gaussian 150 ->
+// 119 at 3 and equal at 4 and 6), sech^2 loops from 768 points that several
+// chunks read also beyond (8: 354 -> 320 us, 16: 656 -> 589; with one chunk
+// 2.42 -> 2.51 ms).  Rows whose last round leaves k_average's waves idle gain
+// most (9 loops: 5.4 walks 295 -> 178 us, 18: 638 -> 534, 42: 1614 -> 1508);
+// at 24 walks the terms take 38 MB, where this stops.  512 points are the
+// shortest with a gain there (256: sech^2 124 -> 132 us at 12).
+static int32_t walk_waves(const wl_ctx* ctx, const wl::Sched& s, int32_t kind, int32_t n_ppl) {
+  const int64_t walks = s.n_items * s.loops_per_sub, simds = 4 * (int64_t)ctx->num_cu;
+  const bool costly = kind == WL_SECH2 || kind == WL_GAUSS;
+  if (walks <= simds) return n_ppl < (costly ? 128 : 384) ? 0 : n_ppl < 256 ? 4 : 8;
+  if (!costly || n_ppl < 512) return 0;
+  const bool uneven = 100 * ((s.loops_per_sub + 7) / 8 * 8) > 115 * s.loops_per_sub;
+  const bool more = uneven || (kind == WL_SECH2 && n_ppl >= 768 && s.n_chunks > 1);
+  return walks <= (more ? 24 : 3) * simds ? 4 : 0;
+}
+static size_t walk_terms_bytes(const wl::Sched& s, int32_t n_pts) {
+  return (size_t)(s.n_items / s.n_chunks) * s.loops_per_sub * 3 * n_pts * sizeof(double);
+}
+static bool is_capturing(const wl_ctx* ctx) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(ctx->stream, &st) != hipSuccess ||
+         st != hipStreamCaptureStatusNone;
+}
+
 // Enqueue one evaluation; grid and outputs are device memory: the main
 // kernel, then the group sums, statistics, scale and rounding estimate per
 // point (and for WL_FP32C the FP64 recomputation of the flagged points).  With `noalloc` the call allocates nothing: the scratch
@@ -888,8 +920,17 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
       if (rc) return rc;
     }
   }
-  const wl::Sched s = make_sched(ctx, ens, n_pts);
-  const size_t need = eval_scratch_bytes(s, ens->n_groups, n_pts);
+  wl::Sched s = make_sched(ctx, ens, n_pts);
+  size_t need = eval_scratch_bytes(s, ens->n_groups, n_pts);
+  const size_t terms_off = (need + 7) & ~(size_t)7;
+  if (precision == WL_FP32C) {
+    // the loops' terms need room; without it, the walk of a wave per loop
+    s.walk = walk_waves(ctx, s, fa.kind, ens->n_ppl);
+    const size_t all = terms_off + walk_terms_bytes(s, n_pts);
+    if (s.walk && noalloc && all > WL_NOALLOC_SCRATCH_BYTES) s.walk = 0;
+    if (s.walk && !noalloc && all > ctx->partial_bytes && is_capturing(ctx)) s.walk = 0;
+    if (s.walk) need = all;
+  }
   void* buf;
   if (noalloc) {
     if (need > WL_NOALLOC_SCRATCH_BYTES)
@@ -916,8 +957,12 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
     if (e == hipSuccess) e = hipEventRecord(ev0, ctx->stream);
   }
   if (e == hipSuccess)
-    e = wl::launch_average(precision, spin, fa, ens->d_seg, ens->d_seg64, ens->d_norm,
-                           ens->n_ppl, d_rho, d_T, n_T, n_pts, s, p_w, p_a, p_v, ctx->stream);
+    e = s.walk ? wl::launch_walk(spin, fa, ens->d_seg, ens->d_norm, ens->n_ppl, d_rho, d_T, n_T,
+                                 n_pts, s, (double*)((char*)buf + terms_off), p_w, p_a, p_v,
+                                 ctx->stream)
+               : wl::launch_average(precision, spin, fa, ens->d_seg, ens->d_seg64, ens->d_norm,
+                                    ens->n_ppl, d_rho, d_T, n_T, n_pts, s, p_w, p_a, p_v,
+                                    ctx->stream);
   if (e == hipSuccess && ctx->timing && !noalloc) {
     e = hipEventRecord(ev1, ctx->stream);
     if (e == hipSuccess) ctx->n_timed++;

@@ -29,6 +29,7 @@ struct Sched {
   int32_t n_wg;             // workgroups (set by the launcher)
   int32_t n_xcd;            // XCDs the dispatcher round-robins over
   int32_t split;            // waves an item's loops are dealt to (launcher)
+  int32_t walk;             // waves to a loop (launch_walk), 0: launch_average
 };
 
 // Which part of each loop a per-loop evaluation walks: segments seg_off ..
@@ -104,6 +105,8 @@ constexpr int kWave = 64;
 constexpr int kFinishPts = 16;  // grid points per tile of the finishing kernels
 // most waves that an item's loops are dealt to (k_average, k_disc)
 constexpr int kSplitWaves = 8;
+// k_walk: waves to a loop (its workgroup), at most.
+constexpr int kWalkWaves = 8;
 
 // Per-segment unit quantities of the segment from
 // (x0, y0) to (x1, y1), formed in FP64 and rounded once to FP32.
@@ -147,6 +150,14 @@ hipError_t launch_average(int precision, int spin, const FieldArgs& f,
                           int32_t n_ppl, const double* d_rho, const double* d_T,
                           int32_t n_T, int32_t n_pts, const Sched& s, double* d_out,
                           double* d_out_a, double* d_out_v, hipStream_t stream);
+
+// The same for compensated FP32 and a launch that would leave most of the chip
+// idle (s.walk waves to each loop): same values, by way of every loop's terms,
+// d_terms [G n_sub][loops_per_sub][3][n_pts].
+hipError_t launch_walk(int spin, const FieldArgs& f, const float4* d_seg, const float2* d_norm,
+                       int32_t n_ppl, const double* d_rho, const double* d_T, int32_t n_T,
+                       int32_t n_pts, const Sched& s, double* d_terms, double* d_out,
+                       double* d_out_a, double* d_out_v, hipStream_t stream);
 
 // The results of an evaluation from its item sums d_out, d_out_a, d_out_v:
 // the group sums d_sums (d_out itself when n_sub == 1), means and errors

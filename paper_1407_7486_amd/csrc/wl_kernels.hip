@@ -414,6 +414,9 @@ __device__ __forceinline__ LaneF32 lane_consts(double rho, double s, double T,
 //          of A), qe_i the scale of qa_i's rounding (field_f32): the
 //          squared size of each term's rounding relative to u, the two
 //          parts of the cross product being summed apart.
+//   EST 3  none: the values qa that EST 1 samples go, in its order, to
+//          samples[0], samples[kWave], ..., and A, B, Q are the three sums
+//          sum c_i qa_i, sum d_y,i qa_i, sum qb_i (k_walk).
 // `stage`: the wave's LDS staging buffer of kWave segments (unused by the
 // walks that read through scalar loads).
 constexpr bool staged_walk(int kind, bool spin, bool comp) {
@@ -424,7 +427,8 @@ template <int KIND, bool SPIN, bool COMP, int EST = 0>
 __device__ __forceinline__ void loop_sums_f32(const float4* __restrict__ seg,
                                               int32_t n, const LaneF32& c,
                                               const FieldArgs& f, float4* stage,
-                                              double& A, double& B, double& Q) {
+                                              double& A, double& B, double& Q,
+                                              float* samples = nullptr) {
   constexpr bool kSpinSum = SPIN && KIND != kConst;
   const float Rf = KIND == kSech2 ? c.R_s : c.R;
   const float Uf = KIND == kSech2 ? c.U_s : c.U;
@@ -461,6 +465,11 @@ __device__ __forceinline__ void loop_sums_f32(const float4* __restrict__ seg,
     if constexpr (EST == 1) {
       if (sample == 1) qs = fmaf(qa, qa, qs);
       if (sample == 2) qs = fmaf(qa * 0.125f, qa, qs);
+    } else if constexpr (EST == 3) {
+      if (sample != 0) {
+        *samples = qa;
+        samples += kWave;
+      }
     } else if constexpr (EST == 2) {
       // the cross product's two parts are summed apart, each carrying
       // rounding of its own size
@@ -559,9 +568,15 @@ __device__ __forceinline__ void loop_sums_f32(const float4* __restrict__ seg,
     dd = s_.d;
     db = s_.b;
   }
+  if constexpr (EST == 3) {
+    A = dc;
+    B = dd;
+    Q = db;
+    return;
+  }
   const double R = Rf;
   const double U = Uf;
-  A = R * dc + U * dd;
+  A = fma(R, dc, U * dd);  // spelled out: every kernel rounds alike
   B = kSpinSum ? db : (double)n;
   Q = EST == 1 ? 8.0 * (double)qs : (double)qs;
 }
@@ -924,6 +939,18 @@ __device__ __forceinline__ int32_t tile_point(int32_t p, int32_t n_T, int32_t n_
   return j * n_T + k;
 }
 
+// A loop's sums to its w and its contributions to the mean's accumulators.
+template <bool SPIN, int PREC>
+__device__ __forceinline__ void sums_terms(double A, double B, double Q, double R, double U,
+                                           float2 nrm, double T, int32_t n_ppl,
+                                           const FieldArgs& f, double& w, double& da,
+                                           double& dv) {
+  double phi, S, cw, ch;
+  epilogue_parts<SPIN, PREC>(A, B, T, n_ppl, f, phi, S, cw, ch);
+  w = wprod<SPIN>(cw, ch);
+  loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, f.cphi), da, dv);
+}
+
 // One loop at this lane's grid point: its w, and its contributions da, dv to
 // the scale and rounding accumulators of the mean (loop_scale).  nrm: the
 // loop's norms sqrt(sum c^2), sqrt(sum d_y^2).  rho, s: FP64 in the walk's
@@ -935,7 +962,7 @@ __device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
                                            double T, const LaneF32& c, const FieldArgs& f,
                                            float4* stage, const Tables64& tab, double& w,
                                            double& da, double& dv) {
-  double A, B, Q, phi, S, cw, ch, R, U;
+  double A, B, Q, R, U;
   if constexpr (PREC == 2) {
     loop_sums_f64<KIND, SPIN, true>(seg64 + l * n_ppl, n_ppl, rho, s, f, tab, A, B, Q);
     R = s * s;
@@ -948,9 +975,7 @@ __device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
     R = KIND == kSech2 ? c.R_s : c.R;
     U = KIND == kSech2 ? c.U_s : c.U;
   }
-  epilogue_parts<SPIN, PREC>(A, B, T, n_ppl, f, phi, S, cw, ch);
-  w = wprod<SPIN>(cw, ch);
-  loop_scale(w, S, cw, ch, phase_l2(Q, n_ppl, R, U, nrm, f.cphi), da, dv);
+  sums_terms<SPIN, PREC>(A, B, Q, R, U, nrm, T, n_ppl, f, w, da, dv);
 }
 
 // The domain of a grid point: rho_cm >= 0 and T > 0, both finite.
@@ -1530,6 +1555,120 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
     out_a[o] = a + bad;
     out_v[o] = v + bad;
   }
+}
+
+// The same values as k_average's (compensated FP32) for a launch too small to
+// fill the chip: a workgroup per (item, loop), its waves taking the loop's
+// blocks (of 32 segments, then of 8, then the rest: the blocks of
+// loop_sums_f32, summed in FP32 and added in FP64) in turn.  A lone wave
+// issues one vector instruction per ~8.5 cycles, whatever its instructions
+// depend on, so that only more waves make such a walk faster.  The block
+// sums and the sampled qa pass through LDS and are added in block order by
+// four waves (one each for the three sums and the sample estimate): every
+// bit is that of one wave's walk.  The loop's terms go to
+// terms[row][loop of the row][w, da, dv][point], added in loop order by
+// k_walk_rows.  256 loops of 512 points on 21 grid points: 57 -> 20 us (the
+// call 90 -> 50); rows of 9 loops, 2040 x 1003 points on 561 Gaussian grid
+// points, 638 -> 534 us.  The rule is walk_waves'.
+constexpr int kBlockVals = 10;  // c, d, b sums and up to 7 samples
+template <int KIND, bool SPIN>
+__global__ __launch_bounds__(kWalkWaves * kWave) void k_walk(
+    const float4* __restrict__ seg, const float2* __restrict__ norm, int32_t n_ppl,
+    const double* __restrict__ rho_g, const double* __restrict__ T_g, int32_t n_T,
+    int32_t n_pts, FieldArgs f, Sched sc, double* __restrict__ terms) {
+  extern __shared__ float block_lds[];  // [waves][kBlockVals][kWave]
+  __shared__ double sums[4][kWave];
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int32_t n_waves = blockDim.x / kWave;  // >= 4
+  const int32_t lane = threadIdx.x % kWave;
+  const int64_t item = blockIdx.x / sc.loops_per_sub;
+  const int64_t j = blockIdx.x - item * sc.loops_per_sub;
+  const ItemRange r = item_range(item, sc.n_chunks, sc.n_sub, sc.loops_per_group,
+                                 sc.loops_per_sub);
+  const int64_t l = r.l0 + j;
+  if (l >= r.l1) return;  // the whole workgroup
+  const int32_t p = r.chunk * kWave + lane;
+  const int32_t pg = tile_point(p < n_pts ? p : n_pts - 1, n_T, n_pts);
+  const double rho = rho_g[pg / n_T];
+  const double T = T_g[pg % n_T];
+  const LaneF32 c = lane_consts(rho, sqrt(T), T, f);
+  const float4* loop = seg + l * n_ppl;
+  const int32_t n32 = n_ppl / 32, n8 = n_ppl % 32 / 8, rest = n_ppl % 8;
+  const int32_t n_blocks = n32 + n8 + (rest ? 1 : 0);
+  float* mine = block_lds + wave * kBlockVals * kWave + lane;
+  double tot = 0.0;  // waves 0-2: sums of c qa, d_y qa, qb
+  float qs = 0.0f;   // wave 3
+  for (int32_t b0 = 0; b0 < n_blocks; b0 += n_waves) {
+    const int32_t b = b0 + wave;
+    if (b < n_blocks) {
+      const int32_t s8 = b - n32;
+      const int32_t at = s8 < 0 ? 32 * b : 32 * n32 + 8 * s8;
+      const int32_t n = s8 < 0 ? 32 : s8 < n8 ? 8 : rest;
+      double bc, bd, bb;
+      loop_sums_f32<KIND, SPIN, true, 3>(loop + at, n, c, f, nullptr, bc, bd, bb,
+                                         mine + 3 * kWave);
+      mine[0] = (float)bc;  // one block's sums: floats
+      mine[kWave] = (float)bd;
+      mine[2 * kWave] = (float)bb;
+    }
+    __syncthreads();
+    const int32_t n_now = n_blocks - b0 < n_waves ? n_blocks - b0 : n_waves;
+    if (wave < 3) {
+      const float* v = block_lds + wave * kWave + lane;
+      for (int32_t k = 0; k < n_now; ++k) tot += (double)v[k * kBlockVals * kWave];
+    } else if (wave == 3) {
+      for (int32_t k = 0; k < n_now; ++k) {
+        const float* v = block_lds + (k * kBlockVals + 3) * kWave + lane;
+        const int32_t s8 = b0 + k - n32;
+        const int32_t n = s8 < 0 ? 4 : s8 < n8 ? 1 : rest;
+        const float unit = s8 < n8 ? 1.0f : 0.125f;  // exact
+        for (int32_t i = 0; i < n; ++i) {
+          const float qa = v[i * kWave];
+          qs = fmaf(qa * unit, qa, qs);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (wave < 4) sums[wave][lane] = wave < 3 ? tot : (double)qs;
+  __syncthreads();
+  if (wave != 0 || p >= n_pts) return;
+  const double R = KIND == kSech2 ? c.R_s : c.R;
+  const double U = KIND == kSech2 ? c.U_s : c.U;
+  const double A = fma(R, sums[0][lane], U * sums[1][lane]);
+  const double B = SPIN && KIND != kConst ? sums[2][lane] : (double)n_ppl;
+  double w, da, dv;
+  sums_terms<SPIN, 0>(A, B, 8.0 * sums[3][lane], R, U, norm[l], T, n_ppl, f, w, da, dv);
+  double* o = terms + (r.gs * sc.loops_per_sub + j) * 3 * n_pts + pg;
+  o[0] = w;
+  o[n_pts] = da;
+  o[2 * (int64_t)n_pts] = dv;
+}
+
+// Sums of k_walk's terms over each row's loops, in loop order.
+__global__ __launch_bounds__(256) void k_walk_rows(
+    const double* __restrict__ terms, const double* __restrict__ rho_g,
+    const double* __restrict__ T_g, int32_t n_T, int32_t n_pts, Sched sc,
+    double* __restrict__ out, double* __restrict__ out_a, double* __restrict__ out_v) {
+  const int32_t pg = blockIdx.x * blockDim.x + threadIdx.x;
+  if (pg >= n_pts) return;
+  const int64_t gs = blockIdx.y;
+  const int64_t first = gs % sc.n_sub * sc.loops_per_sub;
+  const int64_t left = sc.loops_per_group - first;
+  const int64_t n = left < sc.loops_per_sub ? left : sc.loops_per_sub;
+  const double* t = terms + gs * sc.loops_per_sub * 3 * n_pts + pg;
+  double acc = 0.0, a = 0.0, v = 0.0;
+#pragma unroll 4
+  for (int64_t j = 0; j < n; ++j, t += 3 * (int64_t)n_pts) {
+    acc += t[0];
+    a += t[n_pts];
+    v += t[2 * (int64_t)n_pts];
+  }
+  const double bad = grid_ok(rho_g[pg / n_T], T_g[pg % n_T]) ? 0.0 : NAN;  // as k_average
+  const int64_t o = gs * n_pts + pg;
+  out[o] = acc + bad;
+  out_a[o] = a + bad;
+  out_v[o] = v + bad;
 }
 
 // FP64 recomputation of the flagged grid points of an evaluation: the
@@ -2181,6 +2320,16 @@ hipError_t launch_avg_t(const FieldArgs& f, const float4* seg, const double4* se
 }
 
 template <int KIND, bool SPIN>
+hipError_t launch_walk_t(const FieldArgs& f, const float4* seg, const float2* norm,
+                         int32_t n_ppl, const double* rho, const double* T, int32_t n_T,
+                         int32_t n_pts, const Sched& s, double* terms, hipStream_t st) {
+  hipLaunchKernelGGL((k_walk<KIND, SPIN>), dim3((uint32_t)(s.n_items * s.loops_per_sub)),
+                     dim3(s.walk * kWave), (size_t)s.walk * kBlockVals * kWave * sizeof(float),
+                     st, seg, norm, n_ppl, rho, T, n_T, n_pts, f, s, terms);
+  return hipGetLastError();
+}
+
+template <int KIND, bool SPIN>
 hipError_t launch_esc_t(const FieldArgs& f, const float* x, const float* y, int32_t n_ppl,
                         const double* rho, const double* T, int32_t n_T, int32_t n_pts,
                         const Sched& s, const int32_t* list, const int32_t* count,
@@ -2315,6 +2464,34 @@ hipError_t launch_average(int precision, int spin, const FieldArgs& f,
                           double* d_out_a, double* d_out_v, hipStream_t stream) {
   WL_DISPATCH4(launch_avg_t, f, d_seg, d_seg64, d_norm, n_ppl, d_rho, d_T, n_T, n_pts, s,
                d_out, d_out_a, d_out_v, stream)
+}
+
+hipError_t launch_walk(int spin, const FieldArgs& f, const float4* d_seg, const float2* d_norm,
+                       int32_t n_ppl, const double* d_rho, const double* d_T, int32_t n_T,
+                       int32_t n_pts, const Sched& s, double* d_terms, double* d_out,
+                       double* d_out_a, double* d_out_v, hipStream_t stream) {
+  if (d_seg == nullptr || d_norm == nullptr || s.walk < 4 || s.walk > kWalkWaves)
+    return hipErrorInvalidValue;
+  hipError_t e = hipErrorInvalidValue;
+#define WL_WALK(K)                                                                        \
+  case K:                                                                                 \
+    e = spin ? launch_walk_t<K, true>(f, d_seg, d_norm, n_ppl, d_rho, d_T, n_T, n_pts, s, \
+                                      d_terms, stream)                                    \
+             : launch_walk_t<K, false>(f, d_seg, d_norm, n_ppl, d_rho, d_T, n_T, n_pts,   \
+                                       s, d_terms, stream);                               \
+    break;
+  switch (f.kind) {
+    WL_WALK(kConst)
+    WL_WALK(kSech2)
+    WL_WALK(kGauss)
+    WL_WALK(kRational)
+  }
+#undef WL_WALK
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_walk_rows,
+                     dim3((n_pts + 255) / 256, (uint32_t)(s.n_items / s.n_chunks)), dim3(256),
+                     0, stream, d_terms, d_rho, d_T, n_T, n_pts, s, d_out, d_out_a, d_out_v);
+  return hipGetLastError();
 }
 
 hipError_t launch_finish(int precision, int spin, const FieldArgs& f, const float* d_x,
