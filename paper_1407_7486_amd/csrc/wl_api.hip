@@ -359,8 +359,9 @@ ReqPlan plan_request(const wl_ctx* ctx, const wl_ens* ens, const wl_request& q) 
   // point, padded to 8 with the other requests'), the item scale and
   // rounding accumulators, the item partial sums of w when split, the
   // compacted list of flagged points with its count, and the request's
-  // row of the FP64 recomputation table, 8 x 8 bytes (with room for the
-  // table's final row and the alignments, also for a batch of one)
+  // entry of the FP64 recomputation table (64 bytes are set aside for it, 64
+  // more and 32 for the table's last entry and the alignments, also for a
+  // batch of one)
   const size_t part = (size_t)G * p.s.n_sub * p.n_pts;
   p.res_bytes = 8 * ((size_t)G * p.n_pts + 4 * (size_t)p.n_pts + 2 * part +
                      (p.s.n_sub > 1 ? part : 0)) +

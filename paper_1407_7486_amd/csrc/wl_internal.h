@@ -68,12 +68,11 @@ struct BatchHeader {
   int64_t total_items;  // units of work
   int64_t total_sums;
   int64_t total_pts;
-  int64_t* esc_begin;  // [8][n_reqs + 1] first FP64 recomputation item per
-                       // request, per field kind x spin
+  int64_t* esc_begin;  // [n_reqs + 1] first FP64 recomputation item of each
+                       // request
 };
-// Work counters of a batch: the item loop, and one per field kind x spin
-// for the FP64 recomputation.
-constexpr int kBatchCounters = 9;
+// Work counters of a batch: the item loop and the FP64 recomputation.
+constexpr int kBatchCounters = 2;
 constexpr size_t kBatchDescOffset = 64;
 
 // One request of a batched evaluation (device-resident descriptor).

@@ -1940,19 +1940,18 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_batch(
            (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)t);
   }
 }
-#undef WL_EACH_VARIANT
 
 // FP64 recomputation of the flagged grid points of a compensated-FP32
-// batch, one kernel per field kind and spin (a kernel holding every
-// variant would spill inside the segment walks): a persistent loop over the
-// escalate_item items of the batch's requests of that variant, taken from
-// the variant's work counter; the header's esc_begin table of the variant,
-// [n_reqs + 1], holds the first item of each request (k_esc_begin; requests
-// of other variants have none).
-constexpr int kVariants = 8;  // field kind x spin
-template <int KIND, bool SPIN>
+// batch: a persistent loop over the escalate_item items of its requests,
+// taken from a work counter; the header's esc_begin table [n_reqs + 1] holds
+// the first item of each request (k_esc_begin).  One kernel for every field
+// and spin: an item is walked at its waves' own pace, so the variants' items
+// have to run side by side (seven requests of sech^2 and Gaussian tubes, 1024
+// loops of 1024 points: kernels of 151, 71 and 64 us one after the other and
+// five without work, 5 us each, against 204 us in one).
+constexpr int kEscBatchWaves = 4;  // per SIMD: 128 VGPRs hold every variant
 __global__ __launch_bounds__(kWavesPerWG * kWave)
-__attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
+__attribute__((amdgpu_waves_per_eu(kEscBatchWaves))) void k_escalate_batch(
     const float* __restrict__ X, const float* __restrict__ Y, int32_t n_ppl,
     const BatchHeader* __restrict__ hdr, unsigned int* __restrict__ counter,
     int32_t n_groups, int64_t loops_per_group) {
@@ -1961,13 +1960,12 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = hdr->n_reqs;
-  const int64_t* __restrict__ esc_begin =
-      hdr->esc_begin + (int64_t)(KIND * 2 + (SPIN ? 1 : 0)) * (n_reqs + 1);
+  const int64_t* __restrict__ esc_begin = hdr->esc_begin;
   // the table is written by an earlier kernel, so its entries come in
   // through vector loads: wave_uniform keeps the loop's branches scalar
   const int64_t total = wave_uniform(esc_begin[n_reqs]);
   if (blockIdx.x >= total) return;
-  if constexpr (uses_tables<KIND>()) load_tables64(sh.tab);
+  load_tables64(sh.tab);
   int32_t buf = 0, turn = 0;
   for (int64_t item = blockIdx.x; item < total; item = next_item(taken, turn)) {
     ask_item(counter, taken, turn);
@@ -1980,40 +1978,41 @@ __attribute__((amdgpu_waves_per_eu(kEscWaves))) void k_escalate_batch(
     }
     const ReqDesc& q = reqs[lo];
     const int32_t cnt = __builtin_amdgcn_readfirstlane(*q.count);
-    escalate_item<KIND, SPIN>(X, Y, n_ppl, q.rho, q.T, q.n_T, q.n_pts, q.f,
-                              item - wave_uniform(esc_begin[lo]), (int64_t)n_groups * q.n_sub,
-                              q.n_sub, loops_per_group, q.loops_per_sub, q.list, cnt, q.out_v,
-                              q.scale, q.out, sh, buf);
+    const int64_t li = item - wave_uniform(esc_begin[lo]);
+#define WL_ITEM(K, SP)                                                                   \
+  escalate_item<K, SP>(X, Y, n_ppl, q.rho, q.T, q.n_T, q.n_pts, q.f, li,                 \
+                       (int64_t)n_groups * q.n_sub, q.n_sub, loops_per_group,            \
+                       q.loops_per_sub, q.list, cnt, q.out_v, q.scale, q.out, sh, buf)
+    WL_EACH_VARIANT(WL_ITEM)
+#undef WL_ITEM
   }
 }
+#undef WL_EACH_VARIANT
 
-// First recomputation item of each request of a batch, per variant, in
-// request order: for the request's variant v,
-// esc_begin[v][r + 1] = esc_begin[v][r] + esc_items(G n_sub_r, count_r);
-// the other variants' tables repeat their entry.  One workgroup: its threads
-// read a tile of requests side by side, then one thread per variant adds.
+// First recomputation item of each request of a batch, in request order:
+// esc_begin[r + 1] = esc_begin[r] + esc_items(G n_sub_r, count_r).  One
+// workgroup: its threads read a tile of requests side by side, then one
+// thread adds.
 constexpr int kEscTile = 256;
 __global__ __launch_bounds__(kEscTile) void k_esc_begin(const BatchHeader* __restrict__ hdr,
                                                         int32_t n_groups) {
   __shared__ int64_t items[kEscTile];
-  __shared__ int32_t variant[kEscTile];
   const ReqDesc* __restrict__ reqs =
       (const ReqDesc*)((const char*)hdr + kBatchDescOffset);
   const int32_t n_reqs = hdr->n_reqs;
   const int32_t t = threadIdx.x;
-  int64_t* table = hdr->esc_begin + (int64_t)t * (n_reqs + 1);  // t < kVariants
+  int64_t* table = hdr->esc_begin;
   int64_t acc = 0;
-  if (t < kVariants) table[0] = 0;
+  if (t == 0) table[0] = 0;
   for (int32_t r0 = 0; r0 < n_reqs; r0 += kEscTile) {
     if (r0 + t < n_reqs) {
       const ReqDesc& q = reqs[r0 + t];
       items[t] = esc_items((int64_t)n_groups * q.n_sub, *q.count);
-      variant[t] = q.f.kind * 2 + (q.spin ? 1 : 0);
     }
     __syncthreads();
-    if (t < kVariants)
+    if (t == 0)
       for (int32_t r = r0; r < n_reqs && r < r0 + kEscTile; ++r) {
-        if (variant[r - r0] == t) acc += items[r - r0];
+        acc += items[r - r0];
         table[r + 1] = acc;
       }
     __syncthreads();
@@ -2589,7 +2588,7 @@ hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg
   // persistent workgroups: as many as the chip holds at the kernels' waves
   // per SIMD (those without work exit at once)
   const dim3 wide_wg(n_cu * 4 * wide_waves(precision) / kSplitWaves);
-  const dim3 item_wg(n_cu * 4 * 8 / kWavesPerWG), esc_wg(n_cu * 4 * kEscWaves / kWavesPerWG);
+  const dim3 item_wg(n_cu * 4 * 8 / kWavesPerWG), esc_wg(n_cu * 4 * kEscBatchWaves / kWavesPerWG);
 #define WL_BATCH(PREC)                                                                     \
   hipLaunchKernelGGL((k_batch_wide<PREC>), wide_wg, split_blk, 0, stream, d_seg, d_seg64,  \
                      d_norm, n_ppl, hdr, d_counter, n_groups, lpg);                        \
@@ -2614,19 +2613,9 @@ hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_esc_begin, dim3(1), dim3(kEscTile), 0, stream, hdr, n_groups);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-#define WL_ESCB(K, SP, V)                                                              \
-  hipLaunchKernelGGL((k_escalate_batch<K, SP>), esc_wg, blk, 0, stream, d_x, d_y, n_ppl, \
-                     hdr, d_counter + 1 + (V), n_groups, lpg);                          \
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-    WL_ESCB(kConst, false, 0)
-    WL_ESCB(kConst, true, 1)
-    WL_ESCB(kSech2, false, 2)
-    WL_ESCB(kSech2, true, 3)
-    WL_ESCB(kGauss, false, 4)
-    WL_ESCB(kGauss, true, 5)
-    WL_ESCB(kRational, false, 6)
-    WL_ESCB(kRational, true, 7)
-#undef WL_ESCB
+    hipLaunchKernelGGL(k_escalate_batch, esc_wg, blk, 0, stream, d_x, d_y, n_ppl, hdr,
+                       d_counter + 1, n_groups, lpg);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL((k_finish_batch<true>), dim3(512), fin, 0, stream, hdr, n_groups,
                        n_loops, (int32_t)precision, d_res);
     e = hipGetLastError();
