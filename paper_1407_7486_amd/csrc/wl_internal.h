@@ -18,8 +18,8 @@ namespace wl {
 // and its squared radius is (rho_cm + s m_x)^2 + T m_y^2 (m_y only enters
 // squared, so the square is stored: one multiply less per segment).
 
-// Work decomposition of one evaluation: one wavefront per item
-// (group g, loop sub-range `sub`, chunk of 64 grid points).
+// Work decomposition of one evaluation: items (group g, loop sub-range
+// `sub`, chunk of 64 grid points).
 struct Sched {
   int64_t loops_per_group;  // N_l / G
   int64_t loops_per_sub;    // ceil(loops_per_group / n_sub)
@@ -220,8 +220,8 @@ hipError_t launch_disc_finish(const double* d_part, double* d_sums, int32_t n_gr
 // followed by the descriptors, whose pointers place every array).  Results at
 // d_res: [group sums | means | errors | scales | rounding estimates | flags |
 // ...] with the sizes from the header.  Grid sizes are fixed (persistent
-// workgroups filling n_cu compute units) and d_counter holds kBatchCounters work counters, so the
-// sequence can be captured once and replayed.
+// workgroups filling n_cu compute units) and d_counter holds kBatchCounters
+// work counters, so the sequence can be captured once and replayed.
 hipError_t launch_batch(int precision, const float4* d_seg, const double4* d_seg64,
                         const float2* d_norm, const float* d_x, const float* d_y,
                         int32_t n_ppl, const void* d_hdr, int32_t n_groups, int64_t n_loops,

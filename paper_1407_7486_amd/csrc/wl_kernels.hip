@@ -1,17 +1,18 @@
 // Wilson-loop ensemble average: HIP kernels for gfx950 (MI355X).
 //
-// Mapping.  One wavefront owns one work item = (loop group g, sub-range of
-// the group's loops, 64 consecutive (rho_cm, T) grid points).  Lane j holds
-// grid point j of the chunk and walks every segment of every loop of the
-// item in order.  The segment data of the loop being walked are the same
+// Mapping.  A work item is (loop group g, sub-range of the group's loops, 64
+// consecutive (rho_cm, T) grid points): lane j holds grid point j of the
+// chunk, and the item's loops are dealt to the waves of a workgroup (k_average,
+// k_disc, k_batch_wide), walked by one wave (k_batch), or given 4 or 8 waves
+// each (k_walk).  The segment data of the loop being walked are the same
 // for all 64 lanes, so they arrive through wave-uniform (scalar) loads and
 // sit in SGPRs, or (the compensated walks of every field but the sech^2
 // spinor one) are copied 64 at a time into a per-wave LDS buffer and read
 // back as broadcasts: one fetch of a segment serves 64 (rho, T)
 // evaluations, and the loop tile is reused across the whole grid.  A lane's
 // per-loop phase and spin sums therefore need no
-// wavefront reduction, and its FP64 group-sum accumulator has exactly one
-// owner and a fixed loop order (deterministic results).
+// wavefront reduction, and the item's FP64 sum over its loops is taken in
+// loop order whatever the waves (deterministic results).
 //
 // Arithmetic per segment (Sec. 3.2.1, Eqs. rhoi..Ci with the midpoint rule
 // t = 1/2, and Sec. 3.2.2, Eq. Wfermfpl), from the unit midpoint m, the unit
