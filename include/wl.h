@@ -270,9 +270,10 @@ int wl_average_async(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
  * item sums of the evaluation (w when a group's loops are split, and the
  * scale and rounding accumulators: 8 (2 or 3) G n_sub n_rho n_T bytes, n_sub
  * the library's split of each group's loops, at most 64, 1 when a group is
- * small or the grid large) and one flag byte per grid point, lives in a
- * static device array of WL_NOALLOC_SCRATCH_BYTES per device, reserved when
- * the library is loaded and held until the process ends.  Every call on a device shares that
+ * small or the grid large), one flag byte per grid point and, where it fits
+ * too, a small launch's sums per loop, lives in a static device array of
+ * WL_NOALLOC_SCRATCH_BYTES per device, reserved when the library is loaded
+ * and held until the process ends.  Every call on a device shares that
  * array: calls that overlap on one device (two contexts or streams)
  * race and must be serialised by the caller.  Nothing in the array needs
  * to start at zero.

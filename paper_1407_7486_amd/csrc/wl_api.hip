@@ -622,6 +622,8 @@ int wl_destroy(wl_ctx* ctx) {
     if (ctx->d_grid) (void)hipFree(ctx->d_grid);
     if (ctx->d_out) (void)hipFree(ctx->d_out);
     if (ctx->d_partial) (void)hipFree(ctx->d_partial);
+    for (void* p : ctx->d_terms)
+      if (p) (void)hipFree(p);
     if (ctx->d_flag) (void)hipFree(ctx->d_flag);
     if (ctx->d_counter) (void)hipFree(ctx->d_counter);
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
@@ -880,7 +882,7 @@ static size_t eval_scratch_bytes(const wl::Sched& s, int64_t n_groups, int32_t n
 // chunks read also beyond (8: 354 -> 320 us, 16: 656 -> 589; with one chunk
 // 2.42 -> 2.51 ms).  Rows whose last round leaves k_average's waves idle gain
 // most (9 loops: 5.4 walks 295 -> 178 us, 18: 638 -> 534, 42: 1614 -> 1508);
-// at 24 walks the terms take 38 MB, where this stops.  512 points are the
+// at kWalkMost walks the terms take 38 MB, where this stops.  512 points are the
 // shortest with a gain there (256: sech^2 124 -> 132 us at 12).
 static int32_t walk_waves(const wl_ctx* ctx, const wl::Sched& s, int32_t kind, int32_t n_ppl) {
   const int64_t walks = s.n_items * s.loops_per_sub, simds = 4 * (int64_t)ctx->num_cu;
@@ -889,15 +891,27 @@ static int32_t walk_waves(const wl_ctx* ctx, const wl::Sched& s, int32_t kind, i
   if (!costly || n_ppl < 512) return 0;
   const bool uneven = 100 * ((s.loops_per_sub + 7) / 8 * 8) > 115 * s.loops_per_sub;
   const bool more = uneven || (kind == WL_SECH2 && n_ppl >= 768 && s.n_chunks > 1);
-  return walks <= (more ? 24 : 3) * simds ? 4 : 0;
+  return walks <= (more ? kWalkMost : kWalkFew) * simds ? 4 : 0;
 }
 static size_t walk_terms_bytes(const wl::Sched& s, int32_t n_pts) {
   return (size_t)(s.n_items / s.n_chunks) * s.loops_per_sub * 3 * n_pts * sizeof(double);
 }
-static bool is_capturing(const wl_ctx* ctx) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(ctx->stream, &st) != hipSuccess ||
-         st != hipStreamCaptureStatusNone;
+// The context's room for the loops' terms: two buffers, for the launches of up
+// to kWalkFew and kWalkMost walks per SIMD, each allocated by the first call
+// that needs it and never moved, so that no later call takes it from under a
+// captured one.  NULL where it cannot be had (under capture, or out of memory).
+static double* walk_terms(wl_ctx* ctx, const wl::Sched& s) {
+  const int64_t simds = 4 * (int64_t)ctx->num_cu;
+  const bool few = s.n_items * s.loops_per_sub <= kWalkFew * simds;
+  void** p = &ctx->d_terms[few ? 0 : 1];
+  if (!*p) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) (void)hipGetLastError();
+    else if (st == hipStreamCaptureStatusNone)
+      (void)dev_malloc(ctx, p, (size_t)(few ? kWalkFew : kWalkMost) * simds * kWave * 3 *
+                                   sizeof(double));
+  }
+  return (double*)*p;
 }
 
 // Enqueue one evaluation; grid and outputs are device memory: the main
@@ -922,15 +936,17 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
     }
   }
   wl::Sched s = make_sched(ctx, ens, n_pts);
-  size_t need = eval_scratch_bytes(s, ens->n_groups, n_pts);
-  const size_t terms_off = (need + 7) & ~(size_t)7;
+  const size_t need = eval_scratch_bytes(s, ens->n_groups, n_pts);
+  double* terms = nullptr;
   if (precision == WL_FP32C) {
-    // the loops' terms need room; without it, the walk of a wave per loop
+    // without room for the loops' terms, the walk of a wave per loop
     s.walk = walk_waves(ctx, s, fa.kind, ens->n_ppl);
-    const size_t all = terms_off + walk_terms_bytes(s, n_pts);
-    if (s.walk && noalloc && all > WL_NOALLOC_SCRATCH_BYTES) s.walk = 0;
-    if (s.walk && !noalloc && all > ctx->partial_bytes && is_capturing(ctx)) s.walk = 0;
-    if (s.walk) need = all;
+    const size_t off = (need + 7) & ~(size_t)7;
+    if (s.walk && !noalloc)
+      terms = walk_terms(ctx, s);
+    else if (s.walk && off + walk_terms_bytes(s, n_pts) <= WL_NOALLOC_SCRATCH_BYTES)
+      terms = (double*)((char*)ctx->d_noalloc + off);
+    if (!terms) s.walk = 0;
   }
   void* buf;
   if (noalloc) {
@@ -959,8 +975,7 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
   }
   if (e == hipSuccess)
     e = s.walk ? wl::launch_walk(spin, fa, ens->d_seg, ens->d_norm, ens->n_ppl, d_rho, d_T, n_T,
-                                 n_pts, s, (double*)((char*)buf + terms_off), p_w, p_a, p_v,
-                                 ctx->stream)
+                                 n_pts, s, terms, p_w, p_a, p_v, ctx->stream)
                : wl::launch_average(precision, spin, fa, ens->d_seg, ens->d_seg64, ens->d_norm,
                                     ens->n_ppl, d_rho, d_T, n_T, n_pts, s, p_w, p_a, p_v,
                                     ctx->stream);

@@ -29,6 +29,7 @@ struct wl_ctx {
   void* d_batch = nullptr;  // batched evaluation: descriptors, grids, results
   size_t batch_bytes = 0;
   unsigned int* d_counter = nullptr;  // work counters of persistent launches
+  void* d_terms[2] = {};  // loops' terms of small launches (walk_terms)
   void* d_work = nullptr;  // scratch of the correlation, regroup and action calls
   size_t work_bytes = 0;
   // pinned staging of host arrays (two halves of kPinHalf; see copy_in,

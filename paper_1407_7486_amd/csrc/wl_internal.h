@@ -104,8 +104,10 @@ constexpr int kWave = 64;
 constexpr int kFinishPts = 16;  // grid points per tile of the finishing kernels
 // most waves that an item's loops are dealt to (k_average, k_disc)
 constexpr int kSplitWaves = 8;
-// k_walk: waves to a loop (its workgroup), at most.
+// k_walk: waves to a loop (its workgroup) at most, and the walks (loops x
+// chunks) per SIMD up to which it is taken (walk_waves).
 constexpr int kWalkWaves = 8;
+constexpr int kWalkFew = 3, kWalkMost = 24;
 
 // Per-segment unit quantities of the segment from
 // (x0, y0) to (x1, y1), formed in FP64 and rounded once to FP32.

@@ -71,3 +71,63 @@ def test_walk_domain(wl):
     finally:
         wl.wl_ensemble_free(ens)
         wl.wl_destroy(ctx)
+
+
+@pytest.mark.parametrize("warm_fp64", [False, True])
+def test_walk_captured(wl, warm_fp64):
+    """A captured small launch, replayed between eager launches of other sizes,
+    keeps giving the eager result: the loops' terms have a fixed place.  Warmed
+    up in FP64 only, that place does not exist yet and may not be allocated
+    under capture: the captured launch walks each loop with one wave."""
+    import torch
+    print("[case] walk captured", warm_fp64, flush=True)
+    x, y = wlinputs.polygon_loops(256, 600, seed=6)
+    st = torch.cuda.Stream()
+    ctx = wl.wl_create(0, st.cuda_stream)
+    ens = wl.wl_ensemble_upload(ctx, x, y, 8)
+    fld = wl.field(1, 2.0, 1.2)
+
+    def dev(*shape):
+        return torch.zeros(*shape, dtype=torch.float64, device="cuda")
+
+    def grid(n_rho, n_T):
+        return (torch.linspace(0.0, 4.0, n_rho, dtype=torch.float64, device="cuda"),
+                torch.logspace(-2.0, 1.0, n_T, dtype=torch.float64, device="cuda"),
+                dev(8, n_rho, n_T), dev(n_rho, n_T), dev(n_rho, n_T))
+
+    def run(g, prec):
+        rho, T, sums, mean, err = g
+        wl.wl_average_async(ctx, ens, fld, rho, T, 1, prec, mean, err, sums)
+
+    try:
+        small, other = grid(4, 16), grid(8, 24)
+        want = wl.wl_average(ctx, ens, fld, small[0].cpu().numpy(), small[1].cpu().numpy(), 1,
+                             wl.WL_FP32C) if not warm_fp64 else None
+        torch.cuda.synchronize()
+        run(small, wl.WL_FP64 if warm_fp64 else wl.WL_FP32C)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            run(small, wl.WL_FP32C)
+        for k in range(3):
+            if not warm_fp64:  # (a larger scratch would move the captured one)
+                run(grid(2, 16), wl.WL_FP32C)
+            for a in small[2:]:
+                a.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            got = [a.cpu().numpy() for a in (small[3], small[4], small[2])]
+            if want is None:
+                want = got
+            for u, v in zip(got, want):
+                assert np.array_equal(u, v), k
+        del graph
+        run(other, wl.WL_FP32C)
+        eager = wl.wl_average(ctx, ens, fld, small[0].cpu().numpy(), small[1].cpu().numpy(), 1,
+                              wl.WL_FP32C)
+        for u, v in zip(want, eager):
+            assert np.array_equal(u, v)
+    finally:
+        wl.wl_ensemble_free(ens)
+        wl.wl_destroy(ctx)
