@@ -198,8 +198,8 @@ static void* ens_block(wl_ctx* ctx, size_t bytes, size_t* got) {
   *got = bytes;
   return dev_malloc(ctx, &p, bytes) == hipSuccess ? p : nullptr;
 }
-// Takes back a block that no enqueued work uses: the oldest kept ones go when
-// it takes them over the bound.
+// Takes back a block (the caller has waited for the device): the oldest kept
+// ones go when it takes them over the bound.
 static void ens_block_free(wl_ctx* ctx, void* p, size_t bytes) {
   if (!p) return;
   if (bytes > kEnsCacheBytes) {
@@ -775,9 +775,15 @@ int wl_ensemble_download(const wl_ens* ens, float* y_x, float* y_y, int64_t loop
 int wl_ensemble_free(wl_ens* ens) {
   if (!ens) return WL_OK;
   DeviceGuard g(ens->ctx->device);
-  if (ens->ctx->stream) (void)hipStreamSynchronize(ens->ctx->stream);
-  else (void)hipDeviceSynchronize();
-  ens_block_free(ens->ctx, ens->block, ens->block_bytes);
+  // the points may be in use on any stream (a captured launch replayed on
+  // another than the context's): what hipFree waits for itself, the next
+  // ensemble in a kept block would not
+  if (hipDeviceSynchronize() == hipSuccess) {
+    ens_block_free(ens->ctx, ens->block, ens->block_bytes);
+  } else {
+    (void)hipGetLastError();
+    if (ens->block) (void)hipFree(ens->block);
+  }
   if (ens->d_sub) (void)hipFree(ens->d_sub);
   if (ens->d_seg64) (void)hipFree(ens->d_seg64);
   if (ens->d_sub64) (void)hipFree(ens->d_sub64);
