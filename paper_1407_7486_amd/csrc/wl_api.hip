@@ -244,10 +244,14 @@ int check_field(wl_ctx* ctx, const wl_field* f, wl::FieldArgs* a) {
   const double log2e = 1.4426950408889634074;
   a->kind = f->kind;
   a->inv_lam_d = 1.0 / l;
-  a->lam2_d = l * l;
+  // constants that all segments share: one rounding each
+  const long double ll = (long double)l * l, log2el = 1.44269504088896340736L;
+  a->inv_lam2_d = (double)(1.0L / ll);
+  a->exp2_scale_d = 0.0;
+  a->rad2_d = (double)ll;
   a->inv_lam2 = (float)(1.0 / (l * l));
-  a->lam2 = (float)a->lam2_d;
-  a->lam2_lo = (float)(a->lam2_d - (double)a->lam2);
+  a->lam2 = (float)(l * l);
+  a->lam2_lo = (float)(l * l - (double)a->lam2);
   a->thr = 0.0f;
   double e2 = 0.0;
   switch (f->kind) {
@@ -255,20 +259,24 @@ int check_field(wl_ctx* ctx, const wl_field* f, wl::FieldArgs* a) {
       a->cphi = 0.5 * f->eB0;
       a->cspin = f->eB0;
       break;
-    case WL_SECH2:  // g = eB0 lam^2 qa, b = eB0 * 4 * E/(1+E)^2; the walks
-      // work in units scaled by gs = 2 log2(e)/lambda: qa is divided by
-      // ln2 gs^2 and the cross product multiplied by gs^2
-      a->cphi = (f->eB0 * l * l) * 0.69314718055994530942;
+    case WL_SECH2:  // g = eB0 lam^2 ln2 qa, b = eB0 * 4 * E/(1+E)^2; the FP32
+      // walks work in units scaled by gs = 2 log2(e)/lambda (qa is divided by
+      // gs^2 and the cross product multiplied by it)
+      a->cphi = (double)(f->eB0 * ll * 0.69314718055994530942L);
       a->cspin = 4.0 * f->eB0;
+      a->exp2_scale_d = (double)(2.0L * log2el / l);
+      a->rad2_d = (double)(0.25L * ll);  // u < 1/2
       break;
     case WL_GAUSS:  // g = (eB0 lam^2/2) (1-E)/rho^2, b = eB0 E
       e2 = -log2e / (l * l);
-      a->cphi = 0.5 * f->eB0 * l * l;
+      a->cphi = (double)(0.5L * f->eB0 * ll);
       a->cspin = f->eB0;
       a->thr = (float)(0.25 * l * l);  // v < 1/4
+      a->exp2_scale_d = (double)(log2el / ll);
+      a->rad2_d = (double)(0.5L * ll);  // v < 1/2
       break;
     case WL_RATIONAL:  // g = (eB0 lam^2/2) r, b = eB0 lam^4 r^2
-      a->cphi = 0.5 * f->eB0 * l * l;
+      a->cphi = (double)(0.5L * f->eB0 * ll);
       a->cspin = f->eB0 * l * l * l * l;
       break;
   }

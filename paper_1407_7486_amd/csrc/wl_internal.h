@@ -53,9 +53,12 @@ struct FieldArgs {
   float exp2_scale_lo, lam2_lo;  // rounding residues of exp2_scale, lam2
   float thr;         // GAUSS: rho^2 below which the polynomial branch is used
   // FP64 path
-  double inv_lam_d, lam2_d;
+  double inv_lam_d, inv_lam2_d;
+  double exp2_scale_d;  // SECH2: 2 log2(e)/lambda ; GAUSS: log2(e)/lambda^2
+  double rad2_d;        // SECH2, GAUSS: rho^2 below which the polynomial branch
+                        // is used (u < 1/2, v < 1/2) ; RATIONAL: lambda^2
   // epilogue: Phi = cphi * sum_i cross_i qa_i ; S = cspin (T/N) sum_i qb_i
-  // (in the walks' units: sech^2's cphi holds ln 2)
+  // (sech^2's cphi holds ln 2)
   double cphi, cspin;
 };
 

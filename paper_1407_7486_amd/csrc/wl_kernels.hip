@@ -241,8 +241,8 @@ __device__ __forceinline__ void sqrt_rsq64(double x, double& root, double& inv) 
 // workgroup: a lane reads its own entry there while other waves issue.  The
 // walk is bound by FP64 issue (4.5 cycles per wave-instruction): with 64
 // entries 2^-t takes 9 FP64 instructions instead of 16 and with 128 entries
-// log2(1+E) 7 instead of 14.  Together with the scaled units, the third-order
-// steps above and (recomputation) the staged segments: 32768 x 1024 loops on
+// log2(1+E) 7 instead of 14.  Together with the third-order steps above and
+// (recomputation) the staged segments: 32768 x 1024 loops on
 // 64 x 64, sech^2 spinor, 264 -> 211 ms; the recomputation of 558 points of
 // 1024 x 8192 loops 13.9 -> 10.7 ms.  The error against 64-bit values in
 // torch is the same (means of 2048 x 4096 loops 2.6e-14 before and after).
@@ -265,15 +265,15 @@ __device__ __forceinline__ void load_tables64(Tables64& tab) {
 // 2^-t for t >= 0: -t = n/64 + f with n = rint(-64 t) (the low word of
 // 1.5 2^52 - 64 t), |f| <= 1/128; 2^(n mod 64 / 64) from the table with
 // n div 64 added to its exponent, times 1 + f P(f), P of degree 4.  t is
-// held below 1021 first (its high word, an integer minimum), where 2^-t is
-// still normal; beyond, the result stays near 2^-1021 instead of 0.
-__device__ __forceinline__ double exp2_neg64(double t, const Tables64& tab) {
-  const double tc = __hiloint2double((int)min((uint32_t)__double2hiint(t), 0x408fe000u),
-                                     __double2loint(t));
+// held below 1021 first (its high word, an integer minimum; the caller's t
+// too, so that t 2^-t ends with 2^-t), where 2^-t is still normal: beyond
+// 1020 the result stays near 2^-1020 instead of reaching 0.
+__device__ __forceinline__ double exp2_neg64(double& t, const Tables64& tab) {
+  t = __hiloint2double((int)min((uint32_t)__double2hiint(t), 0x408fe000u), __double2loint(t));
   constexpr double kMagic = 6755399441055744.0;  // 1.5 2^52
-  const double z = fma(-64.0, tc, kMagic);
+  const double z = fma(-64.0, t, kMagic);
   const int n = __double2loint(z);
-  const double f = fma(z - kMagic, -0.015625, -tc);
+  const double f = fma(z - kMagic, -0.015625, -t);
   const double T0 = tab.exp2[n & 63];
   const double T = __hiloint2double(__double2hiint(T0) + (int)((uint32_t)(n >> 6) << 20),
                                     __double2loint(T0));
@@ -291,21 +291,13 @@ __device__ __forceinline__ double one_minus_log2_1p(double E, double opE,
   return fma(-r, horner_sv_f64<WL_LOG2P1_F64_DEG>(WL_LOG2P1_F64, r), c.y);
 }
 
-// The FP64 walk's units: the geometry is multiplied by gs so that the squared
-// radius is r2 = t^2 (sech^2: t = 2 u log2(e), u = rho/lambda, as in FP32) or
-// r2 = v log2(e) (Gaussian: v = u^2), the arguments of exp2; the cross
-// product is in the same units, and what the ratio of qa to its value in
-// plain units leaves (ln 2 for sech^2) is in the epilogue constant cphi.
-template <int KIND>
-__device__ __forceinline__ double unit_scale64(const FieldArgs& f) {
-  if constexpr (KIND == kSech2) return kTwoLog2e * f.inv_lam_d;
-  if constexpr (KIND == kGauss) return 1.2011224087864498 * f.inv_lam_d;  // sqrt(log2 e)
-  return 1.0;
-}
-
 // The phase weight qa and the spin integrand b1 b2 (a product the caller
 // adds with one FMA; as for the sums below, written out so that every kernel
-// rounds alike).
+// rounds alike).  The geometry stays unscaled and exp2's argument costs a
+// product: scaled by its factor beforehand, as in FP32, every segment of a lane
+// shares the rounding of the scaled rho and sqrt(T) (Gaussian spin exponents
+// then 1.5e-15 to 2.1e-15 off instead of 0.95e-15, relative rms over loops of 1024 points
+// against long double; the product is 1 of some 50 FP64 instructions).
 template <int KIND>
 __device__ __forceinline__ void field_f64(double r2, const FieldArgs& f, const Tables64& tab,
                                           double& qa, double& b1, double& b2) {
@@ -316,30 +308,33 @@ __device__ __forceinline__ void field_f64(double r2, const FieldArgs& f, const T
     b1 = b2 = 1.0;
   } else if constexpr (KIND == kSech2) {
     // E = exp(-2u) = 2^-t.  Away from the axis (u >= 1/2, so E <= 1/e) the
-    // phase weight is (1 - log2(1+E) - t E/(1+E)) / r2.
-    constexpr double kInv = 1.0 / (kTwoLog2e * kTwoLog2e);  // r2 -> u^2
+    // phase weight is (1 - log2(1+E) - t E/(1+E)) / r2; ln 2 is in cphi.
     double t, q;
     sqrt_rsq64(r2, t, q);
+    t *= f.exp2_scale_d;
     const double E = exp2_neg64(t, tab);
     const double opE = 1.0 + E;
     const double ip = rcp64(opE);
     const double Eip = E * ip;
     b1 = Eip;
     b2 = ip;
-    if (r2 < 0.25 * kTwoLog2e * kTwoLog2e) {
-      qa = horner_sv_f64<WL_Q_SECH2_F64_DEG>(WL_Q_SECH2_F64, r2 * kInv) * (kInv / kLn2);
+    if (r2 < f.rad2_d) {
+      qa = horner_sv_f64<WL_Q_SECH2_F64_DEG>(WL_Q_SECH2_F64, r2 * f.inv_lam2_d) *
+           f.inv_lam2_d * kLog2e;
     } else {
       qa = fma(-t, Eip, one_minus_log2_1p(E, opE, tab)) * (q * q);
     }
   } else if constexpr (KIND == kGauss) {
-    const double E = exp2_neg64(r2, tab);
+    double t = r2 * f.exp2_scale_d;
+    const double E = exp2_neg64(t, tab);
     b1 = E;
     b2 = 1.0;
-    qa = r2 < 0.5 * kLog2e
-             ? horner_sv_f64<WL_P_GAUSS_F64_DEG>(WL_P_GAUSS_F64, r2 * kLn2) * kLn2
+    qa = r2 < f.rad2_d
+             ? horner_sv_f64<WL_P_GAUSS_F64_DEG>(WL_P_GAUSS_F64, r2 * f.inv_lam2_d) *
+                   f.inv_lam2_d
              : (1.0 - E) * rcp64(r2);
   } else {
-    const double r = rcp64(r2 + f.lam2_d);
+    const double r = rcp64(r2 + f.rad2_d);
     qa = r;
     b1 = b2 = r;
   }
@@ -648,8 +643,7 @@ __device__ __forceinline__ void loop_sums_f32k(const float4* __restrict__ seg, i
 // rounding of m_y^2 and c) and read from an array: the midpoint's radius
 // from m_x and m_y^2, and the
 // cross product's two parts summed apart as in the FP32 path,
-// cross = s^2 c + rho s d_y, with rho and s = sqrt(T) in the walk's units
-// (unit_scale64).  With EST, Q = sum_i qa_i^2.
+// cross = s^2 c + rho s d_y, s = sqrt(T).  With EST, Q = sum_i qa_i^2.
 template <int KIND, bool SPIN, bool EST>
 struct Sums64 {
   double ac = 0.0, ad = 0.0, b = 0.0, q2 = 0.0;
@@ -954,8 +948,8 @@ __device__ __forceinline__ void sums_terms(double A, double B, double Q, double 
 
 // One loop at this lane's grid point: its w, and its contributions da, dv to
 // the scale and rounding accumulators of the mean (loop_scale).  nrm: the
-// loop's norms sqrt(sum c^2), sqrt(sum d_y^2).  rho, s: FP64 in the walk's
-// units (unit_scale64; the FP32 paths take theirs from c).
+// loop's norms sqrt(sum c^2), sqrt(sum d_y^2).  rho, s = sqrt(T): for the FP64
+// walk (the FP32 paths take theirs from c).
 template <int KIND, bool SPIN, int PREC>
 __device__ __forceinline__ void loop_terms(const float4* __restrict__ seg,
                                            const double4* __restrict__ seg64, float2 nrm,
@@ -1044,8 +1038,6 @@ __device__ __forceinline__ void run_bundle(const float4* __restrict__ seg,
   const double T = q.T[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, q.f);
-  const double gs = PREC == 2 ? unit_scale64<KIND>(q.f) : 1.0;
-  const double rho_u = rho * gs, s_u = s * gs;
 
   double acc = 0.0, a = 0.0, v = 0.0;
   int32_t buf = 0;
@@ -1053,7 +1045,7 @@ __device__ __forceinline__ void run_bundle(const float4* __restrict__ seg,
     const int64_t l = r.l0 + k + part;
     double w = 0.0, da = 0.0, dv = 0.0;
     if (l < r.l1)
-      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, q.f,
+      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, q.f,
                                    sh.stage[wave], sh.tab, w, da, dv);
     if (team == 1) {
       acc += w;
@@ -1102,13 +1094,11 @@ __device__ __forceinline__ void run_item(const float4* __restrict__ seg,
   const double T = q.T[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, q.f);
-  const double gs = PREC == 2 ? unit_scale64<KIND>(q.f) : 1.0;
-  const double rho_u = rho * gs, s_u = s * gs;
 
   double acc = 0.0, a = 0.0, v = 0.0;
   for (int64_t l = r.l0; l < r.l1; ++l) {
     double w, da, dv;
-    loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, q.f, stage,
+    loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, q.f, stage,
                                  tab, w, da, dv);
     acc += w;
     a += da;
@@ -1227,8 +1217,6 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
   const double rho = rho_g[pg / n_T];
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
-  const double gs_u = unit_scale64<KIND>(f);
-  const double rho_u = rho * gs_u, s_u = s * gs_u;
   double acc = 0.0;
   // copy r's part of the staging buffer: P entries, and 16 bytes between the
   // copies so that their broadcasts fall on different banks
@@ -1240,8 +1228,8 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
     const int64_t l = lr + r;
     Sums64<KIND, SPIN, false> sums;
     if (l < l1)
-      loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, 0, 1, i0, i1, rho_u,
-                                   s_u, f, sh.tab, mine, p, P, sums);
+      loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, 0, 1, i0, i1, rho,
+                                   s, f, sh.tab, mine, p, P, sums);
     sh.part[buf][wave][0][lane] = sums.ac;
     sh.part[buf][wave][1][lane] = sums.ad;
     if constexpr (SPIN && KIND != kConst) sh.part[buf][wave][2][lane] = sums.b;
@@ -1254,7 +1242,7 @@ __device__ __forceinline__ void escalate_item(const float* __restrict__ X,
         sums.ad += sh.part[buf][w][1][lane];
         if constexpr (SPIN && KIND != kConst) sums.b += sh.part[buf][w][2][lane];
       }
-      sums.finish(rho_u, s_u, s_u * s_u, n_ppl, A, B);
+      sums.finish(rho, s, s * s, n_ppl, A, B);
       acc += epilogue<SPIN, 2>(A, B, T, n_ppl, f, phi, S);
     }
     buf ^= 1;
@@ -1510,8 +1498,6 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
-  const double gs = PREC == 2 ? unit_scale64<KIND>(f) : 1.0;
-  const double rho_u = rho * gs, s_u = s * gs;
 
   double acc = 0.0, a = 0.0, v = 0.0;
   double* mine = terms + wave * 3 * kWave + lane;
@@ -1521,7 +1507,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void k_average(
     const int64_t l = l0 + wave;
     double w, da, dv;
     if (l < r.l1)
-      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho_u, s_u, T, c, f, stage,
+      loop_terms<KIND, SPIN, PREC>(seg, seg64, norm[l], n_ppl, l, rho, s, T, c, f, stage,
                                    tab, w, da, dv);
     if (split == 1) {
       acc += w;
@@ -1755,8 +1741,6 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
   const double T = T_g[pg % n_T];
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
-  const double gs = PREC == 2 ? unit_scale64<KIND>(f) : 1.0;
-  const double rho_u = rho * gs, s_u = s * gs;
   const int32_t h = n_ppl / 2, q = n_ppl / 4;
   double Q;
 
@@ -1771,9 +1755,9 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
       double Ac, Bc, As, Bs, At, Bt;
       if constexpr (PREC == 2) {
         const double4* u = sub64 + l * n_ppl;
-        loop_sums_f64<KIND, SPIN, false>(u, h, rho_u, s_u, f, tab, Ac, Bc, Q);
-        loop_sums_f64<KIND, SPIN, false>(u + h, q, rho_u, s_u, f, tab, As, Bs, Q);
-        loop_sums_f64<KIND, SPIN, false>(u + h + q, q, rho_u, s_u, f, tab, At, Bt, Q);
+        loop_sums_f64<KIND, SPIN, false>(u, h, rho, s, f, tab, Ac, Bc, Q);
+        loop_sums_f64<KIND, SPIN, false>(u + h, q, rho, s, f, tab, As, Bs, Q);
+        loop_sums_f64<KIND, SPIN, false>(u + h + q, q, rho, s, f, tab, At, Bt, Q);
       } else {
         const float4* u = sub + l * n_ppl;
         loop_sums_f32<KIND, SPIN, PREC == 0>(u, h, c, f, stage, Ac, Bc, Q);
@@ -1784,7 +1768,7 @@ __attribute__((amdgpu_waves_per_eu(6))) void k_disc(
       if (full) {
         double A, B, phi, S;
         if constexpr (PREC == 2) {
-          loop_sums_f64<KIND, SPIN, false>(seg64 + l * n_ppl, n_ppl, rho_u, s_u, f, tab, A,
+          loop_sums_f64<KIND, SPIN, false>(seg64 + l * n_ppl, n_ppl, rho, s, f, tab, A,
                                            B, Q);
         } else {
           loop_sums_f32<KIND, SPIN, PREC == 0>(seg + l * n_ppl, n_ppl, c, f, stage, A, B, Q);
@@ -2108,10 +2092,9 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
   const double s = sqrt(T);
   const LaneF32 c = lane_consts(rho, s, T, f);
   __shared__ float4 stage[staged_walk(KIND, SPIN, PREC == 0) ? kWavesPerWG : 1][kWave];
-  const double gs = unit_scale64<KIND>(f);
   double A, B, Q, phi, S;
   if constexpr (PREC == 2) {
-    loop_sums_f64<KIND, SPIN, false>(seg64 + l * n_ppl + sl.seg_off, sl.m, rho * gs, s * gs, f,
+    loop_sums_f64<KIND, SPIN, false>(seg64 + l * n_ppl + sl.seg_off, sl.m, rho, s, f,
                                      tab, A, B, Q);
   } else if constexpr (PREC == 3) {
     loop_sums_f32k<KIND, SPIN>(seg + l * n_ppl + sl.seg_off, sl.m, c, f, A, B, Q);
@@ -2128,9 +2111,9 @@ __global__ __launch_bounds__(kWavesPerWG * kWave) void k_per_loop(
       double A64, B64, phi64, S64;
       Sums64<KIND, SPIN, false> sums;
       loop_sums_f64raw<KIND, SPIN>(X + l * n_ppl, Y + l * n_ppl, n_ppl, sl.first, sl.stride, 0,
-                                   sl.m, rho * gs, s * gs, f, tab, raw_stage[kRaw ? wave : 0],
+                                   sl.m, rho, s, f, tab, raw_stage[kRaw ? wave : 0],
                                    lane, kWave, sums);
-      sums.finish(rho * gs, s * gs, (s * gs) * (s * gs), sl.m, A64, B64);
+      sums.finish(rho, s, s * s, sl.m, A64, B64);
       const double w64 = epilogue<SPIN, 2>(A64, B64, T, sl.m, f, phi64, S64);
       if (esc) {
         phi = phi64;
