@@ -384,20 +384,34 @@ bool build_batch(const wl_ens* ens, const wl_request* const* reqs, const FieldAr
   *lay = BatchLayout();
   int64_t grid_n = 0;
   // Wide (k_batch_wide) or narrow: an item per wave ends in a part-empty round
-  // of whole items (~0.4 of one); bundles cost 3%, more where a last round of
-  // loops leaves waves of a team idle, and in FP64, whose bundle kernel keeps
-  // fewer waves.  Rounds of the chip's wave slots, narrow and wide: 1: 1.64
-  // and 1.0 ms; 17: 30.2 and 31.0; 4 (plain FP32) 9.3 and 8.8; 6 with 10
-  // loops per row 19.2 and 21.0; 4 in FP64 28.8 and 32.7.
-  int64_t items_n = 0, uneven = 0;
+  // of whole items; bundles cost a few percent, more where a last round of
+  // loops leaves waves of a team idle, and in FP64, whose bundle kernel holds
+  // half as many waves.  Time of the wide form over the narrow one's, by the
+  // rounds of the chip's wave slots (sech^2 and Gaussian spinor; in brackets
+  // constant and rational):
+  //   rows of 8, FP32C  0.06: 0.35  0.5: 0.89  2: 0.95  4: 0.98  8: 1.02 (1.04)
+  //   rows of 1         0.25: 0.99  2: 1.08 (0.82)  8: 1.02 (0.83)
+  //   rows of 13        0.06: 0.48  0.5: 0.93  2: 0.96 (0.91)
+  //   rows of 9         0.12: 0.78  0.23: 0.89  0.35: 1.07  0.47: 0.98 (1.12)  3.8: 1.14
+  //   rows of 6         0.17: 0.91  0.33: 0.97  0.5: 1.21  2: 1.13  4: 1.15
+  //   rows of 8, FP64   0.06: 0.30  0.25: 0.80 (0.83)  0.5: 1.02 (1.61)  2: 1.05 (1.94)
+  //   rows of 9, FP64   0.03: 0.24  0.12: 0.72 (0.61)  0.23: 1.10 (1.17)  1.9: 1.37
+  //   rows of 6, FP64   0.17: 0.79 (0.83)  0.33: 1.14 (1.19)
+  // Plain FP32 lies within 0.05 of FP32C.
+  int64_t items_n = 0, turns = 0, loops = 0;
   for (int32_t i = 0; i < n; ++i) {
     const int64_t lps = plans[i].s.loops_per_sub, team = wide_team(lps);
     items_n += plans[i].s.n_items;
-    if (100 * ((lps + team - 1) / team * team) > 115 * lps) uneven += plans[i].s.n_items;
+    turns += plans[i].s.n_items * ((lps + team - 1) / team * team);
+    loops += plans[i].s.n_items * lps;
   }
   const int64_t round = 32 * (int64_t)ens->ctx->num_cu;
-  const int64_t limit = reqs[0]->precision == WL_FP64 ? 2 : 2 * uneven > items_n ? 3 : 10;
-  const bool wide = items_n < limit * round;
+  const int64_t idle = 100 * turns / loops - 100;  // waves' turns without a loop, percent
+  const int64_t limit = reqs[0]->precision == WL_FP64 ? (idle <= 25 ? 30 : 20)
+                        : idle <= 15                  ? 1000
+                        : idle <= 25                  ? 300
+                                                      : 45;  // percent of a round
+  const bool wide = 100 * items_n < limit * round;
   for (int32_t i = 0; i < n; ++i) {
     lay->items += wide ? bundles(plans[i].s) : plans[i].s.n_items;
     lay->sums_n += G * plans[i].n_pts;

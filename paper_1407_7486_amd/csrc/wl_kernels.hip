@@ -1870,7 +1870,10 @@ __device__ __forceinline__ int32_t owner(const ReqDesc* __restrict__ reqs, int32
     case 6: X(kRational, false); break;         \
     default: X(kRational, true); break;         \
   }
-constexpr int wide_waves(int prec) { return prec == 2 ? 6 : 8; }  // per SIMD
+// Waves per SIMD of the bundle kernels.  FP64: 128 VGPRs hold every variant
+// (at 6 waves 60 were spilled: 4096 x 512 loops on 16 x 16 points 1.71 ms, 1.28
+// at 4); it is taken for batches that fill few of the slots.
+constexpr int wide_waves(int prec) { return prec == 2 ? 4 : 8; }
 template <int PREC>
 __global__ __launch_bounds__(kSplitWaves * kWave)
 __attribute__((amdgpu_waves_per_eu(wide_waves(PREC)))) void k_batch_wide(
