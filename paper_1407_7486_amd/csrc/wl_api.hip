@@ -80,25 +80,53 @@ Work::~Work() {
   if (temporary && p) (void)hipFree(p);
 }
 
-// The staging buffer, free of copies in flight.
-static hipError_t pin_ready(wl_ctx* ctx) {
-  if (!ctx->h_pin) {
-    hipError_t e = hipHostMalloc((void**)&ctx->h_pin, 2 * kPinHalf, hipHostMallocDefault);
-    for (int k = 0; k < 2 && e == hipSuccess; ++k)
-      e = hipEventCreateWithFlags(&ctx->pin_ev[k], hipEventDisableTiming);
-    if (e != hipSuccess) return e;
+// Makes the staging buffer and its events; false (and nothing left behind, so
+// that the next call tries again) where they cannot be had.
+static bool pin_make(wl_ctx* ctx) {
+  if (ctx->h_pin) return true;
+  char* p = nullptr;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  bool ok = hipHostMalloc((void**)&p, 2 * kPinHalf, hipHostMallocDefault) == hipSuccess;
+  for (int k = 0; k < 2 && ok; ++k)
+    ok = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    for (hipEvent_t e : ev)
+      if (e) (void)hipEventDestroy(e);
+    if (p) (void)hipHostFree(p);
+    return false;
   }
-  if (ctx->pin_busy) {
-    const hipError_t e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return e;
-    ctx->pin_busy = false;
+  ctx->h_pin = p;
+  for (int k = 0; k < 2; ++k) ctx->pin_ev[k] = ev[k];
+  return true;
+}
+
+// The copies of copy_in or copy_out without the staging buffer.
+static hipError_t copy_direct(wl_ctx* ctx, char* d_base, const Piece* pieces, int n,
+                              hipMemcpyKind kind) {
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < n && e == hipSuccess; ++i) {
+    const Piece& q = pieces[i];
+    if (!q.host || !q.bytes) continue;
+    char* d = d_base + q.off;
+    e = kind == hipMemcpyHostToDevice ? hipMemcpyAsync(d, q.host, q.bytes, kind, ctx->stream)
+                                      : hipMemcpyAsync(q.host, d, q.bytes, kind, ctx->stream);
   }
-  return hipSuccess;
+  return e;
 }
 
 hipError_t copy_in(wl_ctx* ctx, void* d_base, const Piece* pieces, int n) {
-  hipError_t e = pin_ready(ctx);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (!pin_make(ctx)) {
+    e = copy_direct(ctx, (char*)d_base, pieces, n, hipMemcpyHostToDevice);
+    const hipError_t w = hipStreamSynchronize(ctx->stream);
+    return e == hipSuccess ? w : e;
+  }
+  if (ctx->pin_busy) {  // copies of an earlier call that failed later on
+    e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess) return e;
+    ctx->pin_busy = false;
+  }
   // halves are filled in turn; pieces that lie side by side on the device and
   // fit a half together travel in one copy
   int half = 0;
@@ -141,10 +169,18 @@ hipError_t copy_out(wl_ctx* ctx, const void* d_base, const Piece* pieces, int n)
       if (pieces[i].off < lo) lo = pieces[i].off;
       if (pieces[i].off + pieces[i].bytes > hi) hi = pieces[i].off + pieces[i].bytes;
     }
-  if (hi == 0) return hipStreamSynchronize(ctx->stream);
+  if (hi == 0) {
+    const hipError_t w = hipStreamSynchronize(ctx->stream);
+    if (w == hipSuccess) ctx->pin_busy = false;
+    return w;
+  }
+  if (!pin_make(ctx)) {
+    const hipError_t r =
+        copy_direct(ctx, (char*)d_base, pieces, n, hipMemcpyDeviceToHost);
+    const hipError_t w = hipStreamSynchronize(ctx->stream);
+    return r == hipSuccess ? w : r;
+  }
   // (copy_in's copies are ahead on the same stream: their half may be reused)
-  hipError_t e = ctx->h_pin ? hipSuccess : pin_ready(ctx);
-  if (e != hipSuccess) return e;
   ctx->pin_busy = true;
   auto ask = [&](size_t c) {  // chunk c of [lo, hi) into its half
     const size_t a = lo + c * kPinHalf, b = a + kPinHalf < hi ? a + kPinHalf : hi;
@@ -154,7 +190,7 @@ hipError_t copy_out(wl_ctx* ctx, const void* d_base, const Piece* pieces, int n)
     return r;
   };
   const size_t chunks = (hi - lo + kPinHalf - 1) / kPinHalf;
-  e = ask(0);
+  hipError_t e = ask(0);
   int first = 0;  // pieces before it are complete
   for (size_t c = 0; c < chunks && e == hipSuccess; ++c) {
     if (c + 1 < chunks) e = ask(c + 1);

@@ -108,7 +108,8 @@ struct Work {
 
 // Host arrays to and from device memory through the context's pinned staging
 // (a pageable copy goes through the runtime's own, piece by piece and each
-// with a wait).  A piece is [host, host + bytes) <-> device offset `off`.
+// with a wait; so these go too where the staging cannot be had).  A piece is
+// [host, host + bytes) <-> device offset `off`.
 struct Piece {
   void* host;
   size_t off, bytes;
