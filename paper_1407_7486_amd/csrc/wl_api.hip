@@ -80,10 +80,22 @@ Work::~Work() {
   if (temporary && p) (void)hipFree(p);
 }
 
+// While it lives, this thread's allocations do not end the capture of another
+// stream (torch captures in the global mode, in which any hipMalloc would): for
+// buffers made on first use, which calls of the same kind did without before.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+
 // Makes the staging buffer and its events; false (and nothing left behind, so
 // that the next call tries again) where they cannot be had.
 static bool pin_make(wl_ctx* ctx) {
   if (ctx->h_pin) return true;
+  const RelaxedCapture relaxed;
   char* p = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool ok = hipHostMalloc((void**)&p, 2 * kPinHalf, hipHostMallocDefault) == hipSuccess;
@@ -971,9 +983,15 @@ static double* walk_terms(wl_ctx* ctx, const wl::Sched& s) {
   if (!*p) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) (void)hipGetLastError();
-    else if (st == hipStreamCaptureStatusNone)
-      (void)dev_malloc(ctx, p, (size_t)(few ? kWalkFew : kWalkMost) * simds * kWave * 3 *
-                                   sizeof(double));
+    else if (st == hipStreamCaptureStatusNone) {
+      const RelaxedCapture relaxed;
+      // (not dev_malloc: the walk can do without, so kept blocks stay)
+      if (hipMalloc(p, (size_t)(few ? kWalkFew : kWalkMost) * simds * kWave * 3 *
+                           sizeof(double)) != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+      }
+    }
   }
   return (double*)*p;
 }
