@@ -234,7 +234,7 @@ int wl_action(wl_ctx* ctx, const wl_action_spec* sp, const wl_field* field, int3
   double* d_am = d_derr + nr;
   hipError_t e = hipSuccess;
   if (flags == WL_HOST_PTR) {
-    const Piece in{(void*)group_sums, 0, sums_n * sizeof(double)};
+    Piece in{(void*)group_sums, 0, sums_n * sizeof(double)};
     e = copy_in(ctx, d_sums, &in, 1);
   }
   if (e == hipSuccess)
@@ -243,7 +243,7 @@ int wl_action(wl_ctx* ctx, const wl_action_spec* sp, const wl_field* field, int3
                           ctx->stream);
   // results from d_dens on: densities (the LCF row last), actions, statistics
   const size_t D = sizeof(double);
-  const Piece out_p[] = {{out->density, 0, G * nr * D},
+  Piece out_p[] = {{out->density, 0, G * nr * D},
                          {out->lcf_density, G * nr * D, nr * D},
                          {out->action, dens_n * D, G * D},
                          {out->lcf_action, (dens_n + G) * D, D},

@@ -113,42 +113,47 @@ static bool pin_make(wl_ctx* ctx) {
   return true;
 }
 
-// The copies of copy_in or copy_out without the staging buffer.
-static hipError_t copy_direct(wl_ctx* ctx, char* d_base, const Piece* pieces, int n,
-                              hipMemcpyKind kind) {
-  hipError_t e = hipSuccess;
-  for (int i = 0; i < n && e == hipSuccess; ++i) {
-    const Piece& q = pieces[i];
+// Which pieces go without staging: all where it cannot be had, and arrays of at
+// least kPinDirect bytes that the device reaches itself (pinned by the caller):
+// the staging's memcpy is slower than the copy (wl_per_loop, three pinned arrays
+// of 1 MiB 108 us, staged 200; of 64 MiB 3.6 ms, staged 7.2).  Pageable arrays
+// the runtime copies piece by piece itself (three of 1 MiB 205 us, staged 187;
+// of 64 MiB 11.3 ms, staged 7.3).
+static bool mark_direct(wl_ctx* ctx, Piece* pieces, int n) {
+  const bool staging = pin_make(ctx);
+  bool any_staged = false;
+  for (int i = 0; i < n; ++i) {
+    Piece& q = pieces[i];
     if (!q.host || !q.bytes) continue;
-    char* d = d_base + q.off;
-    e = kind == hipMemcpyHostToDevice ? hipMemcpyAsync(d, q.host, q.bytes, kind, ctx->stream)
-                                      : hipMemcpyAsync(q.host, d, q.bytes, kind, ctx->stream);
+    q.direct = !staging;
+    if (staging && q.bytes >= kPinDirect) {
+      hipPointerAttribute_t a;
+      if (hipPointerGetAttributes(&a, q.host) != hipSuccess) (void)hipGetLastError();
+      else q.direct = a.type != hipMemoryTypeUnregistered;
+    }
+    any_staged |= !q.direct;
   }
-  return e;
+  return any_staged;
 }
 
-hipError_t copy_in(wl_ctx* ctx, void* d_base, const Piece* pieces, int n) {
+hipError_t copy_in(wl_ctx* ctx, void* d_base, Piece* pieces, int n) {
   hipError_t e = hipSuccess;
-  if (!pin_make(ctx)) {
-    e = copy_direct(ctx, (char*)d_base, pieces, n, hipMemcpyHostToDevice);
-    const hipError_t w = hipStreamSynchronize(ctx->stream);
-    return e == hipSuccess ? w : e;
-  }
-  if (ctx->pin_busy) {  // copies of an earlier call that failed later on
+  if (mark_direct(ctx, pieces, n) && ctx->pin_busy) {
+    // copies of an earlier call that failed later on
     e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return e;
-    ctx->pin_busy = false;
+    if (e == hipSuccess) ctx->pin_busy = false;
   }
   // halves are filled in turn; pieces that lie side by side on the device and
   // fit a half together travel in one copy
   int half = 0;
   bool used[2] = {false, false};
   size_t fill = 0, start = 0;  // staged bytes of the half, their device offset
-  auto flush = [&]() {
+  auto flush = [&](bool last) {
     if (fill == 0) return hipSuccess;
     hipError_t r = hipMemcpyAsync((char*)d_base + start, ctx->h_pin + half * kPinHalf, fill,
                                   hipMemcpyHostToDevice, ctx->stream);
     ctx->pin_busy = true;
+    if (last) return r;
     if (r == hipSuccess) r = hipEventRecord(ctx->pin_ev[half], ctx->stream);
     used[half] = true;
     half ^= 1;
@@ -157,68 +162,109 @@ hipError_t copy_in(wl_ctx* ctx, void* d_base, const Piece* pieces, int n) {
     return r;
   };
   for (int i = 0; i < n && e == hipSuccess; ++i) {
+    const Piece& q = pieces[i];
+    if (q.direct) {
+      e = hipMemcpyAsync((char*)d_base + q.off, q.host, q.bytes, hipMemcpyHostToDevice,
+                         ctx->stream);
+      continue;
+    }
     size_t done = 0;
-    while (done < pieces[i].bytes && e == hipSuccess) {
-      const size_t off = pieces[i].off + done;
-      if (fill > 0 && (off != start + fill || fill == kPinHalf)) e = flush();
+    while (done < q.bytes && e == hipSuccess) {
+      const size_t off = q.off + done;
+      if (fill > 0 && (off != start + fill || fill == kPinHalf)) e = flush(false);
       if (e != hipSuccess) break;
       if (fill == 0) start = off;
-      const size_t left = pieces[i].bytes - done, room = kPinHalf - fill;
+      const size_t left = q.bytes - done, room = kPinHalf - fill;
       const size_t take = left < room ? left : room;
-      memcpy(ctx->h_pin + half * kPinHalf + fill, (const char*)pieces[i].host + done, take);
+      memcpy(ctx->h_pin + half * kPinHalf + fill, (const char*)q.host + done, take);
       fill += take;
       done += take;
     }
   }
-  if (e == hipSuccess) e = flush();
+  if (e == hipSuccess) e = flush(true);
+  if (!ctx->h_pin) {  // pageable arrays: the caller may reuse them now
+    const hipError_t w = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess) e = w;
+  }
   return e;
 }
 
-hipError_t copy_out(wl_ctx* ctx, const void* d_base, const Piece* pieces, int n) {
-  size_t lo = SIZE_MAX, hi = 0;
-  for (int i = 0; i < n; ++i)
-    if (pieces[i].host && pieces[i].bytes) {
-      if (pieces[i].off < lo) lo = pieces[i].off;
-      if (pieces[i].off + pieces[i].bytes > hi) hi = pieces[i].off + pieces[i].bytes;
+// The staged pieces of a copy_out as chunks of at most a half, from one piece's
+// start or the last chunk's end: pieces whose gap is small share a chunk.
+namespace {
+struct Chunk {
+  size_t a, b;  // device offsets; empty: none left
+};
+struct Chunks {
+  const Piece* pieces;
+  int n;
+  int at = 0;       // the next piece,
+  size_t done = 0;  // its bytes in earlier chunks
+  static bool skip(const Piece& q) { return !q.host || !q.bytes || q.direct; }
+  Chunk next() {
+    Chunk c{0, 0};
+    for (; at < n; ++at, done = 0) {
+      const Piece& q = pieces[at];
+      if (skip(q)) continue;
+      const size_t from = q.off + done;
+      if (c.a == c.b) c.a = c.b = from;
+      const size_t room = c.a + kPinHalf;
+      if (from > c.b + kPinGap || from >= room) break;
+      const size_t left = q.bytes - done, fit = room - from;
+      c.b = from + (left < fit ? left : fit);
+      if (left > fit) {
+        done += fit;
+        break;
+      }
     }
-  if (hi == 0) {
-    const hipError_t w = hipStreamSynchronize(ctx->stream);
-    if (w == hipSuccess) ctx->pin_busy = false;
-    return w;
+    return c;
   }
-  if (!pin_make(ctx)) {
-    const hipError_t r =
-        copy_direct(ctx, (char*)d_base, pieces, n, hipMemcpyDeviceToHost);
-    const hipError_t w = hipStreamSynchronize(ctx->stream);
-    return r == hipSuccess ? w : r;
-  }
-  // (copy_in's copies are ahead on the same stream: their half may be reused)
-  ctx->pin_busy = true;
-  auto ask = [&](size_t c) {  // chunk c of [lo, hi) into its half
-    const size_t a = lo + c * kPinHalf, b = a + kPinHalf < hi ? a + kPinHalf : hi;
-    hipError_t r = hipMemcpyAsync(ctx->h_pin + (c & 1) * kPinHalf, (const char*)d_base + a,
-                                  b - a, hipMemcpyDeviceToHost, ctx->stream);
-    if (r == hipSuccess) r = hipEventRecord(ctx->pin_ev[c & 1], ctx->stream);
-    return r;
-  };
-  const size_t chunks = (hi - lo + kPinHalf - 1) / kPinHalf;
-  hipError_t e = ask(0);
-  int first = 0;  // pieces before it are complete
-  for (size_t c = 0; c < chunks && e == hipSuccess; ++c) {
-    if (c + 1 < chunks) e = ask(c + 1);
-    if (e == hipSuccess) e = hipEventSynchronize(ctx->pin_ev[c & 1]);
-    if (e != hipSuccess) break;
-    const size_t a = lo + c * kPinHalf, b = a + kPinHalf < hi ? a + kPinHalf : hi;
-    for (int i = first; i < n; ++i) {
-      const Piece& q = pieces[i];
-      if (q.off >= b) break;
-      if (q.off + q.bytes <= b && i == first) ++first;
-      if (!q.host || q.off + q.bytes <= a) continue;
-      const size_t from = q.off > a ? q.off : a;
-      const size_t to = q.off + q.bytes < b ? q.off + q.bytes : b;
-      memcpy((char*)q.host + (from - q.off), ctx->h_pin + (c & 1) * kPinHalf + (from - a),
-             to - from);
+};
+}  // namespace
+
+hipError_t copy_out(wl_ctx* ctx, const void* d_base, Piece* pieces, int n) {
+  hipError_t e = hipSuccess;
+  const bool staged = mark_direct(ctx, pieces, n);
+  for (int i = 0; i < n && e == hipSuccess; ++i)
+    if (pieces[i].direct)
+      e = hipMemcpyAsync(pieces[i].host, (const char*)d_base + pieces[i].off, pieces[i].bytes,
+                         hipMemcpyDeviceToHost, ctx->stream);
+  if (staged && e == hipSuccess) {
+    // (copy_in's copies are ahead on the same stream: their half may be reused)
+    ctx->pin_busy = true;
+    auto ask = [&](const Chunk& c, int half) {
+      return hipMemcpyAsync(ctx->h_pin + half * kPinHalf, (const char*)d_base + c.a, c.b - c.a,
+                            hipMemcpyDeviceToHost, ctx->stream);
+    };
+    Chunks rest{pieces, n};
+    Chunk c = rest.next();
+    e = ask(c, 0);
+    int first = 0;  // pieces before it are complete
+    for (int half = 0; c.b > c.a && e == hipSuccess; half ^= 1) {
+      const Chunk more = rest.next();
+      if (more.b > more.a) {
+        e = hipEventRecord(ctx->pin_ev[half], ctx->stream);
+        if (e == hipSuccess) e = ask(more, half ^ 1);
+        if (e == hipSuccess) e = hipEventSynchronize(ctx->pin_ev[half]);
+      } else {
+        e = hipStreamSynchronize(ctx->stream);
+      }
+      if (e != hipSuccess) break;
+      for (int i = first; i < n; ++i) {
+        const Piece& q = pieces[i];
+        if (q.off >= c.b) break;
+        if (q.off + q.bytes <= c.b && i == first) ++first;
+        if (Chunks::skip(q) || q.off + q.bytes <= c.a) continue;
+        const size_t from = q.off > c.a ? q.off : c.a;
+        const size_t to = q.off + q.bytes < c.b ? q.off + q.bytes : c.b;
+        memcpy((char*)q.host + (from - q.off), ctx->h_pin + half * kPinHalf + (from - c.a),
+               to - from);
+      }
+      c = more;
     }
+  } else {
+    const hipError_t w = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess) e = w;
   }
   if (e == hipSuccess) ctx->pin_busy = false;
   return e;
@@ -1077,7 +1123,7 @@ static int average_device(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& f
 static hipError_t grids_in(wl_ctx* ctx, double* d_rho, const double* rho, int32_t n_rho,
                            const double* T, int32_t n_T) {
   const size_t rb = n_rho * sizeof(double);
-  const Piece p[] = {{(void*)rho, 0, rb}, {(void*)T, rb, n_T * sizeof(double)}};
+  Piece p[] = {{(void*)rho, 0, rb}, {(void*)T, rb, n_T * sizeof(double)}};
   return copy_in(ctx, d_rho, p, 2);
 }
 
@@ -1135,7 +1181,7 @@ static int average_impl(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
     return rc;
   auto off = [&](const void* p) { return (size_t)((const char*)p - (const char*)ctx->d_out); };
   const size_t pt = n_pts * sizeof(double);
-  const Piece pieces[] = {{out->group_sums, off(o.sums), sums_n * sizeof(double)},
+  Piece pieces[] = {{out->group_sums, off(o.sums), sums_n * sizeof(double)},
                           {out->mean, off(o.mean), pt},
                           {out->err, off(o.err), pt},
                           {out->scale, off(o.scale), pt},
@@ -1229,7 +1275,7 @@ int wl_average_batch(wl_ctx* ctx, const wl_ens* ens, const wl_request* reqs,
     if (!build_batch(ens, rq.data(), rf.data(), pl.data(), (int32_t)rq.size(), h_in.data(),
                      in_b, d_in, d_res, res_b, &lay))
       return fail(ctx, WL_EINVAL, "internal: batch layout exceeds its buffer");
-    const Piece in{h_in.data(), 0, lay.in_bytes};
+    Piece in{h_in.data(), 0, lay.in_bytes};
     hipError_t e = copy_in(ctx, d_in, &in, 1);
     if (e == hipSuccess)
       e = wl::launch_batch(prec, ens->d_seg, ens->d_seg64, ens->d_norm, ens->d_x, ens->d_y,
@@ -1395,7 +1441,7 @@ static int per_loop_impl(wl_ctx* ctx, const wl_ens* ens, const wl::FieldArgs& fa
                             d_rho, d_T, n_T, (int32_t)n_pts, loop0, n_loops, d_ph, d_sp, d_w,
                             ctx->stream);
   const size_t eb = each * sizeof(double);
-  const Piece pieces[] = {{phase, 0, eb}, {spin_exp, eb, eb}, {w, 2 * eb, eb}};
+  Piece pieces[] = {{phase, 0, eb}, {spin_exp, eb, eb}, {w, 2 * eb, eb}};
   if (e == hipSuccess) e = copy_out(ctx, d_ph, pieces, 3);
   if (e != hipSuccess) return hip_fail(ctx, e, "per-loop evaluation");
   return WL_OK;
@@ -1461,7 +1507,7 @@ int wl_discretisation(wl_ctx* ctx, const wl_ens* ens, const wl_field* field,
     e = wl::launch_disc_finish(level_out, d_sums, (int32_t)G, s.n_sub, (int32_t)n_pts,
                                ens->n_loops, d_mean, d_err, d_delta, ctx->stream);
   const size_t sb = sums_n * sizeof(double), pb = n_pts * sizeof(double);
-  const Piece pieces[] = {{group_sums, 0, sb},
+  Piece pieces[] = {{group_sums, 0, sb},
                           {mean, sb, 4 * pb},
                           {err, sb + 4 * pb, 4 * pb},
                           {delta, sb + 8 * pb, pb}};

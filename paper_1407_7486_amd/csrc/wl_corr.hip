@@ -304,7 +304,7 @@ int wl_correlation(wl_ctx* ctx, const double* values, int64_t n_units, int32_t n
   double* d_mu = d_mp + (int64_t)mean_rows * n_pts;
   hipError_t e = hipSuccess;
   if (flags == WL_HOST_PTR) {
-    const Piece in{(void*)values, 0, vals_n * sizeof(double)};
+    Piece in{(void*)values, 0, vals_n * sizeof(double)};
     e = copy_in(ctx, d_x, &in, 1);
   }
   if (e == hipSuccess) {
@@ -337,7 +337,7 @@ int wl_correlation(wl_ctx* ctx, const double* values, int64_t n_units, int32_t n
                        d_part, (int32_t)n_split, n_pts, d_out);
     e = hipGetLastError();
   }
-  const Piece out{flags == WL_HOST_PTR ? corr : nullptr, 0, sz * sizeof(double)};
+  Piece out{flags == WL_HOST_PTR ? corr : nullptr, 0, sz * sizeof(double)};
   if (e == hipSuccess) e = copy_out(ctx, d_out, &out, 1);
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_correlation");
   return WL_OK;
@@ -394,7 +394,7 @@ int wl_regroup(wl_ctx* ctx, const double* per_unit, int64_t n_units, int32_t n_p
   int* d_bad = (int*)(d_out + sn);
   hipError_t e = hipSuccess;
   if (host) {
-    const Piece in[] = {{(void*)per_unit, 0, xn * sizeof(double)},
+    Piece in[] = {{(void*)per_unit, 0, xn * sizeof(double)},
                         {(void*)perms, xn * sizeof(double), pn * sizeof(int64_t)},
                         {(void*)point_perm, (xn + pn) * sizeof(double), qn * sizeof(int32_t)}};
     e = copy_in(ctx, buf, in, point_perm ? 3 : 2);
@@ -408,7 +408,7 @@ int wl_regroup(wl_ctx* ctx, const double* per_unit, int64_t n_units, int32_t n_p
     e = hipGetLastError();
   }
   int bad = 0;
-  const Piece out[] = {{host ? sums : nullptr, 0, sn * sizeof(double)},
+  Piece out[] = {{host ? sums : nullptr, 0, sn * sizeof(double)},
                        {&bad, sn * sizeof(double), sizeof(int)}};
   if (e == hipSuccess) e = copy_out(ctx, d_out, out, 2);
   if (e != hipSuccess) return hip_fail(ctx, e, "wl_regroup");

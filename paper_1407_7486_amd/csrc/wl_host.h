@@ -106,23 +106,25 @@ struct Work {
   Work& operator=(const Work&) = delete;
 };
 
-// Host arrays to and from device memory through the context's pinned staging
-// (a pageable copy goes through the runtime's own, piece by piece and each
-// with a wait; so these go too where the staging cannot be had).  A piece is
-// [host, host + bytes) <-> device offset `off`.
+// Host arrays to and from device memory through the context's pinned staging,
+// or directly (mark_direct).  A piece is [host, host + bytes) <-> device offset
+// `off`.
 struct Piece {
   void* host;
   size_t off, bytes;
+  bool direct = false;  // set by the copies
 };
 constexpr size_t kPinHalf = (size_t)8 << 20;
-// Enqueues the copies of the pieces to d_base + off on the ctx stream; the
-// host arrays may be reused on return.
-hipError_t copy_in(wl_ctx* ctx, void* d_base, const Piece* pieces, int n);
+// From these sizes on a pinned array is copied directly, and the bytes between
+// two pieces are left out.
+constexpr size_t kPinDirect = (size_t)64 << 10, kPinGap = (size_t)64 << 10;
+// Enqueues the copies of the pieces to d_base + off on the ctx stream; pageable
+// arrays may be reused on return, pinned ones once the stream has got there.
+hipError_t copy_in(wl_ctx* ctx, void* d_base, Piece* pieces, int n);
 // Copies d_base + off to the pieces after the work enqueued on the ctx stream
 // and waits for it: on return everything enqueued is complete.  The pieces'
-// offsets ascend (bytes between them are copied along); empty ones (host
-// NULL or no bytes) are skipped.
-hipError_t copy_out(wl_ctx* ctx, const void* d_base, const Piece* pieces, int n);
+// offsets ascend; empty ones (host NULL or no bytes) are skipped.
+hipError_t copy_out(wl_ctx* ctx, const void* d_base, Piece* pieces, int n);
 
 // Event pair for the next timed launch of ctx (pooled; created on first use).
 hipError_t next_events(wl_ctx* ctx, hipEvent_t* a, hipEvent_t* b);

@@ -21,6 +21,7 @@ std::map<char*, size_t> device, pinned;  // live allocations
 std::map<const void*, std::string> kernels;
 std::map<std::string, int> fail_at;  // call -> calls left before it fails
 size_t limit = (size_t)288 << 30, used = 0;
+bool fill = false;             // fresh device memory holds the doubles 0, 1, 2, ...
 bool foreign_work = false;     // unfinished work on a stream that is not the library's
 bool foreign_capture = false;  // such a stream is being captured (global mode)
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
@@ -52,6 +53,7 @@ void fake_reset() { std::lock_guard<std::recursive_mutex> l(mu); log_.clear(); }
 const char* fake_log() { return log_.c_str(); }
 void fake_limit(size_t bytes) { limit = bytes; }
 size_t fake_used() { return used; }
+void fake_fill(int on) { fill = on; }
 void fake_fail(const char* call, int after) { fail_at[call] = after; }
 void fake_foreign_work(int on) { foreign_work = on; }
 int fake_foreign_work_left() { return foreign_work; }
@@ -88,6 +90,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (unsafe_now()) return rc(hipErrorStreamCaptureUnsupported);
   if (fails("malloc") || used + n > limit) return rc(hipErrorOutOfMemory);
   *p = calloc(n ? n : 1, 1);
+  for (size_t i = 0; fill && i < n / 8; ++i) ((double*)*p)[i] = (double)i;
   device[(char*)*p] = n;
   used += n;
   return hipSuccess;
