@@ -193,7 +193,8 @@ hipError_t copy_in(wl_ctx* ctx, void* d_base, Piece* pieces, int n) {
 // start or the last chunk's end: pieces whose gap is small share a chunk.
 namespace {
 struct Chunk {
-  size_t a, b;  // device offsets; empty: none left
+  size_t a, b;  // device offsets
+  bool none() const { return a == b; }
 };
 struct Chunks {
   const Piece* pieces;
@@ -232,22 +233,25 @@ hipError_t copy_out(wl_ctx* ctx, const void* d_base, Piece* pieces, int n) {
   if (staged && e == hipSuccess) {
     // (copy_in's copies are ahead on the same stream: their half may be reused)
     ctx->pin_busy = true;
-    auto ask = [&](const Chunk& c, int half) {
-      return hipMemcpyAsync(ctx->h_pin + half * kPinHalf, (const char*)d_base + c.a, c.b - c.a,
-                            hipMemcpyDeviceToHost, ctx->stream);
+    // a chunk into its half; its event at once unless it is the last (recorded
+    // when it is waited for, it is 15 us late)
+    auto ask = [&](const Chunk& c, int half, bool last) {
+      hipError_t r = hipMemcpyAsync(ctx->h_pin + half * kPinHalf, (const char*)d_base + c.a,
+                                    c.b - c.a, hipMemcpyDeviceToHost, ctx->stream);
+      if (r == hipSuccess && !last) r = hipEventRecord(ctx->pin_ev[half], ctx->stream);
+      return r;
     };
     Chunks rest{pieces, n};
-    Chunk c = rest.next();
-    e = ask(c, 0);
+    Chunk c = rest.next(), more = rest.next();
+    e = ask(c, 0, more.none());
     int first = 0;  // pieces before it are complete
-    for (int half = 0; c.b > c.a && e == hipSuccess; half ^= 1) {
-      const Chunk more = rest.next();
-      if (more.b > more.a) {
-        e = hipEventRecord(ctx->pin_ev[half], ctx->stream);
-        if (e == hipSuccess) e = ask(more, half ^ 1);
-        if (e == hipSuccess) e = hipEventSynchronize(ctx->pin_ev[half]);
-      } else {
+    for (int half = 0; !c.none() && e == hipSuccess; half ^= 1) {
+      const Chunk after = rest.next();
+      if (more.none()) {
         e = hipStreamSynchronize(ctx->stream);
+      } else {
+        e = ask(more, half ^ 1, after.none());
+        if (e == hipSuccess) e = hipEventSynchronize(ctx->pin_ev[half]);
       }
       if (e != hipSuccess) break;
       for (int i = first; i < n; ++i) {
@@ -261,6 +265,7 @@ hipError_t copy_out(wl_ctx* ctx, const void* d_base, Piece* pieces, int n) {
                to - from);
       }
       c = more;
+      more = after;
     }
   } else {
     const hipError_t w = hipStreamSynchronize(ctx->stream);
