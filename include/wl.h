@@ -111,7 +111,12 @@ typedef struct wl_ens wl_ens;
 int wl_create(wl_ctx** out, int device, void* hip_stream);
 
 /* Free the context and its scratch buffers (ensembles are freed with
- * wl_ensemble_free).  NULL is allowed. */
+ * wl_ensemble_free).  NULL is allowed.  Until then the context holds, from
+ * their first use on: the grids, results and item sums of its largest
+ * evaluations, up to 1 GiB for wl_correlation, wl_regroup and wl_action
+ * (given back before an allocation of the library on that device fails),
+ * up to 43 MB for the loops' terms of small evaluations, and 16 MiB of pinned
+ * host memory. */
 int wl_destroy(wl_ctx* ctx);
 
 /* Message of the last failing call on ctx ("" if none).  The pointer stays
@@ -161,10 +166,11 @@ int wl_ensemble_download(const wl_ens* ens, float* y_x, float* y_y, int64_t loop
                          int64_t n_loops);
 
 /* Free an ensemble (NULL allowed).  Must be called before wl_destroy of the
- * context that created it.  The context keeps the device memory of freed
- * ensembles (points and FP32 segments, at most 8 GiB in all) for the next
- * ones; it goes back with wl_destroy, and before an allocation of the
- * library fails. */
+ * context that created it.  Waits for all work on the device.  The context
+ * keeps the device memory of freed ensembles (points and FP32 segments, at
+ * most 8 GiB in all and, beyond 64 MiB, a quarter of the memory that is still
+ * free on the device) for the next ones; it goes back with wl_destroy, and before an
+ * allocation of the library on that device fails. */
 int wl_ensemble_free(wl_ens* ens);
 
 /* Shape of an uploaded ensemble (any output pointer may be NULL). */

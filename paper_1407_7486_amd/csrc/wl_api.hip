@@ -31,15 +31,39 @@ int hip_fail(wl_ctx* ctx, hipError_t e, const char* what) {
   return fail(ctx, WL_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+// The live contexts, whose idle device memory serves any of them.
+struct Contexts {
+  std::mutex mu;
+  std::vector<wl_ctx*> live;
+};
+static Contexts& contexts() {
+  static Contexts* c = new Contexts;  // outlives every static destructor
+  return *c;
+}
+
+// Gives back what the contexts of a device hold without using it: the blocks of
+// freed ensembles and the scratch that no call is working with.
+static void give_back(int device) {
+  Contexts& all = contexts();
+  std::lock_guard<std::mutex> lock(all.mu);
+  for (wl_ctx* c : all.live) {
+    if (c->device != device) continue;
+    std::lock_guard<std::mutex> idle(c->cache_mu);
+    for (const auto& b : c->ens_cache) (void)hipFree(b.first);
+    c->ens_cache.clear();
+    if (c->d_work && !c->work_busy) {
+      (void)hipFree(c->d_work);
+      c->d_work = nullptr;
+      c->work_bytes = 0;
+    }
+  }
+}
+
 hipError_t dev_malloc(wl_ctx* ctx, void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
   if (e == hipSuccess) return e;
   (void)hipGetLastError();
-  {
-    std::lock_guard<std::mutex> lock(ctx->cache_mu);
-    for (const auto& b : ctx->ens_cache) (void)hipFree(b.first);
-    ctx->ens_cache.clear();
-  }
+  give_back(ctx->device);
   e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     *p = nullptr;
@@ -66,6 +90,11 @@ static int ensure(wl_ctx* ctx, void** p, size_t* have, size_t need, const char* 
 
 Work::Work(wl_ctx* ctx, size_t bytes, const char* what) {
   if (bytes <= kWorkKeep) {
+    {
+      std::lock_guard<std::mutex> lock(ctx->cache_mu);
+      ctx->work_busy = true;
+    }
+    holder = ctx;
     if (ensure(ctx, &ctx->d_work, &ctx->work_bytes, bytes, what) == WL_OK) p = ctx->d_work;
     return;
   }
@@ -78,6 +107,10 @@ Work::Work(wl_ctx* ctx, size_t bytes, const char* what) {
 
 Work::~Work() {
   if (temporary && p) (void)hipFree(p);
+  if (holder) {
+    std::lock_guard<std::mutex> lock(holder->cache_mu);
+    holder->work_busy = false;
+  }
 }
 
 // While it lives, this thread's allocations do not end the capture of another
@@ -284,36 +317,53 @@ constexpr size_t kEnsCacheBytes = (size_t)8 << 30;
 static void* ens_block(wl_ctx* ctx, size_t bytes, size_t* got) {
   {
     std::lock_guard<std::mutex> lock(ctx->cache_mu);
-    for (size_t i = 0; i < ctx->ens_cache.size(); ++i) {
-      const auto b = ctx->ens_cache[i];
-      if (b.second >= bytes && b.second - bytes <= b.second / 4) {
-        ctx->ens_cache.erase(ctx->ens_cache.begin() + i);
-        *got = b.second;
-        return b.first;
-      }
+    auto best = ctx->ens_cache.end();  // the smallest that fits
+    for (auto b = ctx->ens_cache.begin(); b != ctx->ens_cache.end(); ++b)
+      if (b->second >= bytes && b->second - bytes <= b->second / 4 &&
+          (best == ctx->ens_cache.end() || b->second < best->second))
+        best = b;
+    if (best != ctx->ens_cache.end()) {
+      void* p = best->first;
+      *got = best->second;
+      ctx->ens_cache.erase(best);
+      return p;
     }
   }
   void* p = nullptr;
   *got = bytes;
   return dev_malloc(ctx, &p, bytes) == hipSuccess ? p : nullptr;
 }
-// Takes back a block (the caller has waited for the device): the oldest kept
-// ones go when it takes them over the bound.
+// Takes back a block (the caller has waited for the device).  Kept are at most
+// kEnsCacheBytes and, since other allocators of the process do not see them, a
+// quarter of the memory that is free beside them (asked for beyond 64 MiB only:
+// it takes 10 us); the oldest go first.
 static void ens_block_free(wl_ctx* ctx, void* p, size_t bytes) {
   if (!p) return;
-  if (bytes > kEnsCacheBytes) {
-    (void)hipFree(p);
-    return;
-  }
   std::lock_guard<std::mutex> lock(ctx->cache_mu);
-  size_t held = bytes;
+  size_t held = bytes, most = kEnsCacheBytes;
   for (const auto& b : ctx->ens_cache) held += b.second;
-  while (held > kEnsCacheBytes) {
-    held -= ctx->ens_cache.front().second;
-    (void)hipFree(ctx->ens_cache.front().first);
-    ctx->ens_cache.erase(ctx->ens_cache.begin());
+  if (held > (size_t)64 << 20) {
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+      (void)hipGetLastError();
+      avail = 0;
+    }
+    if (avail / 4 < most) most = avail / 4;
   }
-  ctx->ens_cache.emplace_back(p, bytes);
+  size_t drop = 0;  // kept blocks that go
+  for (; drop < ctx->ens_cache.size() && held > most; ++drop) {
+    held -= ctx->ens_cache[drop].second;
+    (void)hipFree(ctx->ens_cache[drop].first);
+  }
+  ctx->ens_cache.erase(ctx->ens_cache.begin(), ctx->ens_cache.begin() + drop);
+  try {
+    if (held <= most) {
+      ctx->ens_cache.emplace_back(p, bytes);
+      return;
+    }
+  } catch (const std::bad_alloc&) {
+  }
+  (void)hipFree(p);
 }
 // The arrays of an ensemble of the given shape, in one block.
 static bool ens_alloc(wl_ctx* ctx, wl_ens* e) {
@@ -721,8 +771,16 @@ int wl_create(wl_ctx** out, int device, void* hip_stream) {
   c->stream = (hipStream_t)hip_stream;
   c->num_cu = prop.multiProcessorCount;
   DeviceGuard g(device);
-  if (g.status != hipSuccess || hipMalloc((void**)&c->d_flag, sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&c->d_counter, kBatchCounters * sizeof(unsigned int)) != hipSuccess) {
+  if (g.status != hipSuccess || dev_malloc(c, (void**)&c->d_flag, sizeof(int)) != hipSuccess ||
+      dev_malloc(c, (void**)&c->d_counter, kBatchCounters * sizeof(unsigned int)) !=
+          hipSuccess) {
+    wl_destroy(c);
+    return WL_ENOMEM;
+  }
+  try {
+    std::lock_guard<std::mutex> lock(contexts().mu);
+    contexts().live.push_back(c);
+  } catch (const std::bad_alloc&) {
     wl_destroy(c);
     return WL_ENOMEM;
   }
@@ -736,6 +794,15 @@ int wl_create(wl_ctx** out, int device, void* hip_stream) {
 
 int wl_destroy(wl_ctx* ctx) {
   if (!ctx) return WL_OK;
+  {
+    Contexts& all = contexts();
+    std::lock_guard<std::mutex> lock(all.mu);
+    for (size_t i = 0; i < all.live.size(); ++i)
+      if (all.live[i] == ctx) {
+        all.live.erase(all.live.begin() + i);
+        break;
+      }
+  }
   {
     DeviceGuard g(ctx->device);
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);

@@ -32,14 +32,15 @@ struct wl_ctx {
   void* d_terms[2] = {};  // loops' terms of small launches (walk_terms)
   void* d_work = nullptr;  // scratch of the correlation, regroup and action calls
   size_t work_bytes = 0;
+  bool work_busy = false;  // a call is working with it (guarded by cache_mu)
   // pinned staging of host arrays (two halves of kPinHalf; see copy_in,
   // copy_out); `pin_busy` while copies from or to it may be in flight
   char* h_pin = nullptr;
   hipEvent_t pin_ev[2] = {nullptr, nullptr};
   bool pin_busy = false;
-  // device blocks of freed ensembles kept for the next ones, at most
-  // kEnsCacheBytes in all; given back by wl_destroy and when an allocation
-  // fails (also one of a server's thread, hence the lock)
+  // device blocks of freed ensembles kept for the next ones (ens_block_free);
+  // given back, as is d_work, by wl_destroy and when an allocation of any
+  // context on the device fails (also one of a server's thread, hence the lock)
   std::vector<std::pair<void*, size_t>> ens_cache;
   std::mutex cache_mu;
   // device address of the allocation-free entry point's static scratch
@@ -89,8 +90,8 @@ Sched make_sched(const wl_ctx* ctx, const wl_ens* e, int32_t n_pts);
 // FP64 segment array of an ensemble, built on first use on `stream`
 // (thread-safe; hipErrorOutOfMemory when the allocation fails).
 hipError_t ensure_seg64(const wl_ens* ens, hipStream_t stream);
-// hipMalloc that gives the context's kept ensemble blocks back and tries again
-// before it fails.
+// hipMalloc that has the device's contexts give back what they hold unused and
+// tries again before it fails.
 hipError_t dev_malloc(wl_ctx* ctx, void** p, size_t bytes);
 
 // Device scratch of one call: the context's kept buffer (grown on demand) up
@@ -100,6 +101,7 @@ constexpr size_t kWorkKeep = (size_t)1 << 30;
 struct Work {
   void* p = nullptr;
   bool temporary = false;
+  wl_ctx* holder = nullptr;  // of the kept buffer
   Work(wl_ctx* ctx, size_t bytes, const char* what);
   ~Work();
   Work(const Work&) = delete;

@@ -308,7 +308,8 @@ int wl_server_create(wl_ctx* ctx, const wl_ens* ens, const wl_server_config* cfg
     if (e == hipSuccess) e = wl::dev_malloc(ctx, &sl->d_in, c.input_bytes);
     if (e == hipSuccess) e = wl::dev_malloc(ctx, &sl->d_res, c.result_bytes);
     if (e == hipSuccess)
-      e = hipMalloc((void**)&sl->d_counter, wl::kBatchCounters * sizeof(unsigned int));
+      e = wl::dev_malloc(ctx, (void**)&sl->d_counter,
+                         wl::kBatchCounters * sizeof(unsigned int));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl->ev_done, hipEventDisableTiming);
     s->slots.push_back(std::move(sl));
     if (e != hipSuccess) {
