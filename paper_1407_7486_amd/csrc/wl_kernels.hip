@@ -280,8 +280,8 @@ __device__ __forceinline__ double exp2_neg64(double& t, const Tables64& tab) {
   return fma(T, f * horner_sv_f64<WL_EXP2M1_F64_DEG>(WL_EXP2M1_F64, f), T);
 }
 
-// 1 - log2(1 + E) for E < 1/2, opE = 1 + E rounded: the interval of width
-// 1/256 from the top mantissa bits of opE, c its middle's reciprocal,
+// 1 - log2(1 + E) for E < 0.37 (opE = 1 + E rounded has to stay below 3/2): the
+// interval of width 1/256 from the top mantissa bits of opE, c its middle's reciprocal,
 // log2(1 + E) = log2(1 + r) - log2 c with r = E c + (c - 1) (rounded once,
 // c - 1 is exact), |r| <= 1/511, and log2(1 + r) = r Q(r), Q of degree 4.
 __device__ __forceinline__ double one_minus_log2_1p(double E, double opE,
@@ -2320,9 +2320,8 @@ hipError_t launch_esc_t(const FieldArgs& f, const float* x, const float* y, int3
                         const double* rho, const double* T, int32_t n_T, int32_t n_pts,
                         const Sched& s, const int32_t* list, const int32_t* count,
                         const double* pv, const double* scale, double* out, hipStream_t st) {
-  // at most n_pts points flagged: enough workgroups for the largest count
-  // (the evaluation's n_items items), up to 4096 (16384 waves, 4 per SIMD on
-  // 1024 SIMDs four times over)
+  // a workgroup per item of the evaluation, up to 4096; the smaller chunks of a
+  // small count can make up to 8 times as many items, taken in turn
   int64_t n_wg = s.n_items;
   if (n_wg > 4096) n_wg = 4096;
   hipLaunchKernelGGL((k_escalate<KIND, SPIN>), dim3((uint32_t)n_wg), dim3(kWavesPerWG * kWave),
