@@ -266,26 +266,30 @@ hipError_t copy_out(wl_ctx* ctx, const void* d_base, Piece* pieces, int n) {
   if (staged && e == hipSuccess) {
     // (copy_in's copies are ahead on the same stream: their half may be reused)
     ctx->pin_busy = true;
-    // a chunk into its half; its event at once unless it is the last (recorded
-    // when it is waited for, it is 15 us late)
-    auto ask = [&](const Chunk& c, int half, bool last) {
+    // A chunk into its half; its event at once (recorded when it is waited for,
+    // it is 15 us late).
+    auto ask = [&](const Chunk& c, int half, bool event) {
       hipError_t r = hipMemcpyAsync(ctx->h_pin + half * kPinHalf, (const char*)d_base + c.a,
                                     c.b - c.a, hipMemcpyDeviceToHost, ctx->stream);
-      if (r == hipSuccess && !last) r = hipEventRecord(ctx->pin_ev[half], ctx->stream);
+      if (r == hipSuccess && event) r = hipEventRecord(ctx->pin_ev[half], ctx->stream);
       return r;
     };
     Chunks rest{pieces, n};
     Chunk c = rest.next(), more = rest.next();
-    e = ask(c, 0, more.none());
+    // A lone chunk of more than 16 KiB is waited for with the stream: such a copy
+    // runs on a DMA engine, whose event comes 7 us after it (an 18 KiB result 77.1
+    // us, with the stream 70.1); a smaller one runs as a kernel, and the stream's
+    // wait is then late by up to 25 us (0.2 KiB of 256 x 512 loops 66.6 us, with
+    // the event 40.6; 13.5 KiB 63.6 both).
+    const bool by_stream = more.none() && c.b - c.a > kPinEvent;
+    e = ask(c, 0, !by_stream);
     int first = 0;  // pieces before it are complete
     for (int half = 0; !c.none() && e == hipSuccess; half ^= 1) {
       const Chunk after = rest.next();
-      if (more.none()) {
-        e = hipStreamSynchronize(ctx->stream);
-      } else {
-        e = ask(more, half ^ 1, after.none());
-        if (e == hipSuccess) e = hipEventSynchronize(ctx->pin_ev[half]);
-      }
+      if (!more.none()) e = ask(more, half ^ 1, true);
+      if (e == hipSuccess)
+        e = by_stream ? hipStreamSynchronize(ctx->stream)
+                      : hipEventSynchronize(ctx->pin_ev[half]);
       if (e != hipSuccess) break;
       for (int i = first; i < n; ++i) {
         const Piece& q = pieces[i];

@@ -118,8 +118,10 @@ struct Piece {
 };
 constexpr size_t kPinHalf = (size_t)8 << 20;
 // From these sizes on a pinned array is copied directly, and the bytes between
-// two pieces are left out.
-constexpr size_t kPinDirect = (size_t)64 << 10, kPinGap = (size_t)64 << 10;
+// two pieces are left out (a copy of its own costs 8 us, 256 KiB more 5).
+constexpr size_t kPinDirect = (size_t)64 << 10, kPinGap = (size_t)256 << 10;
+// Up to this size a lone copy out is waited for with an event.
+constexpr size_t kPinEvent = (size_t)16 << 10;
 // Enqueues the copies of the pieces to d_base + off on the ctx stream; pageable
 // arrays may be reused on return, pinned ones once the stream has got there.
 hipError_t copy_in(wl_ctx* ctx, void* d_base, Piece* pieces, int n);

@@ -54,7 +54,7 @@ def copied():
 def test_outputs_are_whole_and_nothing_else_is_copied(side):
     """Arrays of 4 KiB to 16 MiB each, pageable, pinned and mixed, with any of
     the three left out: the same values, and of the bytes that were not asked
-    for at most a gap of 64 KiB."""
+    for at most a gap of 256 KiB."""
     fake_hip.run(PER_LOOP + """
 import itertools
 side = %d
@@ -68,7 +68,7 @@ for kinds in itertools.product((0, 1, 2), repeat=3):  # none, pageable, pinned
     for a, b in zip(out, full):
         assert a is None or np.array_equal(a, b), kinds
     asked = 8 * n * sum(k > 0 for k in kinds)
-    assert asked <= sum(copied()) <= asked + (2 << 16), (kinds, copied())
+    assert asked <= sum(copied()) <= asked + (1 << 18), (kinds, copied())
     big = sum(k == 2 for k in kinds) if 8 * n >= 1 << 16 else 0
     # a pinned array of 64 KiB or more travels in one copy, however large
     assert copied()[:big] == [8 * n] * big, (kinds, copied())
