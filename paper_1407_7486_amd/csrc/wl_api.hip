@@ -339,14 +339,17 @@ static void* ens_block(wl_ctx* ctx, size_t bytes, size_t* got) {
 }
 // Takes back a block (the caller has waited for the device).  Kept are at most
 // kEnsCacheBytes and, since other allocators of the process do not see them, a
-// quarter of the memory that is free beside them (asked for beyond 64 MiB only:
-// it takes 10 us); the oldest go first.
+// quarter of the memory that is free beside them (asked for, which takes 10 us,
+// for larger blocks and whenever 64 MiB have come together since); the oldest
+// go first.
 static void ens_block_free(wl_ctx* ctx, void* p, size_t bytes) {
   if (!p) return;
   std::lock_guard<std::mutex> lock(ctx->cache_mu);
+  constexpr size_t kAsk = (size_t)64 << 20;
   size_t held = bytes, most = kEnsCacheBytes;
   for (const auto& b : ctx->ens_cache) held += b.second;
-  if (held > (size_t)64 << 20) {
+  const bool ask = bytes > kAsk || held > ctx->cache_asked + kAsk;
+  if (ask) {
     size_t avail = 0, total = 0;
     if (hipMemGetInfo(&avail, &total) != hipSuccess) {
       (void)hipGetLastError();
@@ -360,6 +363,7 @@ static void ens_block_free(wl_ctx* ctx, void* p, size_t bytes) {
     (void)hipFree(ctx->ens_cache[drop].first);
   }
   ctx->ens_cache.erase(ctx->ens_cache.begin(), ctx->ens_cache.begin() + drop);
+  if (ask) ctx->cache_asked = held <= most ? held : held - bytes;
   try {
     if (held <= most) {
       ctx->ens_cache.emplace_back(p, bytes);

@@ -42,6 +42,7 @@ struct wl_ctx {
   // given back, as is d_work, by wl_destroy and when an allocation of any
   // context on the device fails (also one of a server's thread, hence the lock)
   std::vector<std::pair<void*, size_t>> ens_cache;
+  size_t cache_asked = 0;  // bytes held when the free memory was last asked for
   std::mutex cache_mu;
   // device address of the allocation-free entry point's static scratch
   // array on this context's device (nullptr if it could not be obtained;
