@@ -2270,17 +2270,44 @@ int32_t finish_threads(int32_t n_groups) {
 }
 
 // ------------------------------------------------------------ dispatch
+// SIMD cycles of a segment's walk with full wave slots, by field and precision.
+constexpr int seg_cycles(int kind, int prec) {
+  return prec == 2 ? (kind == kConst ? 60 : kind == kSech2 ? 300 : kind == kGauss ? 190 : 95)
+                   : (kind == kConst ? 17 : kind == kSech2 ? 73 : kind == kGauss ? 55 : 35);
+}
+
 // Over how many waves the loops of an item are dealt, the waves of its
-// workgroup: one per loop, at most 8.  Measured over 1 to 16 waves, rows of
-// 1 to 32 loops and 32 to 131072 items, 8 is the fastest or within 1% of it
-// wherever a row has 8 loops, also where it leaves waves idle in a last
-// round (9 loops, 4096 items of 1024 segments: 1.38 ms, with 3 waves 1.50,
-// with 1 1.72): workgroups of whole multiples of 4 waves load the 4 SIMDs
-// evenly, and many short workgroups even out the chunks' unequal costs.  The
-// sums do not depend on the split.  A grid whose threads would not fit 32
+// workgroup: at most 8, one per loop at least.  Long walks take 8, the fastest
+// or within 1% of it over 1 to 16 waves, rows of 1 to 32 loops and 32 to 131072
+// items: whole multiples of 4 waves load the 4 SIMDs evenly, and many short
+// workgroups even out the chunks' unequal costs.  But the exchange of the terms
+// costs about 100, 190 and 480 cycles per loop with 2, 4 and 8 waves, which a
+// short walk feels, so that it takes the fewest waves that still fill the wave
+// slots (8192; four times over where the walk is not the smaller part, so that the
+// last round is not part-empty).  Time over that of a wave per item in step with
+// others, 86016 items, 1, 4 and 8 waves:
+//   constant, 16 points  0.89 1.18 1.54   sech^2, 16 points  0.98 1.05 1.18
+//   constant, 64         0.88 1.05 1.36   sech^2, 64         0.99 1.01 1.05
+//   constant, 256        0.93 0.87 0.91   sech^2, 256        0.97 0.92 0.93
+// and where 1024 items of 40 12-point loops are few, sech^2 with 2 waves 52 us,
+// with 8 41.  Rows whose last round of 8 leaves many waves idle take 4, but for
+// k_average on the fields whose walk costs much (rows of 9 loops of 1000 points,
+// 4 and 8 waves: constant FP64 1.20 and 1.39 ms, its discretisation 1.37 and 1.90,
+// rational 1.69 and 2.23; sech^2 FP64 5.32 and 5.02).
+// The sums do not depend on the split.  A grid whose threads would not fit 32
 // bits takes fewer waves.
-int32_t loop_split(const Sched& sc) {
-  int64_t s = sc.loops_per_sub < kSplitWaves ? sc.loops_per_sub : kSplitWaves;
+int32_t loop_split(const Sched& sc, int32_t n_ppl, int kind, int prec, bool disc) {
+  const int64_t walk = (int64_t)n_ppl * seg_cycles(kind, prec) + 400;  // and its epilogue
+  int64_t most = kSplitWaves;
+  if (walk < 25000) {
+    const int64_t fill = walk < 2000 ? 8192 : 32768;
+    most = walk < 10000 ? 1 : 4;
+    while (most < kSplitWaves && sc.n_items * most < fill) most *= 2;
+  }
+  const int64_t turns = (sc.loops_per_sub + 7) / 8 * 8;
+  const bool uneven = sc.loops_per_sub > 8 && 100 * turns > 125 * sc.loops_per_sub;
+  if (most == 8 && uneven && (disc || kind == kConst || kind == kRational)) most = 4;
+  int64_t s = sc.loops_per_sub < most ? sc.loops_per_sub : most;
   while (s > 1 && sc.n_items * s > ((int64_t)1 << 25)) s >>= 1;
   return (int32_t)s;
 }
@@ -2298,7 +2325,7 @@ hipError_t launch_avg_t(const FieldArgs& f, const float4* seg, const double4* se
   if ((PREC == 2 ? seg64 == nullptr : seg == nullptr) || norm == nullptr)
     return hipErrorInvalidValue;
   Sched s = s0;
-  s.split = loop_split(s);
+  s.split = loop_split(s, n_ppl, KIND, PREC, false);
   s.n_wg = (int32_t)s.n_items;
   hipLaunchKernelGGL((k_average<KIND, SPIN, PREC>), dim3(s.n_wg), dim3(s.split * kWave),
                      split_lds_bytes(s.split), st, seg, seg64, norm, n_ppl, rho, T, n_T, n_pts,
@@ -2361,7 +2388,7 @@ hipError_t launch_disc_t(const FieldArgs& f, const float4* seg, const float4* su
                 : (sub == nullptr || (full && seg == nullptr)))
     return hipErrorInvalidValue;
   Sched s = s0;
-  s.split = loop_split(s);
+  s.split = loop_split(s, n_ppl, KIND, PREC, true);
   s.n_wg = (int32_t)s.n_items;
   hipLaunchKernelGGL((k_disc<KIND, SPIN, PREC>), dim3(s.n_wg), dim3(s.split * kWave),
                      split_lds_bytes(s.split), st, seg, sub, seg64, sub64, n_ppl, rho, T, n_T,

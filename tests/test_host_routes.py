@@ -65,3 +65,37 @@ for kind in range(4):
     walk = any("k_walkI" in c for c in calls())
     assert walk == (kind in kinds) and walk != any("k_average" in c for c in calls()), kind
 """ % ((n_ppl, per, G, n_rho, n_T, kinds),))
+
+
+SPLIT = [
+    # n_ppl, loops per group, groups, n_rho, n_T, then the waves of a workgroup in
+    # FP64: k_average and k_disc in the constant field, the same in sech^2
+    (2048, 64, 64, 32, 32, 8, 8, 8, 8),      # long walks
+    (1000, 85, 24, 40, 33, 4, 4, 8, 4),      # rows of 9
+    (1000, 5, 24, 8, 8, 5, 5, 5, 5), (1000, 1, 24, 8, 8, 1, 1, 1, 1),
+    (256, 128, 64, 40, 33, 4, 4, 8, 8),      # 21504 items
+    (128, 256, 64, 40, 33, 1, 1, 8, 8), (64, 512, 64, 40, 33, 1, 1, 4, 4),
+    (16, 1024, 64, 40, 33, 1, 1, 1, 1), (16, 64, 64, 16, 16, 4, 4, 8, 8),  # 2048 items
+    (12, 2496, 8, 9, 9, 8, 8, 8, 8), (8, 1, 64, 16, 16, 1, 1, 1, 1),
+]
+
+
+@pytest.mark.parametrize("n_ppl,per,G,n_rho,n_T,ca,cd,sa,sd", SPLIT)
+def test_waves_of_an_item(n_ppl, per, G, n_rho, n_T, ca, cd, sa, sd):
+    fake_hip.run("""
+n_ppl, per, G, n_rho, n_T, ca, cd, sa, sd = %r
+ctx = wl.wl_create(0, 0x1000)
+ens = wl.wl_ensemble_upload(ctx, np.ones((per * G, n_ppl), np.float32),
+                            np.ones((per * G, n_ppl), np.float32), G)
+rho, T = np.linspace(0, 4, n_rho), np.geomspace(1e-2, 20, n_T)
+def waves(name):
+    return [int(c.split("x")[-1]) // 64 for c in calls() if name in c][0]
+for kind, want, disc in ((0, ca, cd), (1, sa, sd)):
+    clear()
+    wl.wl_average(ctx, ens, wl.field(kind, 2.0, 1.2), rho, T, 1, wl.WL_FP64)
+    assert waves("k_average") == want, (kind, waves("k_average"))
+    if n_ppl %% 4 == 0:
+        clear()
+        wl.wl_discretisation(ctx, ens, wl.field(kind, 2.0, 1.2), rho, T, 1, wl.WL_FP64)
+        assert waves("k_disc") == disc, (kind, waves("k_disc"))
+""" % ((n_ppl, per, G, n_rho, n_T, ca, cd, sa, sd),))
