@@ -2292,9 +2292,11 @@ constexpr int seg_cycles(int kind, int prec) {
 //   constant, 256        0.93 0.87 0.91   sech^2, 256        0.97 0.92 0.93
 // and where 1024 items of 40 12-point loops are few, sech^2 with 2 waves 52 us,
 // with 8 41.  Rows whose last round of 8 leaves many waves idle take 4, but for
-// k_average on the fields whose walk costs much (rows of 9 loops of 1000 points,
-// 4 and 8 waves: constant FP64 1.20 and 1.39 ms, its discretisation 1.37 and 1.90,
-// rational 1.69 and 2.23; sech^2 FP64 5.32 and 5.02).
+// the walks that cost most (rows of 9 loops of 1000 points, 4 and 8 waves:
+// constant FP64 1.20 and 1.39 ms, its discretisation 1.37 and 1.90, rational 1.69
+// and 2.23, the Gaussian's 3.48 and 3.63; sech^2 FP64 5.32 and 5.02, its
+// discretisation 5.19 and 5.08; k_average of sech^2 and Gaussian in FP32C 1.57 and
+// 1.51, 1.13 and 1.12).
 // The sums do not depend on the split.  A grid whose threads would not fit 32
 // bits takes fewer waves.
 int32_t loop_split(const Sched& sc, int32_t n_ppl, int kind, int prec, bool disc) {
@@ -2307,7 +2309,8 @@ int32_t loop_split(const Sched& sc, int32_t n_ppl, int kind, int prec, bool disc
   }
   const int64_t turns = (sc.loops_per_sub + 7) / 8 * 8;
   const bool uneven = sc.loops_per_sub > 8 && 100 * turns > 125 * sc.loops_per_sub;
-  if (most == 8 && uneven && (disc || kind == kConst || kind == kRational)) most = 4;
+  const bool cheap = kind == kConst || kind == kRational;
+  if (most == 8 && uneven && (cheap || (disc && !(kind == kSech2 && prec == 2)))) most = 4;
   int64_t s = sc.loops_per_sub < most ? sc.loops_per_sub : most;
   while (s > 1 && sc.n_items * s > ((int64_t)1 << 25)) s >>= 1;
   return (int32_t)s;

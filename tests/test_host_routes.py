@@ -71,7 +71,7 @@ SPLIT = [
     # n_ppl, loops per group, groups, n_rho, n_T, then the waves of a workgroup in
     # FP64: k_average and k_disc in the constant field, the same in sech^2
     (2048, 64, 64, 32, 32, 8, 8, 8, 8),      # long walks
-    (1000, 85, 24, 40, 33, 4, 4, 8, 4),      # rows of 9
+    (1000, 85, 24, 40, 33, 4, 4, 8, 8),      # rows of 9
     (1000, 5, 24, 8, 8, 5, 5, 5, 5), (1000, 1, 24, 8, 8, 1, 1, 1, 1),
     (256, 128, 64, 40, 33, 4, 4, 8, 8),      # 21504 items
     (128, 256, 64, 40, 33, 1, 1, 8, 8), (64, 512, 64, 40, 33, 1, 1, 4, 4),
